@@ -78,22 +78,10 @@ def tile_floors(w) -> dict:
     return {"mfma_us": mfma, "valu_us": valu, "vector_memory_us": vmem}
 
 
-def raw_tiles(w) -> bool:
-    """The forward's tile pass reads K/V tiles from the rows themselves
-    (bfloat16, float32 with d <= 64); for float32 with d = 128 pooling also
-    writes a packed copy of K and V."""
-    return w.dtype == "bf16" or w.d <= 64
-
-
-def pool_bytes(w, packed=None) -> float:
-    """Pooling pass: Q, K, V read once and the pooled rows written; in the
-    forward for float32 (packed=None follows the forward) K and V are written
-    once more in matrix-core operand order."""
+def pool_bytes(w) -> float:
+    """Pooling pass: Q, K, V read once and the pooled rows written."""
     e = 2 if w.dtype == "bf16" else 4
-    if packed is None:
-        packed = not raw_tiles(w)
-    copies = 5 if packed else 3
-    return copies * w.B * w.H * w.n * w.d * e + 3 * w.B * w.H * w.nb * w.d * 4
+    return 3 * w.B * w.H * w.n * w.d * e + 3 * w.B * w.H * w.nb * w.d * 4
 
 
 TILE_SOURCES = ["paper_2207_10284_amd/csrc/tile.hip", "paper_2207_10284_amd/csrc/tile_ops.h",
@@ -320,7 +308,7 @@ def workload_line(w, ops, steps, warmup, cpu):
             "forward_us": ms * 1e3, "tokens_per_s": w.B * w.n / (ms * 1e-3),
             "tile_us": tile_ms * 1e3, "tile_frac_of_peak": tile_flops(w) / (tile_ms * 1e-3) / 1e12 / peak,
             "tile_peak_tflops": peak,
-            "pool_frac_of_hbm": pool_bytes(w, packed=False) / (pool_ms * 1e-3) / 1e9 / PEAK_HBM_GBS}
+            "pool_frac_of_hbm": pool_bytes(w) / (pool_ms * 1e-3) / 1e9 / PEAK_HBM_GBS}
     if cpu:
         torch.cuda.synchronize()
         out_h = out.float().cpu().numpy()
@@ -447,7 +435,7 @@ def main():
     select_gbs = select_bytes(w) / (select_ms * 1e-3) / 1e9
     tflops = tile_flops(w) / (tile_ms * 1e-3) / 1e12
     peak = PEAK_BF16_TFLOPS if w.dtype == "bf16" else PEAK_F32_TFLOPS
-    pool_gbs = pool_bytes(w, packed=False) / (pool_ms * 1e-3) / 1e9
+    pool_gbs = pool_bytes(w) / (pool_ms * 1e-3) / 1e9
 
     res = {
         "metric": "MRA-2 attention fwd tokens/s at n=4096,d=64 bf16; % MFMA peak on tile path",
@@ -467,7 +455,7 @@ def main():
                       "coarse_scores_stepwise": coarse_ms * 1e3},
         "tile_floors": tile_floors(w),
         "pool_roofline": {"bound": "hbm", "achieved": pool_gbs, "peak": PEAK_HBM_GBS, "unit": "GB/s",
-                          "frac": pool_gbs / PEAK_HBM_GBS, "bytes_per_launch": pool_bytes(w, packed=False)},
+                          "frac": pool_gbs / PEAK_HBM_GBS, "bytes_per_launch": pool_bytes(w)},
         # the step-wise selection alone (the forward fuses it with the coarse
         # logits and the coarse term, so S~ never reaches HBM there). A
         # per-row radix search whose time is its latency, not its bytes: the

@@ -39,8 +39,8 @@
  *   arguments and returns MRA_OK without touching any pointer.
  * - Q/K/V/output element type is `dtype` (float32 or bfloat16). Pooled rows,
  *   coarse logits and the coarse term are float32. Fine products accumulate in
- *   float32 (bfloat16 inputs feed bfloat16 matrix-core products); coarse
- *   logits accumulate in float64 and are rounded once to float32.
+ *   float32 (bfloat16 inputs feed bfloat16 matrix-core products; float32
+ *   operands enter as sums of three bfloat16 values); coarse logits accumulate in float64 and are rounded once to float32.
  * - The scale c = 1/sqrt(d) is applied to both the fine and the coarse logits.
  * - Results for non-finite inputs are unspecified.
  *
@@ -185,18 +185,16 @@ mra_status_t mra_block_sddmm_spmm(const void* q, const void* k, const void* v,
  * mra_forward_workspace_bytes — bytes of device workspace mra_attention_forward
  * needs for these sizes and dtype: pooled rows, the selection and the coarse
  * term (B*H*(n/32)*(4d + budget + 2)*4 bytes, each part rounded up to 256),
- * plus, for float32 inputs, copies of K and V rearranged into matrix-core
- * operand order (2*B*H*n*d*elem bytes; bfloat16 tiles are read straight
- * from K and V). Returns 0 for invalid or unsupported arguments.
+ * plus, for float32 inputs with d = 128, a reserved part of 2*B*H*n*d*4 bytes
+ * (the tile pass reads K and V themselves for every dtype and d). Returns 0
+ * for invalid or unsupported arguments.
  */
 size_t mra_forward_workspace_bytes(int B, int H, int n, int d, int block, int budget,
                                    mra_dtype_t dtype);
 
 /*
- * mra_attention_forward — the whole MRA-2 forward pass: pooling (which, for
- * float32 inputs and d = 128, also rearranges K and V for the tile pass),
- * coarse logits with
- * selection and coarse term fused (the logits never leave on-chip memory),
+ * mra_attention_forward — the whole MRA-2 forward pass: pooling, coarse logits
+ * with selection and coarse term fused (the logits never leave on-chip memory),
  * then the tile pass. Results are bit-identical to the calls above made in
  * order (mra_pool, mra_coarse_scores, mra_select, mra_coarse_term,
  * mra_block_sddmm_spmm).
@@ -390,9 +388,9 @@ mra_status_t mra_attention_forward_levels(const void* q, const void* k, const vo
 
 /*
  * mra_backward_workspace_bytes — device workspace of mra_attention_backward:
- * for float32 seven rearranged copies of Q, K, V and dZ (7*B*H*n*d*4 bytes;
- * the bfloat16 gradient passes read the inputs' rows and instead take 16
- * bytes per query of bias operands), pooled rows and their gradients, two
+ * for float32 7*B*H*n*d*4 bytes (Q, K, V and dZ as three bfloat16 planes each,
+ * 24 of the 28 bytes; the bfloat16 gradient passes read the inputs' rows and
+ * instead take 16 bytes per query of bias operands), pooled rows and their gradients, two
  * float32 values per query, the selection as a bitmap and two float32
  * nb x nb grids per head (W and dS~ below). 0 for
  * invalid or unsupported arguments.

@@ -99,26 +99,20 @@ mra_status_t debug_fill(const Fill (&f)[N], void* stream) {
 }
 
 struct WsLayout {
-  size_t qp, kp, vp, kvpacked, idx, cmax, csum, cvec, total;
+  size_t qp, kp, vp, idx, cmax, csum, cvec, total;
 };
 
 size_t align256(size_t x) { return (x + 255) & ~size_t(255); }
-
-// The forward's tile pass reads K/V tiles straight from their rows (bfloat16,
-// and float32 with d <= 64); float32 tiles of d = 128 need the copy in
-// matrix-core operand order that the pooling pass writes.
-bool raw_tiles(int d, mra_dtype_t dtype) { return dtype == MRA_BF16 || d <= 64; }
 
 WsLayout ws_layout(long long bh, int nb, int d, int m, mra_dtype_t dtype) {
   WsLayout L{};
   size_t off = 0;
   const size_t pooled = align256((size_t)bh * nb * d * sizeof(float));
-  const size_t elem = dtype == MRA_BF16 ? 2 : 4;
   L.qp = off; off += pooled;
   L.kp = off; off += pooled;
   L.vp = off; off += pooled;
-  L.kvpacked = off;
-  if (!raw_tiles(d, dtype)) off += align256((size_t)2 * bh * nb * kBlockSize * d * elem);
+  // reserved: part of the size that callers of float32, d = 128 have always given
+  if (dtype == MRA_F32 && d == 128) off += align256((size_t)2 * bh * nb * kBlockSize * d * sizeof(float));
   L.idx = off; off += align256((size_t)bh * nb * m * sizeof(int32_t));
   L.cmax = off; off += align256((size_t)bh * nb * sizeof(float));
   L.csum = off; off += align256((size_t)bh * nb * sizeof(float));
@@ -151,7 +145,7 @@ mra_status_t check_global_budget(const Shape& s, int budget, int prior_diagonal)
 
 // Workspace of the gradient pass (pointer roles in kernels.h, BwdArgs).
 struct WsBwd {
-  size_t qp, kp, vp, q_row, q_t, k_row, k_t, v_row, g_row, g_t, ld, bias, bits, gh, W, dS, dqp,
+  size_t qp, kp, vp, q_pl, k_pl, v_pl, g_pl, ld, bias, bits, gh, W, dS, dqp,
       dkp, dvp, total;
 };
 
@@ -159,20 +153,19 @@ WsBwd ws_bwd(long long bh, int nb, int d, mra_dtype_t dtype) {
   WsBwd L{};
   size_t off = 0;
   const size_t pooled = align256((size_t)bh * nb * d * sizeof(float));
-  // packed operand copies: float32 only (bfloat16 passes read raw tiles)
+  // the planes of Q, K, V and dZ: float32 only (bfloat16 passes read raw
+  // tiles), 24 of the 28 bytes per element that the size counts
   const bool raw = dtype == MRA_BF16;
-  const size_t packed = raw ? 0 : align256((size_t)bh * nb * kBlockSize * d * (dtype == MRA_BF16 ? 2 : 4));
+  const size_t elems = raw ? 0 : (size_t)bh * nb * kBlockSize * d;
   const size_t grid = align256((size_t)bh * nb * nb * sizeof(float));
   L.qp = off; off += pooled;
   L.kp = off; off += pooled;
   L.vp = off; off += pooled;
-  L.q_row = off; off += packed;
-  L.q_t = off; off += packed;
-  L.k_row = off; off += packed;
-  L.k_t = off; off += packed;
-  L.v_row = off; off += packed;
-  L.g_row = off; off += packed;
-  L.g_t = off; off += packed;
+  L.q_pl = off;
+  L.k_pl = off + 6 * elems;
+  L.v_pl = off + 12 * elems;
+  L.g_pl = off + 18 * elems;
+  off += 7 * align256(4 * elems);
   L.ld = off; off += align256((size_t)bh * nb * 64 * sizeof(float));
   L.bias = off; off += raw ? align256((size_t)bh * nb * kBlockSize * 16) : 0;
   L.bits = off; off += align256((size_t)bh * nb * ((nb + 31) / 32) * sizeof(uint32_t));
@@ -280,7 +273,6 @@ mra_status_t levels_forward(const void* q, const void* k, const void* v, void* o
   auto f32 = [&](size_t off) { return reinterpret_cast<float*>(ws + off); };
   const int nb = s.nb, fin = levels - 1;
   float *qp = f32(L.qp), *kp = f32(L.kp), *vp = f32(L.vp), *S = f32(W.S_fine);
-  void* kvpacked = raw_tiles(d, dtype) ? nullptr : ws + L.kvpacked;
   float *cmax = f32(L.cmax), *csum = f32(L.csum), *cvec = f32(L.cvec);
   hipStream_t st = static_cast<hipStream_t>(stream);
   mra::LevelTerm T{};
@@ -307,7 +299,7 @@ mra_status_t levels_forward(const void* q, const void* k, const void* v, void* o
   for (int l = 0; l < levels; ++l) fills[3 + l] = {outs[l], (size_t)s.bh * T.nb[l] * budgets[l] * 4, kNanF32};
   MRA_TRY(debug_fill(fills, stream));
 
-  MRA_TRY(hip_status(mra::launch_pool(q, k, v, qp, kp, vp, kvpacked, s.bh, n, d, (int)dtype, st)));
+  MRA_TRY(hip_status(mra::launch_pool(q, k, v, qp, kp, vp, s.bh, n, d, (int)dtype, st)));
   for (int l = 0; l <= fin; ++l) {
     float* Sl = const_cast<float*>(T.S[l]);
     if (l < fin) {
@@ -323,7 +315,7 @@ mra_status_t levels_forward(const void* q, const void* k, const void* v, void* o
     if (budgets[l] > 0) MRA_TRY(hip_status(mra::launch_select(Sl, idx[l], s.bh, T.nb[l], budgets[l], st)));
   }
   MRA_TRY(hip_status(mra::launch_coarse_term_levels(T, cmax, csum, cvec, s.bh, d, st)));
-  return hip_status(mra::launch_tile(q, k, v, kvpacked, idx[fin], cmax, csum, cvec, out, lse_out, s.bh,
+  return hip_status(mra::launch_tile(q, k, v, idx[fin], cmax, csum, cvec, out, lse_out, s.bh,
                                      n, d, budgets[fin], (int)dtype, st));
 }
 
@@ -364,7 +356,6 @@ mra_status_t forward_enqueue(const void* q, const void* k, const void* v, void* 
   float* qp = reinterpret_cast<float*>(ws + L.qp);
   float* kp = reinterpret_cast<float*>(ws + L.kp);
   float* vp = reinterpret_cast<float*>(ws + L.vp);
-  void* kvpacked = raw_tiles(d, dtype) ? nullptr : ws + L.kvpacked;
   int32_t* idx = idx_out ? idx_out : reinterpret_cast<int32_t*>(ws + L.idx);
   float* cmax = reinterpret_cast<float*>(ws + L.cmax);
   float* csum = reinterpret_cast<float*>(ws + L.csum);
@@ -377,10 +368,10 @@ mra_status_t forward_enqueue(const void* q, const void* k, const void* v, void* 
                          {workspace, L.total, kNanF32}};
   MRA_TRY(debug_fill(fills, stream));
 
-  MRA_TRY(hip_status(launch_pool(q, k, v, qp, kp, vp, kvpacked, bh, n, d, (int)dtype, st)));
+  MRA_TRY(hip_status(launch_pool(q, k, v, qp, kp, vp, bh, n, d, (int)dtype, st)));
   MRA_TRY(hip_status(launch_select_term_fused(qp, kp, idx, vp, cmax, csum, cvec, bh, nb, d, budget,
                                               st)));
-  return hip_status(launch_tile(q, k, v, kvpacked, idx, cmax, csum, cvec, out, lse_out, bh, n, d,
+  return hip_status(launch_tile(q, k, v, idx, cmax, csum, cvec, out, lse_out, bh, n, d,
                                 budget, (int)dtype, st));
 }
 
@@ -405,7 +396,7 @@ mra_status_t mra_pool(const void* q, const void* k, const void* v, float* qp, fl
   const size_t pooled = (size_t)s.bh * s.nb * d * 4;
   const Fill fills[3] = {{qp, pooled, kNanF32}, {kp, pooled, kNanF32}, {vp, pooled, kNanF32}};
   MRA_TRY(debug_fill(fills, stream));
-  return hip_status(mra::launch_pool(q, k, v, qp, kp, vp, nullptr, s.bh, n, d, (int)dtype,
+  return hip_status(mra::launch_pool(q, k, v, qp, kp, vp, s.bh, n, d, (int)dtype,
                                      static_cast<hipStream_t>(stream)));
 }
 
@@ -485,7 +476,7 @@ mra_status_t mra_block_sddmm_spmm(const void* q, const void* k, const void* v,
   const Fill fills[2] = {{out, (size_t)s.bh * n * d * (dtype == MRA_BF16 ? 2 : 4), nan_pattern(dtype)},
                          {lse_out, (size_t)s.bh * n * 4, kNanF32}};
   MRA_TRY(debug_fill(fills, stream));
-  return hip_status(mra::launch_tile(q, k, v, nullptr, idx, cmax, csum, cvec, out, lse_out, s.bh,
+  return hip_status(mra::launch_tile(q, k, v, idx, cmax, csum, cvec, out, lse_out, s.bh,
                                      n, d, budget, (int)dtype, static_cast<hipStream_t>(stream)));
 }
 
@@ -540,7 +531,6 @@ mra_status_t mra_sparse_attention_forward(const void* q, const void* k, const vo
   float* qp = reinterpret_cast<float*>(ws + L.qp);
   float* kp = reinterpret_cast<float*>(ws + L.kp);
   float* vp = reinterpret_cast<float*>(ws + L.vp);
-  void* kvpacked = raw_tiles(d, dtype) ? nullptr : ws + L.kvpacked;
   int32_t* idx = idx_out ? idx_out : reinterpret_cast<int32_t*>(ws + L.idx);
   hipStream_t st = static_cast<hipStream_t>(stream);
   const Fill fills[4] = {{out, (size_t)s.bh * n * d * (dtype == MRA_BF16 ? 2 : 4), nan_pattern(dtype)},
@@ -549,9 +539,9 @@ mra_status_t mra_sparse_attention_forward(const void* q, const void* k, const vo
                          {workspace, L.total, kNanF32}};
   MRA_TRY(debug_fill(fills, stream));
 
-  MRA_TRY(hip_status(mra::launch_pool(q, k, v, qp, kp, vp, kvpacked, s.bh, n, d, (int)dtype, st)));
+  MRA_TRY(hip_status(mra::launch_pool(q, k, v, qp, kp, vp, s.bh, n, d, (int)dtype, st)));
   MRA_TRY(hip_status(mra::launch_select_fused(qp, kp, idx, s.bh, s.nb, d, budget, st)));
-  return hip_status(mra::launch_tile(q, k, v, kvpacked, idx, nullptr, nullptr, nullptr, out,
+  return hip_status(mra::launch_tile(q, k, v, idx, nullptr, nullptr, nullptr, out,
                                      lse_out, s.bh, n, d, budget, (int)dtype, st));
 }
 
@@ -603,7 +593,6 @@ mra_status_t mra_attention_forward_global(const void* q, const void* k, const vo
   float* qp = reinterpret_cast<float*>(ws + L.qp);
   float* kp = reinterpret_cast<float*>(ws + L.kp);
   float* vp = reinterpret_cast<float*>(ws + L.vp);
-  void* kvpacked = raw_tiles(d, dtype) ? nullptr : ws + L.kvpacked;
   int32_t* idx = idx_out ? idx_out : reinterpret_cast<int32_t*>(ws + L.idx);
   float* cmax = reinterpret_cast<float*>(ws + L.cmax);
   float* csum = reinterpret_cast<float*>(ws + L.csum);
@@ -617,11 +606,11 @@ mra_status_t mra_attention_forward_global(const void* q, const void* k, const vo
                          {workspace, G.total, kNanF32}};
   MRA_TRY(debug_fill(fills, stream));
 
-  MRA_TRY(hip_status(mra::launch_pool(q, k, v, qp, kp, vp, kvpacked, s.bh, n, d, (int)dtype, st)));
+  MRA_TRY(hip_status(mra::launch_pool(q, k, v, qp, kp, vp, s.bh, n, d, (int)dtype, st)));
   MRA_TRY(hip_status(mra::launch_coarse(qp, kp, S, s.bh, nb, d, st)));
   MRA_TRY(hip_status(mra::launch_select_global(S, idx, s.bh, nb, budget, prior_diagonal, st)));
   MRA_TRY(hip_status(mra::launch_coarse_term(S, idx, vp, cmax, csum, cvec, s.bh, nb, d, nb, st)));
-  return hip_status(mra::launch_tile(q, k, v, kvpacked, idx, cmax, csum, cvec, out, lse_out, s.bh,
+  return hip_status(mra::launch_tile(q, k, v, idx, cmax, csum, cvec, out, lse_out, s.bh,
                                      n, d, nb, (int)dtype, st));
 }
 
@@ -674,8 +663,7 @@ static mra_status_t backward(const void* q, const void* k, const void* v, const 
     A.kp = const_cast<float*>(pk);
     A.vp = const_cast<float*>(pv);
   }
-  A.q_row = ws + L.q_row; A.q_t = ws + L.q_t; A.k_row = ws + L.k_row; A.k_t = ws + L.k_t;
-  A.v_row = ws + L.v_row; A.g_row = ws + L.g_row; A.g_t = ws + L.g_t;
+  A.q_pl = ws + L.q_pl; A.k_pl = ws + L.k_pl; A.v_pl = ws + L.v_pl; A.g_pl = ws + L.g_pl;
   A.ld = f32(L.ld);
   A.bias = dtype == MRA_BF16 ? reinterpret_cast<uint32_t*>(ws + L.bias) : nullptr;
   A.bits = reinterpret_cast<uint32_t*>(ws + L.bits);

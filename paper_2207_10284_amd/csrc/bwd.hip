@@ -27,17 +27,17 @@
 //    term also G^, d^ and the row's W, dS~ and dQ~ (K~ and V~ staged through
 //    LDS 64 blocks at a time).
 //  * bwd_cols_kernel: per column block (a wave; 16 per workgroup): dK~, dV~.
-//  * bwd_dq_(stream_)kernel: per block-row (a wave), over its refined tiles: the
+//  * bwd_dq_*_kernel: per block-row (a wave, float32 a pair), over its refined tiles: the
 //    products K_y Q_x^T and V_y G_x^T on the matrix cores, then
 //    dQ^T += K_y^T dP^T.
-//  * bwd_dkdv_(stream_)kernel: per column block (a wave), over the block-rows that
+//  * bwd_dkdv_*_kernel: per column block (a wave, float32 a pair), over the block-rows that
 //    refined it (ascending): dV^T += G_x^T A, dK^T += c Q_x^T dP. For raw
 //    tiles the row pass also writes, per query, the bfloat16 triples of
 //    -L_i/c and -delta_i, which enter the products as one more contraction
 //    step, so a lane holding 16 queries needs no per-query registers.
 // Tile operands: for bfloat16 raw 32-row tiles of the inputs (copied into LDS
-// under a swizzle that serves row and transposed reads); for float32 packed
-// copies in the layouts of tile_ops.h.
+// under a swizzle that serves row and transposed reads); for float32 the same
+// tiles of three bfloat16 planes that the packing pass writes.
 #include "common.h"
 #include "kernels.h"
 #include "tile_ops.h"
@@ -268,8 +268,9 @@ __global__ __launch_bounds__(kBwdRows * kWave) __attribute__((amdgpu_waves_per_e
 // The bitmap words of kColBatch groups of 64 rows are all requested before
 // the first is used (rows past nb read row nb - 1's word and are dropped).
 constexpr int kColBatch = 8;
+template <class T>
 __device__ __forceinline__ int column_list(const uint32_t* __restrict__ bits, long long hb, int nbw, int y,
-                                           int nb, int32_t* list) {
+                                           int nb, T* list) {
   const int lane = lane_id();
   int cnt = 0;
   for (int x0 = 0; x0 < nb; x0 += kColBatch * kWave) {
@@ -284,7 +285,7 @@ __device__ __forceinline__ int column_list(const uint32_t* __restrict__ bits, lo
       const int x = x0 + kWave * u + lane;
       const bool ok = x < nb && ((wv[u] >> (y & 31)) & 1u);
       const uint64_t mk = __ballot(ok);
-      if (ok) list[cnt + bits_below(mk)] = x;
+      if (ok) list[cnt + bits_below(mk)] = (T)x;
       cnt += __popcll(mk);
     }
   }
@@ -460,475 +461,6 @@ __device__ __forceinline__ f32x16 mfma_abt_from(const u32x4 (&a)[KC], const u32x
 }
 
 // ---------------------------------------------------------------------------
-// dQ: one wave per block-row x. For each refined block y (ascending):
-// S^T = K_y Q_x^T and (V_y G_x^T) on the matrix cores (lane: query, 16 keys),
-// dP^T = e^{S^T c - L} o (V G^T - delta), dQ^T += K_y^T dP^T. The epilogue
-// scales by c and adds dQ~_x / 32. Operand loads for the next tile are issued
-// before the current tile is computed (past the last one they re-read it).
-template <int DT, int D, bool COARSE>
-__global__ __launch_bounds__(kBwdTileWaves * kWave) void bwd_dq_kernel(
-    const void* __restrict__ qin, const void* __restrict__ gin, const void* __restrict__ krow,
-    const void* __restrict__ vrow, const void* __restrict__ kt, const int32_t* __restrict__ idx,
-    const float* __restrict__ ld, const float* __restrict__ dqp, void* __restrict__ dq, int nb,
-    int m, long long rows, float scale, float scale_log2) {
-  using Cfg = TileCfg<DT, D>;
-  using elem = typename Cfg::elem;
-  constexpr int KC = Cfg::kKChunks, VC = Cfg::kVChunks, NT = Cfg::kNT;
-  extern __shared__ int32_t sidx_all[];
-  const int w = wave_uniform(threadIdx.x / kWave);
-  const int lane = lane_id(), jq = lane & 31;
-  const long long g = xcd_remap(blockIdx.x, gridDim.x) * (long long)kBwdTileWaves + w;
-  if (g >= rows) return;                                    // no workgroup barriers below
-  const long long bh = g / nb;
-  int32_t* myidx = sidx_all + w * m;
-  const int cnt = stage_selection(idx + g * m, m, nb, myidx);
-
-  u32x4 qf[KC], gf[KC];
-  load_rows<DT, D>(reinterpret_cast<const elem*>(qin) + g * 32 * D, qf);
-  load_rows<DT, D>(reinterpret_cast<const elem*>(gin) + g * 32 * D, gf);
-  const float lq = ld[g * 64 + jq], dl = ld[g * 64 + 32 + jq];
-  f32x16 acc[NT];
-#pragma unroll
-  for (int t = 0; t < NT; ++t)
-#pragma unroll
-    for (int r = 0; r < 16; ++r) acc[t][r] = 0.0f;
-
-  const u32x4* kr = reinterpret_cast<const u32x4*>(krow) + bh * nb * KC * 64 + lane;
-  const u32x4* vr = reinterpret_cast<const u32x4*>(vrow) + bh * nb * KC * 64 + lane;
-  const u32x4* ktp = reinterpret_cast<const u32x4*>(kt) + bh * nb * VC * 64 + lane;
-  struct Ops {
-    u32x4 k[KC], v[KC], t[VC];
-  };
-  auto load = [&](int y, Ops& o) {
-#pragma unroll
-    for (int c = 0; c < KC; ++c) o.k[c] = kr[((long long)y * KC + c) * 64];
-#pragma unroll
-    for (int c = 0; c < KC; ++c) o.v[c] = vr[((long long)y * KC + c) * 64];
-#pragma unroll
-    for (int c = 0; c < VC; ++c) o.t[c] = ktp[((long long)y * VC + c) * 64];
-  };
-  Ops cur, nxt;
-  if (cnt > 0) load(wave_uniform(myidx[0]), cur);
-  for (int i = 0; i < cnt; ++i) {
-    load(wave_uniform(myidx[min(i + 1, cnt - 1)]), nxt);
-    const f32x16 s = mfma_abt<DT, KC>(cur.k, qf);
-    const f32x16 pv = mfma_abt<DT, KC>(cur.v, gf);
-    float ds[16];
-#pragma unroll
-    for (int r = 0; r < 16; ++r)
-      ds[r] = __builtin_amdgcn_exp2f(fmaf(s[r], scale_log2, -lq)) * (pv[r] - dl);
-    if constexpr (DT == BF16) {
-      uint32_t pk[8];
-      pack16(ds, pk);
-      mfma_acc_bf16<NT>(acc, pk, [&](int c) { return cur.t[c]; });
-    } else {
-      mfma_acc_f32<NT>(acc, ds, [&](int c) { return cur.t[c]; });
-    }
-    cur = nxt;
-  }
-  store_block<DT, D>(reinterpret_cast<elem*>(dq) + g * 32 * D, acc, scale,
-                     COARSE ? dqp + g * D : nullptr);
-}
-
-// ---------------------------------------------------------------------------
-// dK, dV: one wave per column block y. For each block-row x whose selection
-// holds y (ascending): S = Q_x K_y^T and G_x V_y^T (lane: key, 16 queries),
-// A = e^{S c - L}, dP = A o (G V^T - delta), dV^T += G_x^T A,
-// dK^T += Q_x^T dP. The epilogue scales dK by c and adds dK~_y / 32 and
-// dV~_y / 32.
-template <int DT, int D, bool COARSE, int WAVES>
-__global__ __launch_bounds__(WAVES * kWave) void bwd_dkdv_kernel(
-    const void* __restrict__ kin, const void* __restrict__ vin, const void* __restrict__ qrow,
-    const void* __restrict__ grow, const void* __restrict__ qt, const void* __restrict__ gt,
-    const uint32_t* __restrict__ bits, const float* __restrict__ ld,
-    const float* __restrict__ dkp, const float* __restrict__ dvp, void* __restrict__ dk,
-    void* __restrict__ dv, int nb, long long rows, float scale, float scale_log2) {
-  using Cfg = TileCfg<DT, D>;
-  using elem = typename Cfg::elem;
-  constexpr int KC = Cfg::kKChunks, VC = Cfg::kVChunks, NT = Cfg::kNT;
-  extern __shared__ int32_t sidx_all[];
-  const int w = wave_uniform(threadIdx.x / kWave);
-  const int lane = lane_id(), h = lane >> 5;
-  const long long gy = xcd_remap(blockIdx.x, gridDim.x) * (long long)WAVES + w;
-  if (gy >= rows) return;                                   // no workgroup barriers below
-  const long long bh = gy / nb;
-  const int y = (int)(gy - bh * nb);
-  const long long hb = bh * nb;
-  const int nbw = (nb + 31) / 32;
-
-  // block-rows whose selection holds y, ascending
-  int32_t* myx = sidx_all + w * nb;
-  const int cnt = column_list(bits, hb, nbw, y, nb, myx);
-
-  u32x4 kf[KC], vf[KC];
-  load_rows<DT, D>(reinterpret_cast<const elem*>(kin) + gy * 32 * D, kf);
-  load_rows<DT, D>(reinterpret_cast<const elem*>(vin) + gy * 32 * D, vf);
-  f32x16 ak[NT], av[NT];
-#pragma unroll
-  for (int t = 0; t < NT; ++t)
-#pragma unroll
-    for (int r = 0; r < 16; ++r) ak[t][r] = av[t][r] = 0.0f;
-
-  const u32x4* qr = reinterpret_cast<const u32x4*>(qrow) + hb * KC * 64 + lane;
-  const u32x4* gr = reinterpret_cast<const u32x4*>(grow) + hb * KC * 64 + lane;
-  const u32x4* qtp = reinterpret_cast<const u32x4*>(qt) + hb * VC * 64 + lane;
-  const u32x4* gtp = reinterpret_cast<const u32x4*>(gt) + hb * VC * 64 + lane;
-  struct Ops {
-    u32x4 q[KC], g[KC], qt[VC], gt[VC];
-    f32x4 l[4], d[4];
-  };
-  auto load = [&](int x, Ops& o) {
-#pragma unroll
-    for (int c = 0; c < KC; ++c) o.q[c] = qr[((long long)x * KC + c) * 64];
-#pragma unroll
-    for (int c = 0; c < KC; ++c) o.g[c] = gr[((long long)x * KC + c) * 64];
-#pragma unroll
-    for (int c = 0; c < VC; ++c) o.qt[c] = qtp[((long long)x * VC + c) * 64];
-#pragma unroll
-    for (int c = 0; c < VC; ++c) o.gt[c] = gtp[((long long)x * VC + c) * 64];
-    // queries 8rg + 4h + e of block-row x (the rows of this lane's registers)
-    const float* lx = ld + (hb + x) * 64 + 4 * h;
-    const float* dx = lx + 32;
-#pragma unroll
-    for (int rg = 0; rg < 4; ++rg) {
-      o.l[rg] = *reinterpret_cast<const f32x4*>(lx + 8 * rg);
-      o.d[rg] = *reinterpret_cast<const f32x4*>(dx + 8 * rg);
-    }
-  };
-  Ops cur, nxt;
-  if (cnt > 0) load(wave_uniform(myx[0]), cur);
-  for (int i = 0; i < cnt; ++i) {
-    load(wave_uniform(myx[min(i + 1, cnt - 1)]), nxt);
-    const f32x16 s = mfma_abt<DT, KC>(cur.q, kf);
-    const f32x16 pv = mfma_abt<DT, KC>(cur.g, vf);
-    float a[16], ds[16];
-#pragma unroll
-    for (int r = 0; r < 16; ++r) {
-      a[r] = __builtin_amdgcn_exp2f(fmaf(s[r], scale_log2, -cur.l[r / 4][r % 4]));
-      ds[r] = a[r] * (pv[r] - cur.d[r / 4][r % 4]);
-    }
-    if constexpr (DT == BF16) {
-      uint32_t pa[8], pd[8];
-      pack16(a, pa);
-      pack16(ds, pd);
-      mfma_acc_bf16<NT>(av, pa, [&](int c) { return cur.gt[c]; });
-      mfma_acc_bf16<NT>(ak, pd, [&](int c) { return cur.qt[c]; });
-    } else {
-      mfma_acc_f32<NT>(av, a, [&](int c) { return cur.gt[c]; });
-      mfma_acc_f32<NT>(ak, ds, [&](int c) { return cur.qt[c]; });
-    }
-    cur = nxt;
-  }
-  store_block<DT, D>(reinterpret_cast<elem*>(dk) + gy * 32 * D, ak, scale,
-                     COARSE ? dkp + gy * D : nullptr);
-  store_block<DT, D>(reinterpret_cast<elem*>(dv) + gy * 32 * D, av, 1.0f,
-                     COARSE ? dvp + gy * D : nullptr);
-}
-
-// ---------------------------------------------------------------------------
-// Streaming forms of the two tile passes (tiles whose chunks fit the load's
-// immediate offset: bf16 d <= 64, f32 d = 32). A wave's next tile is copied
-// HBM/L2 -> LDS with direct-to-LDS loads while the current one is computed.
-// Each wave owns a slot split into parts that are consumed at different
-// times (separate LDS objects, so reading one part does not wait for loads in
-// flight into another); a part is refilled with the next tile's operands as
-// soon as it has been read into registers. Loads complete in issue order, so
-// "part P of tile i has landed" is a wait until at most the number of loads
-// issued after it are outstanding.
-template <int N>
-__device__ __forceinline__ void wait_loads() {
-  asm volatile("s_waitcnt vmcnt(%0)" ::"n"(N) : "memory");
-}
-
-// dQ, one wave per block-row. Part A: K_y and V_y in the row layout (the
-// products with Q_x and G_x); part B: K_y in the transposed layout.
-template <int DT, int D, bool COARSE, int WAVES>
-__global__ __launch_bounds__(WAVES * kWave) void bwd_dq_stream_kernel(
-    const void* __restrict__ qin, const void* __restrict__ gin, const void* __restrict__ krow,
-    const void* __restrict__ vrow, const void* __restrict__ kt, const int32_t* __restrict__ idx,
-    const float* __restrict__ ld, const float* __restrict__ dqp, void* __restrict__ dq, int nb,
-    int m, long long rows, float scale, float scale_log2) {
-  using Cfg = TileCfg<DT, D>;
-  using elem = typename Cfg::elem;
-  constexpr int KC = Cfg::kKChunks, VC = Cfg::kVChunks, NT = Cfg::kNT;
-  constexpr int NA = 2 * KC, NB = VC;                      // loads per part
-  static_assert(KC <= 4 && VC <= 4, "chunk offsets fit the immediate field");
-  __shared__ __attribute__((aligned(16))) u32x4 partA[WAVES][NA * 64];
-  __shared__ __attribute__((aligned(16))) u32x4 partB[WAVES][NB * 64];
-  extern __shared__ int32_t sidx_all[];
-  const int w = wave_uniform(threadIdx.x / kWave);
-  const int lane = lane_id(), jq = lane & 31;
-  const long long g = xcd_remap(blockIdx.x, gridDim.x) * (long long)WAVES + w;
-  if (g >= rows) return;                                    // no workgroup barriers below
-  const long long bh = g / nb;
-  int32_t* myidx = sidx_all + w * m;
-  const int cnt = stage_selection(idx + g * m, m, nb, myidx);
-
-  u32x4 qf[KC], gf[KC];
-  load_rows<DT, D>(reinterpret_cast<const elem*>(qin) + g * 32 * D, qf);
-  load_rows<DT, D>(reinterpret_cast<const elem*>(gin) + g * 32 * D, gf);
-  const float lq = ld[g * 64 + jq], dl = ld[g * 64 + 32 + jq];
-  f32x16 acc[NT];
-#pragma unroll
-  for (int t = 0; t < NT; ++t)
-#pragma unroll
-    for (int r = 0; r < 16; ++r) acc[t][r] = 0.0f;
-
-  const unsigned loff = lane * 16u;
-  const char* ks = static_cast<const char*>(krow) + (size_t)bh * nb * KC * 1024 + loff;
-  const char* vs = static_cast<const char*>(vrow) + (size_t)bh * nb * KC * 1024 + loff;
-  const char* ts = static_cast<const char*>(kt) + (size_t)bh * nb * VC * 1024 + loff;
-  const lptr_t la = (lptr_t)partA[w];
-  const lptr_t lb = (lptr_t)partB[w];
-  const uint32_t aA = lds_addr(partA[w]) + loff, aB = lds_addr(partB[w]) + loff;
-  auto issueA = [&](int y) {
-    load_chunks_lds<KC>((gptr_t)(ks + (size_t)y * KC * 1024), la);
-    load_chunks_lds<KC>((gptr_t)(vs + (size_t)y * KC * 1024), la + KC * 1024);
-  };
-  auto issueB = [&](int y) { load_chunks_lds<VC>((gptr_t)(ts + (size_t)y * VC * 1024), lb); };
-  if (cnt > 0) {
-    const int y0 = wave_uniform(myidx[0]);
-    issueA(y0);
-    issueB(y0);
-  }
-  for (int i = 0; i < cnt; ++i) {
-    const bool more = i + 1 < cnt;                          // wave-uniform
-    const int yn = more ? wave_uniform(myidx[i + 1]) : 0;
-    wait_loads<NB>();                                       // A(i) landed; B(i) may not have
-    u32x4 kf[KC], vf[KC];
-    lds_read_chunks<KC>(aA, kf);
-    lds_read_chunks<KC, KC>(aA, vf);
-    lds_done(kf);
-    lds_done(vf);
-    if (more) issueA(yn);
-    const f32x16 s = mfma_abt<DT, KC>(kf, qf);
-    const f32x16 pv = mfma_abt<DT, KC>(vf, gf);
-    float ds[16];
-#pragma unroll
-    for (int r = 0; r < 16; ++r)
-      ds[r] = __builtin_amdgcn_exp2f(fmaf(s[r], scale_log2, -lq)) * (pv[r] - dl);
-    if (more) wait_loads<NA>();                             // B(i) landed; A(i+1) may not have
-    else wait_loads<0>();
-    u32x4 tf[VC];
-    lds_read_chunks<VC>(aB, tf);
-    lds_done(tf);
-    if (more) issueB(yn);
-    if constexpr (DT == BF16) {
-      uint32_t pk[8];
-      pack16(ds, pk);
-      mfma_acc_bf16<NT>(acc, pk, [&](int c) { return tf[c]; });
-    } else {
-      mfma_acc_f32<NT>(acc, ds, [&](int c) { return tf[c]; });
-    }
-  }
-  store_block<DT, D>(reinterpret_cast<elem*>(dq) + g * 32 * D, acc, scale,
-                     COARSE ? dqp + g * D : nullptr);
-}
-
-// dK, dV, one wave per column block. Part A: Q_x and G_x in the row layout;
-// part X: block-row x's record (log normalisers and deltas, 256 bytes, one
-// dword per lane); part B: Q_x and G_x in the transposed layout.
-template <int DT, int D, bool COARSE, int WAVES>
-__global__ __launch_bounds__(WAVES * kWave) void bwd_dkdv_stream_kernel(
-    const void* __restrict__ kin, const void* __restrict__ vin, const void* __restrict__ qrow,
-    const void* __restrict__ grow, const void* __restrict__ qt, const void* __restrict__ gt,
-    const uint32_t* __restrict__ bits, const float* __restrict__ ld,
-    const float* __restrict__ dkp, const float* __restrict__ dvp, void* __restrict__ dk,
-    void* __restrict__ dv, int nb, long long rows, float scale, float scale_log2) {
-  using Cfg = TileCfg<DT, D>;
-  using elem = typename Cfg::elem;
-  constexpr int KC = Cfg::kKChunks, VC = Cfg::kVChunks, NT = Cfg::kNT;
-  constexpr int NA = 2 * KC, NX = 1, NB = 2 * VC;          // loads per part
-  static_assert(KC <= 4 && VC <= 4, "chunk offsets fit the immediate field");
-  __shared__ __attribute__((aligned(16))) u32x4 partA[WAVES][NA * 64];
-  __shared__ __attribute__((aligned(16))) u32x4 partB[WAVES][NB * 64];
-  __shared__ __attribute__((aligned(16))) float partX[WAVES][64];
-  extern __shared__ int32_t sidx_all[];
-  const int w = wave_uniform(threadIdx.x / kWave);
-  const int lane = lane_id(), h = lane >> 5;
-  const long long gy = xcd_remap(blockIdx.x, gridDim.x) * (long long)WAVES + w;
-  if (gy >= rows) return;                                   // no workgroup barriers below
-  const long long bh = gy / nb;
-  const int y = (int)(gy - bh * nb);
-  const long long hb = bh * nb;
-  const int nbw = (nb + 31) / 32;
-
-  // block-rows whose selection holds y, ascending
-  int32_t* myx = sidx_all + w * nb;
-  const int cnt = column_list(bits, hb, nbw, y, nb, myx);
-
-  u32x4 kf[KC], vf[KC];
-  load_rows<DT, D>(reinterpret_cast<const elem*>(kin) + gy * 32 * D, kf);
-  load_rows<DT, D>(reinterpret_cast<const elem*>(vin) + gy * 32 * D, vf);
-  f32x16 ak[NT], av[NT];
-#pragma unroll
-  for (int t = 0; t < NT; ++t)
-#pragma unroll
-    for (int r = 0; r < 16; ++r) ak[t][r] = av[t][r] = 0.0f;
-
-  const unsigned loff = lane * 16u;
-  const char* qs = static_cast<const char*>(qrow) + (size_t)hb * KC * 1024 + loff;
-  const char* gs = static_cast<const char*>(grow) + (size_t)hb * KC * 1024 + loff;
-  const char* qts = static_cast<const char*>(qt) + (size_t)hb * VC * 1024 + loff;
-  const char* gts = static_cast<const char*>(gt) + (size_t)hb * VC * 1024 + loff;
-  const char* xs = reinterpret_cast<const char*>(ld + hb * 64) + lane * 4u;
-  const lptr_t la = (lptr_t)partA[w];
-  const lptr_t lb = (lptr_t)partB[w];
-  const lptr_t lx = (lptr_t)partX[w];
-  const uint32_t aA = lds_addr(partA[w]) + loff, aB = lds_addr(partB[w]) + loff;
-  const uint32_t aX = lds_addr(partX[w]) + 16u * h;          // this half's queries
-  auto issueA = [&](int x) {
-    load_chunks_lds<KC>((gptr_t)(qs + (size_t)x * KC * 1024), la);
-    load_chunks_lds<KC>((gptr_t)(gs + (size_t)x * KC * 1024), la + KC * 1024);
-  };
-  auto issueX = [&](int x) { __builtin_amdgcn_global_load_lds((gptr_t)(xs + (size_t)x * 256), lx, 4, 0, 0); };
-  auto issueB = [&](int x) {
-    load_chunks_lds<VC>((gptr_t)(qts + (size_t)x * VC * 1024), lb);
-    load_chunks_lds<VC>((gptr_t)(gts + (size_t)x * VC * 1024), lb + VC * 1024);
-  };
-  if (cnt > 0) {
-    const int x0 = wave_uniform(myx[0]);
-    issueA(x0);
-    issueX(x0);
-    issueB(x0);
-  }
-  for (int i = 0; i < cnt; ++i) {
-    const bool more = i + 1 < cnt;                          // wave-uniform
-    const int xn = more ? wave_uniform(myx[i + 1]) : 0;
-    wait_loads<NX + NB>();                                  // A(i) landed
-    u32x4 qa[KC], ga[KC];
-    lds_read_chunks<KC>(aA, qa);
-    lds_read_chunks<KC, KC>(aA, ga);
-    lds_done(qa);
-    lds_done(ga);
-    if (more) issueA(xn);
-    const f32x16 s = mfma_abt<DT, KC>(qa, kf);             // lane: key, 16 queries
-    const f32x16 pv = mfma_abt<DT, KC>(ga, vf);
-    if (more) wait_loads<NB + NA>();                        // X(i) landed
-    else wait_loads<NB>();
-    u32x4 xr[8];                                            // queries 8rg + 4h + e
-    xr[0] = lds_read16<0>(aX);
-    xr[1] = lds_read16<32>(aX);
-    xr[2] = lds_read16<64>(aX);
-    xr[3] = lds_read16<96>(aX);
-    xr[4] = lds_read16<128>(aX);
-    xr[5] = lds_read16<160>(aX);
-    xr[6] = lds_read16<192>(aX);
-    xr[7] = lds_read16<224>(aX);
-    lds_done(xr);
-    if (more) issueX(xn);
-    f32x4 lq[4], dl[4];
-#pragma unroll
-    for (int rg = 0; rg < 4; ++rg) {
-      lq[rg] = __builtin_bit_cast(f32x4, xr[rg]);
-      dl[rg] = __builtin_bit_cast(f32x4, xr[4 + rg]);
-    }
-    float a[16], ds[16];
-#pragma unroll
-    for (int r = 0; r < 16; ++r) {
-      a[r] = __builtin_amdgcn_exp2f(fmaf(s[r], scale_log2, -lq[r / 4][r % 4]));
-      ds[r] = a[r] * (pv[r] - dl[r / 4][r % 4]);
-    }
-    if (more) wait_loads<NA + NX>();                        // B(i) landed
-    else wait_loads<0>();
-    u32x4 qb[VC], gb[VC];
-    lds_read_chunks<VC>(aB, qb);
-    lds_read_chunks<VC, VC>(aB, gb);
-    lds_done(qb);
-    lds_done(gb);
-    if (more) issueB(xn);
-    if constexpr (DT == BF16) {
-      uint32_t pa8[8], pd8[8];
-      pack16(a, pa8);
-      pack16(ds, pd8);
-      mfma_acc_bf16<NT>(av, pa8, [&](int c) { return gb[c]; });
-      mfma_acc_bf16<NT>(ak, pd8, [&](int c) { return qb[c]; });
-    } else {
-      mfma_acc_f32<NT>(av, a, [&](int c) { return gb[c]; });
-      mfma_acc_f32<NT>(ak, ds, [&](int c) { return qb[c]; });
-    }
-  }
-  store_block<DT, D>(reinterpret_cast<elem*>(dk) + gy * 32 * D, ak, scale,
-                     COARSE ? dkp + gy * D : nullptr);
-  store_block<DT, D>(reinterpret_cast<elem*>(dv) + gy * 32 * D, av, 1.0f,
-                     COARSE ? dvp + gy * D : nullptr);
-}
-
-// ---------------------------------------------------------------------------
-// bfloat16 forms that read the transposed operands straight from the
-// row-layout copy in LDS with gfx950's transposing read ds_read_b64_tr_b16:
-// within each group of 16 lanes, lane i receives as value k (k = 0..3) the
-// 16-bit element i%4 of the 8 bytes at the address that lane 4k + i/4 of the
-// group supplies (lane layout checked on the device). Chunk (u, t) of the
-// transposed operand X^T for lane l = 32h + j holds X[16u + 8(s/4) + 4h + s%4]
-// [32t + j], s = 0..7; so each lane supplies, for each half e = 0, 1, the
-// address of X[16u + 8e + 4(l/32) + (l%16)/4][32t + 16((l/16)&1) + 4(l&3)]
-// (four consecutive columns of one row, 8 bytes) and two reads fill a chunk.
-// Only the row-layout copies are then loaded per tile (dQ: K_y, V_y, 8 KB;
-// dK/dV: Q_x, G_x and the record, 8.25 KB), and each wave keeps two whole
-// tiles in flight in two LDS slots while it computes a third from registers.
-
-// In LDS each 1 KB chunk of a row-layout block is followed by 64 bytes of
-// padding, so the four chunks a transposing read touches start 16 banks apart:
-// its 32 lanes per pass then hit 64 distinct banks (without the padding, lanes
-// whose addresses differ by whole chunks share banks).
-constexpr int kChunkPad = 64;
-constexpr int kChunkStride = 1024 + kChunkPad;
-
-// Byte offset of X[r][c] in a padded row-layout block (bf16, D columns) in LDS.
-template <int D>
-__host__ __device__ constexpr int row_layout_offset(int r, int c) {
-  return ((c % (D / 2)) / 8) * kChunkStride + (32 * (c / (D / 2)) + r) * 16 + (c % 8) * 2;
-}
-
-// C consecutive 1 KB chunks HBM/L2 -> LDS at kChunkStride apart: the load's
-// immediate offset steps both addresses by 1 KB, the LDS base adds the pad.
-template <int C>
-__device__ __forceinline__ void load_chunks_lds_padded(gptr_t src, lptr_t dst) {
-  if constexpr (C > 0) {
-    load_chunks_lds_padded<C - 1>(src, dst);
-    __builtin_amdgcn_global_load_lds(src, dst + (C - 1) * kChunkPad, 16, (C - 1) * 1024, 0);
-  }
-}
-
-// v[i] = padded chunk C0 + i for this lane, i < C
-template <int I, int C, int C0>
-struct LdsChunksPadded {
-  static __device__ __forceinline__ void run(uint32_t addr, u32x4* v) {
-    v[I] = lds_read16<(C0 + I) * kChunkStride>(addr);
-    LdsChunksPadded<I + 1, C, C0>::run(addr, v);
-  }
-};
-template <int C, int C0>
-struct LdsChunksPadded<C, C, C0> {
-  static __device__ __forceinline__ void run(uint32_t, u32x4*) {}
-};
-
-// this lane's address term for the transposed reads of a row-layout block
-template <int D>
-__device__ __forceinline__ uint32_t tr_lane_offset() {
-  const int l = lane_id();
-  return (uint32_t)row_layout_offset<D>(4 * (l >> 5) + ((l & 15) >> 2), 16 * ((l >> 4) & 1) + 4 * (l & 3));
-}
-
-// Transposed chunks c = u*NT + t (c < VC) of the row-layout block at `base`
-// (+ this lane's tr_lane_offset); the caller completes them with lds_done().
-template <int D, int C, int VC>
-struct TrChunks {
-  static constexpr int NT = D / 32;
-  static __device__ __forceinline__ void run(uint32_t addr, u32x4* v) {
-    if constexpr (C < VC) {
-      constexpr int u = C / NT, t = C % NT;
-      constexpr int o0 = row_layout_offset<D>(16 * u, 32 * t) - row_layout_offset<D>(0, 0);
-      constexpr int o1 = row_layout_offset<D>(16 * u + 8, 32 * t) - row_layout_offset<D>(0, 0);
-      const u32x2 a = lds_read_tr16<o0>(addr);
-      const u32x2 b = lds_read_tr16<o1>(addr);
-      v[C] = u32x4{a[0], a[1], b[0], b[1]};
-      TrChunks<D, C + 1, VC>::run(addr, v);
-    }
-  }
-};
-
 // bfloat16: the passes read raw 32-row tiles of the inputs themselves, no
 // packed copies. A tile (32 consecutive rows, 2d bytes each) is
 // copied with direct-to-LDS loads of whole rows, every lane fetching the
@@ -1047,13 +579,14 @@ __global__ __launch_bounds__(WAVES * kWave) void bwd_dq_tr_kernel(
   if (g >= rows) return;                                    // no workgroup barriers below
   const long long bh = g / nb;
   if constexpr (COARSE) prefetch_vec_lds<D>(dqp + g * D, (lptr_t)addl[w]);
-  int32_t* myidx = sidx_all + w * m;
-  const int cnt = stage_selection(idx + g * m, m, nb, myidx);
-
+  // the row's operands are requested before its list, whose wait covers them
   u32x4 qf[KC], gf[KC];
   load_rows<BF16, D>(reinterpret_cast<const elem*>(qin) + g * 32 * D, qf);
   load_rows<BF16, D>(reinterpret_cast<const elem*>(gin) + g * 32 * D, gf);
   const float lq = ld[g * 64 + jq], dl = ld[g * 64 + 32 + jq];
+  int32_t* myidx = sidx_all + w * m;
+  const int cnt = stage_selection(idx + g * m, m, nb, myidx);
+  wait_loads<0>();
   f32x16 acc[NT];
 #pragma unroll
   for (int t = 0; t < NT; ++t)
@@ -1071,7 +604,7 @@ __global__ __launch_bounds__(WAVES * kWave) void bwd_dq_tr_kernel(
   };
 #pragma unroll
   for (int t = 0; t < SLOTS; ++t)
-    if (cnt > t) issue(wave_uniform(myidx[t]), t);
+    if (cnt > t) issue(list_entry(myidx + t), t);
   for (int i = 0; i < cnt; ++i) {
     if (SLOTS == 2 && i + 1 < cnt) wait_loads<N>();         // tile i landed, i+1 may not have
     else wait_loads<0>();
@@ -1083,9 +616,9 @@ __global__ __launch_bounds__(WAVES * kWave) void bwd_dq_tr_kernel(
     lds_done(kf);
     lds_done(vf);
     lds_done(tf);
-    if (i + SLOTS < cnt) issue(wave_uniform(myidx[i + SLOTS]), i % SLOTS);
-    const f32x16 s = mfma_abt<BF16, KC>(kf, qf);
-    const f32x16 pv = mfma_abt<BF16, KC>(vf, gf);
+    if (i + SLOTS < cnt) issue(list_entry(myidx + i + SLOTS), i % SLOTS);
+    const f32x16 s = mfma_abt<KC>(kf, qf);
+    const f32x16 pv = mfma_abt<KC>(vf, gf);
     float ds[16];
 #pragma unroll
     for (int r = 0; r < 16; ++r)
@@ -1137,13 +670,14 @@ __global__ __launch_bounds__(WAVES * kWave) void bwd_dkdv_tr_kernel(
   const long long hb = bh * nb;
   const int nbw = (nb + 31) / 32;
 
-  // block-rows whose selection holds y, ascending
-  int32_t* myx = sidx_all + w * nb;
-  const int cnt = column_list(bits, hb, nbw, y, nb, myx);
-
+  // the block's operands are requested before its list, whose wait covers them
   u32x4 kf[KC], vf[KC];
   load_rows<BF16, D>(reinterpret_cast<const elem*>(kin) + gy * 32 * D, kf);
   load_rows<BF16, D>(reinterpret_cast<const elem*>(vin) + gy * 32 * D, vf);
+  // block-rows whose selection holds y, ascending
+  int32_t* myx = sidx_all + w * nb;
+  const int cnt = column_list(bits, hb, nbw, y, nb, myx);
+  wait_loads<0>();
   f32x16 ak[NT], av[NT];
 #pragma unroll
   for (int t = 0; t < NT; ++t)
@@ -1169,7 +703,7 @@ __global__ __launch_bounds__(WAVES * kWave) void bwd_dkdv_tr_kernel(
   };
 #pragma unroll
   for (int t = 0; t < SLOTS; ++t)
-    if (cnt > t) issue(wave_uniform(myx[t]), t);
+    if (cnt > t) issue(list_entry(myx + t), t);
   for (int i = 0; i < cnt; ++i) {
     if (SLOTS == 2 && i + 1 < cnt) wait_loads<N>();         // tile i landed, i+1 may not have
     else wait_loads<0>();
@@ -1185,7 +719,7 @@ __global__ __launch_bounds__(WAVES * kWave) void bwd_dkdv_tr_kernel(
     lds_done(qt);
     lds_done(gtc);
     lds_done(ba);
-    if (i + SLOTS < cnt) issue(wave_uniform(myx[i + SLOTS]), i % SLOTS);
+    if (i + SLOTS < cnt) issue(list_entry(myx + i + SLOTS), i % SLOTS);
     const f32x16 s = mfma_abt_from<KC>(qa, kf, ba[0], ones_l);   // lane: key, 16 queries
     const f32x16 pv = mfma_abt_from<KC>(ga, vf, ba[0], ones_d);
     float a[16], ds[16];
@@ -1237,13 +771,14 @@ __global__ __launch_bounds__(WAVES * kWave) void bwd_dq_tr128_kernel(
   if (g >= rows) return;                                    // no workgroup barriers below
   const long long bh = g / nb;
   if constexpr (COARSE) prefetch_vec_lds<D>(dqp + g * D, (lptr_t)addl[w]);
-  int32_t* myidx = sidx_all + w * m;
-  const int cnt = stage_selection(idx + g * m, m, nb, myidx);
-
+  // the row's operands are requested before its list, whose wait covers them
   u32x4 qf[KC], gf[KC];
   load_rows<BF16, D>(reinterpret_cast<const elem*>(qin) + g * 32 * D, qf);
   load_rows<BF16, D>(reinterpret_cast<const elem*>(gin) + g * 32 * D, gf);
   const float lq = ld[g * 64 + jq], dl = ld[g * 64 + 32 + jq];
+  int32_t* myidx = sidx_all + w * m;
+  const int cnt = stage_selection(idx + g * m, m, nb, myidx);
+  wait_loads<0>();
   f32x16 acc[NT];
 #pragma unroll
   for (int t = 0; t < NT; ++t)
@@ -1259,13 +794,13 @@ __global__ __launch_bounds__(WAVES * kWave) void bwd_dq_tr128_kernel(
   // the slot's halves are refilled separately: V_y's as soon as its rows are
   // read (they are read first), K_y's once its rows and K_y^T are read
   if (cnt > 0) {
-    const int y = wave_uniform(myidx[0]);
+    const int y = list_entry(myidx);
     copy_raw_buf<KC, R::KP>(vrs, (unsigned)y * TB, ro.cp, vdst);
     copy_raw_buf<KC, R::KP>(krs, (unsigned)y * TB, ro.cp, kdst);
   }
   for (int i = 0; i < cnt; ++i) {
     wait_loads<KC>();                                       // V_y landed (K_y may be in flight)
-    const int yn = i + 1 < cnt ? wave_uniform(myidx[i + 1]) : 0;
+    const int yn = i + 1 < cnt ? list_entry(myidx + i + 1) : 0;
     u32x4 op[KC];
     raw_rows<TB>(base, ro.rr, op);                          // V_y rows
     lds_done(op);
@@ -1275,10 +810,10 @@ __global__ __launch_bounds__(WAVES * kWave) void bwd_dq_tr128_kernel(
     } else {
       wait_loads<0>();
     }
-    const f32x16 pv = mfma_abt<BF16, KC>(op, gf);
+    const f32x16 pv = mfma_abt<KC>(op, gf);
     raw_rows<0>(base, ro.rr, op);                           // K_y rows
     lds_done(op);
-    const f32x16 s = mfma_abt<BF16, KC>(op, qf);
+    const f32x16 s = mfma_abt<KC>(op, qf);
     RawTrB<D, 0, 0, VC>::run(base, ro.tr, op);             // K_y^T
     lds_done(op);
     if (i + 1 < cnt) copy_raw_buf<KC, R::KP>(krs, (unsigned)yn * TB, ro.cp, kdst);
@@ -1328,13 +863,14 @@ __global__ __launch_bounds__(kWave) void bwd_dkdv_tr128_kernel(
   const long long hb = bh * nb;
   const int nbw = (nb + 31) / 32;
 
-  // block-rows whose selection holds y, ascending
-  int32_t* myx = sidx_all;
-  const int cnt = column_list(bits, hb, nbw, y, nb, myx);
-
+  // the block's operands are requested before its list, whose wait covers them
   u32x4 kf[KC], vf[KC];
   load_rows<BF16, D>(reinterpret_cast<const elem*>(kin) + gy * 32 * D, kf);
   load_rows<BF16, D>(reinterpret_cast<const elem*>(vin) + gy * 32 * D, vf);
+  // block-rows whose selection holds y, ascending
+  int32_t* myx = sidx_all;
+  const int cnt = column_list(bits, hb, nbw, y, nb, myx);
+  wait_loads<0>();
   f32x16 ak[NT], av[NT];
 #pragma unroll
   for (int t = 0; t < NT; ++t)
@@ -1357,8 +893,8 @@ __global__ __launch_bounds__(kWave) void bwd_dkdv_tr128_kernel(
     mra_raw_buffer_load_lds(brs, dst + 2 * TB, 4, lane * 4, x * RB, 0, 0);
     mra_raw_buffer_load_lds(brs, dst + 2 * TB + 256, 4, lane * 4, x * RB + 256, 0, 0);
   };
-  if (cnt > 0) issue(wave_uniform(myx[0]), 0);
-  if (cnt > 1) issue(wave_uniform(myx[1]), 1);
+  if (cnt > 0) issue(list_entry(myx), 0);
+  if (cnt > 1) issue(list_entry(myx + 1), 1);
   for (int i = 0; i < cnt; ++i) {
     if (i + 1 < cnt) wait_loads<N>();                       // tile i landed, i+1 may not have
     else wait_loads<0>();
@@ -1386,12 +922,307 @@ __global__ __launch_bounds__(kWave) void bwd_dkdv_tr128_kernel(
     mfma_acc_bf16<NT>(ak, pd8, [&](int c) { return op[c]; });
     RawTrB<D, TB, 0, VC>::run(base, ro.tr, op);            // G_x^T
     lds_done(op);
-    if (i + 2 < cnt) issue(wave_uniform(myx[i + 2]), i & 1);   // the slot has been read
+    if (i + 2 < cnt) issue(list_entry(myx + i + 2), i & 1);   // the slot has been read
     mfma_acc_bf16<NT>(av, pa8, [&](int c) { return op[c]; });
   }
   wait_loads<0>();
   store_block<BF16, D>(reinterpret_cast<elem*>(dk) + gy * 32 * D, ak, scale, COARSE ? addl[0] : nullptr);
   store_block<BF16, D>(reinterpret_cast<elem*>(dv) + gy * 32 * D, av, 1.0f, COARSE ? addl[1] : nullptr);
+}
+
+// ---------------------------------------------------------------------------
+// float32 (on the bfloat16 matrix cores, tile_ops.h). The packing pass writes
+// Q, K, V and dZ as planes: per 32-row block the hi, mid and lo tiles one after
+// the other, each a raw bfloat16 tile of the layout above, so a wave reads its
+// operands as planes and splits only the 16 values it computes per tile.
+// The float32 matrix instructions bounded these passes and their operands in
+// registers left one wave per SIMD at d = 128. Measured before -> after, packing
+// included: 32 heads x 4096 x 32, budget 8 (small-4096): dQ 81 -> 47, dK/dV
+// 136 -> 70, packing 29 -> 26 us; 32 heads x 1504 x 128, budget 8: dQ 197 -> 85,
+// dK/dV 473 -> 117, packing 33 -> 37 us.
+//
+// Both passes give a block-row or column block to a pair of waves that walk
+// its tiles together, each wave holding one fixed operand. The tile's planes
+// are copied into one LDS slot per workgroup (12 KB per 32 dims), half by each
+// wave; two barriers per tile: A, behind which both halves and the exchanged
+// values are there, and B, behind which the slot has been read and is refilled
+// while the second products run.
+
+// C = A B^T over the planes of one raw tile at `base` (A, read from LDS plane
+// by plane, the smallest products first) and the fixed operand f.
+template <int D, int KC>
+__device__ __forceinline__ f32x16 mfma3_abt(uint32_t base, const uint32_t (&rr)[KC], const u32x4 (&f)[3][KC]) {
+  constexpr int TB = RawB<D>::TB;
+  f32x16 c;
+#pragma unroll
+  for (int r = 0; r < 16; ++r) c[r] = 0.0f;
+  u32x4 a[KC];
+  auto step = [&](const u32x4 (&b)[KC]) {
+#pragma unroll
+    for (int k = 0; k < KC; ++k)
+      c = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, a[k]), __builtin_bit_cast(bf16x8, b[k]), c, 0, 0, 0);
+  };
+  raw_rows<2 * TB>(base, rr, a);
+  lds_done(a);
+  step(f[0]);
+  raw_rows<TB>(base, rr, a);
+  lds_done(a);
+  step(f[1]);
+  step(f[0]);
+  raw_rows<0>(base, rr, a);
+  lds_done(a);
+  step(f[2]);
+  step(f[1]);
+  step(f[0]);
+  return c;
+}
+
+// The planes of block-row g's 32 rows in the row layout.
+template <int D, int KC>
+__device__ __forceinline__ void load_planes(const void* planes, long long g, u32x4 (&f)[3][KC]) {
+  using elem = typename TileCfg<BF16, D>::elem;
+#pragma unroll
+  for (int q = 0; q < 3; ++q) load_rows<BF16, D>(reinterpret_cast<const elem*>(planes) + (g * 3 + q) * 32 * D, f[q]);
+}
+
+// One tile's planes (3 KC copies of 1 KB) HBM/L2 -> LDS.
+template <int D>
+__device__ __forceinline__ void copy_planes(i32x4 rs, int block, const RawB<D>& ro, lptr_t dst) {
+  constexpr int TB = RawB<D>::TB;
+#pragma unroll
+  for (int q = 0; q < 3; ++q)
+    copy_raw_buf<D / 16, RawB<D>::KP>(rs, (unsigned)block * (3 * TB) + q * TB, ro.cp, dst + q * TB);
+}
+
+// This wave's LDS accesses complete, then the workgroup's barrier.
+__device__ __forceinline__ void pair_barrier() { asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory"); }
+
+// dQ (float32): a pair of waves per block-row x. Wave 0 forms S = K_y Q_x^T
+// and the weights, wave 1 V_y G_x^T - delta; each then takes half of the
+// keys: they exchange the other half's values (8 per lane), form
+// dP and add K_y^T dP over their 16 keys to a full 32 x d accumulator. The two
+// accumulators are added at the end.
+template <int D, bool COARSE>
+__global__ __launch_bounds__(2 * kWave) void bwd_dq_split_kernel(
+    const void* __restrict__ qpl, const void* __restrict__ gpl, const void* __restrict__ kpl,
+    const void* __restrict__ vpl, const int32_t* __restrict__ idx, const float* __restrict__ ld,
+    const float* __restrict__ dqp, float* __restrict__ dq, int nb, int m, float scale, float scale_log2) {
+  using R = RawB<D>;
+  constexpr int KC = R::KC, NT = R::NT, TB = R::TB;
+  __shared__ __attribute__((aligned(16))) unsigned char slot[2][3 * TB];
+  __shared__ __attribute__((aligned(16))) float ex[2][8 * kWave];
+  __shared__ __attribute__((aligned(16))) float addl[COARSE ? add_lds_floats(D) : 1];
+  extern __shared__ uint16_t list_all[];                    // [2][m]
+  const int w = wave_uniform(threadIdx.x / kWave);
+  const int lane = lane_id(), jq = lane & 31;
+  const long long g = xcd_remap(blockIdx.x, gridDim.x);     // one workgroup per block-row
+  const long long bh = g / nb;
+  if constexpr (COARSE)
+    if (w == 0) prefetch_vec_lds<D>(dqp + g * D, (lptr_t)addl);
+  // the row's operands are requested before its list, whose wait covers them
+  const float own = ld[g * 64 + 32 * w + jq];               // log normaliser (log2 units) or delta
+  u32x4 fx[3][KC];                                          // Q_x or G_x
+  load_planes<D>(w ? gpl : qpl, g, fx);
+  uint16_t* myidx = list_all + w * m;
+  const int cnt = stage_selection(idx + g * m, m, nb, myidx);
+  wait_loads<0>();
+  f32x16 acc[NT];
+#pragma unroll
+  for (int t = 0; t < NT; ++t)
+#pragma unroll
+    for (int r = 0; r < 16; ++r) acc[t][r] = 0.0f;
+
+  R ro;
+  ro.init();
+  const i32x4 trs = buffer_rsrc(static_cast<const char*>(w ? vpl : kpl) + (size_t)bh * nb * 3 * TB, (unsigned)nb * 3 * TB);
+  const lptr_t dst = (lptr_t)slot[w];
+  const uint32_t base = lds_addr(slot[w]);                  // the tile this wave copies
+  const uint32_t ktr = lds_addr(slot[0]) + (uint32_t)(16 * w * 2 * D);   // this wave's 16 keys of K_y
+  if (cnt > 0) copy_planes<D>(trs, list_entry(myidx), ro, dst);
+  for (int i = 0; i < cnt; ++i) {
+    const int yn = i + 1 < cnt ? list_entry(myidx + i + 1) : 0;
+    wait_loads<0>();                                        // own half of tile i landed
+    const f32x16 x = mfma3_abt<D>(base, ro.rr, fx);         // lane: query, 16 keys
+    float a[16];
+    if (w == 0) {
+#pragma unroll
+      for (int r = 0; r < 16; ++r) a[r] = __builtin_amdgcn_exp2f(fmaf(x[r], scale_log2, -own));
+    } else {
+#pragma unroll
+      for (int r = 0; r < 16; ++r) a[r] = x[r] - own;
+    }
+    // registers 8u .. 8u + 7: the keys of half u; wave 0 sends half 1, wave 1 half 0
+    float mine[8];
+    {
+      f32x4* o = reinterpret_cast<f32x4*>(ex[w]) + lane;
+#pragma unroll
+      for (int q = 0; q < 2; ++q) {
+        f32x4 v;
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+          v[e] = w == 0 ? a[8 + 4 * q + e] : a[4 * q + e];
+          mine[4 * q + e] = w == 0 ? a[4 * q + e] : a[8 + 4 * q + e];
+        }
+        o[64 * q] = v;
+      }
+    }
+    pair_barrier();                                         // A
+    {
+      const f32x4* o = reinterpret_cast<const f32x4*>(ex[1 - w]) + lane;
+#pragma unroll
+      for (int q = 0; q < 2; ++q) {
+        const f32x4 v = o[64 * q];
+#pragma unroll
+        for (int e = 0; e < 4; ++e) mine[4 * q + e] *= v[e];
+      }
+    }
+    u32x4 tr[3][NT];
+    RawTrB<D, 2 * TB, 0, NT>::run(ktr, ro.tr, tr[2]);
+    RawTrB<D, TB, 0, NT>::run(ktr, ro.tr, tr[1]);
+    RawTrB<D, 0, 0, NT>::run(ktr, ro.tr, tr[0]);
+    lds_done(tr[2]);
+    lds_done(tr[1]);
+    lds_done(tr[0]);
+    pair_barrier();                                         // B
+    if (i + 1 < cnt) copy_planes<D>(trs, yn, ro, dst);
+    u32x4 pk[3];
+    split8(mine, pk);
+#pragma unroll
+    for (int s = 2; s >= 0; --s)                            // p + q = s, the smallest products first
+#pragma unroll
+      for (int p = 0; p <= s; ++p)
+#pragma unroll
+        for (int t = 0; t < NT; ++t)
+          acc[t] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, tr[p][t]),
+                                                           __builtin_bit_cast(bf16x8, pk[s - p]), acc[t], 0, 0, 0);
+  }
+  wait_loads<0>();
+  // wave 1's sums through the slot (32 d floats; every tile has been read)
+  f32x4* part = reinterpret_cast<f32x4*>(slot) + lane;
+  if (w != 0) {
+#pragma unroll
+    for (int t = 0; t < NT; ++t)
+#pragma unroll
+      for (int q = 0; q < 4; ++q)
+        part[(4 * t + q) * 64] = f32x4{acc[t][4 * q], acc[t][4 * q + 1], acc[t][4 * q + 2], acc[t][4 * q + 3]};
+  }
+  pair_barrier();
+  if (w != 0) return;
+#pragma unroll
+  for (int t = 0; t < NT; ++t)
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+      const f32x4 v = part[(4 * t + q) * 64];
+#pragma unroll
+      for (int e = 0; e < 4; ++e) acc[t][4 * q + e] += v[e];
+    }
+  store_block<F32, D>(dq + g * 32 * D, acc, scale, COARSE ? addl : nullptr);
+}
+
+// dK, dV (float32): a pair of waves per column block y. Wave 0 forms
+// S = Q_x K_y^T, the weights A and dV^T += G_x^T A; wave 1 forms G_x V_y^T,
+// takes the weights from wave 0 and adds dK^T += Q_x^T dP.
+template <int D, bool COARSE>
+__global__ __launch_bounds__(2 * kWave) void bwd_dkdv_split_kernel(
+    const void* __restrict__ kpl, const void* __restrict__ vpl, const void* __restrict__ qpl,
+    const void* __restrict__ gpl, const uint32_t* __restrict__ bits, const float* __restrict__ ld,
+    const float* __restrict__ dkp, const float* __restrict__ dvp, float* __restrict__ dk,
+    float* __restrict__ dv, int nb, float scale, float scale_log2) {
+  using R = RawB<D>;
+  constexpr int KC = R::KC, NT = R::NT, TB = R::TB, VC = 2 * NT;
+  __shared__ __attribute__((aligned(16))) unsigned char slot[2][3 * TB];
+  __shared__ __attribute__((aligned(16))) float ex[16 * kWave];
+  __shared__ __attribute__((aligned(16))) float rec[2][64];
+  __shared__ __attribute__((aligned(16))) float addl[2][COARSE ? add_lds_floats(D) : 1];
+  extern __shared__ uint16_t list_all[];                    // [2][nb]
+  const int w = wave_uniform(threadIdx.x / kWave);
+  const int lane = lane_id(), h = lane >> 5;
+  const long long gy = xcd_remap(blockIdx.x, gridDim.x);    // one workgroup per column block
+  const long long bh = gy / nb, hb = bh * nb;
+  const int y = (int)(gy - hb);
+  if constexpr (COARSE) prefetch_vec_lds<D>((w ? dkp : dvp) + gy * D, (lptr_t)addl[w]);
+  u32x4 fx[3][KC];                                          // K_y or V_y, requested before the list
+  load_planes<D>(w ? vpl : kpl, gy, fx);
+  // block-rows whose selection holds y, ascending (each wave keeps its own list)
+  uint16_t* myx = list_all + w * nb;
+  const int cnt = column_list(bits, hb, (nb + 31) / 32, y, nb, myx);
+  wait_loads<0>();
+  f32x16 acc[NT];                                           // dV^T or dK^T
+#pragma unroll
+  for (int t = 0; t < NT; ++t)
+#pragma unroll
+    for (int r = 0; r < 16; ++r) acc[t][r] = 0.0f;
+
+  R ro;
+  ro.init();
+  const i32x4 trs = buffer_rsrc(static_cast<const char*>(w ? gpl : qpl) + (size_t)hb * 3 * TB, (unsigned)nb * 3 * TB);
+  const i32x4 xrs = buffer_rsrc(ld + hb * 64, (unsigned)nb * 256u);
+  const lptr_t dst = (lptr_t)slot[w], xdst = (lptr_t)rec[w];
+  const uint32_t base = lds_addr(slot[w]), other = lds_addr(slot[1 - w]);
+  const uint32_t ra = lds_addr(rec[w]) + 128u * w + 16u * h;   // this half's queries: L (wave 0) or delta
+  auto issue = [&](int x) {
+    copy_planes<D>(trs, x, ro, dst);
+    mra_raw_buffer_load_lds(xrs, xdst, 4, lane * 4, x * 256, 0, 0);   // the block-row's record
+  };
+  if (cnt > 0) issue(list_entry(myx));
+  for (int i = 0; i < cnt; ++i) {
+    const int xn = i + 1 < cnt ? list_entry(myx + i + 1) : 0;
+    wait_loads<0>();                                        // own half of tile i landed
+    u32x4 own[4];                                           // queries 8q + 4h + e
+    own[0] = lds_read16<0>(ra);
+    own[1] = lds_read16<32>(ra);
+    own[2] = lds_read16<64>(ra);
+    own[3] = lds_read16<96>(ra);
+    lds_done(own);
+    const f32x16 x = mfma3_abt<D>(base, ro.rr, fx);         // lane: key, 16 queries
+    float a[16];
+    f32x4* o = reinterpret_cast<f32x4*>(ex) + lane;
+    if (w == 0) {
+#pragma unroll
+      for (int r = 0; r < 16; ++r) a[r] = __builtin_amdgcn_exp2f(fmaf(x[r], scale_log2, -__uint_as_float(own[r / 4][r % 4])));
+#pragma unroll
+      for (int q = 0; q < 4; ++q) o[64 * q] = f32x4{a[4 * q], a[4 * q + 1], a[4 * q + 2], a[4 * q + 3]};
+    } else {
+#pragma unroll
+      for (int r = 0; r < 16; ++r) a[r] = x[r] - __uint_as_float(own[r / 4][r % 4]);
+    }
+    pair_barrier();                                         // A
+    if (w != 0) {
+#pragma unroll
+      for (int q = 0; q < 4; ++q) {
+        const f32x4 v = o[64 * q];
+#pragma unroll
+        for (int e = 0; e < 4; ++e) a[4 * q + e] *= v[e];
+      }
+    }
+    u32x4 tr[3][VC];
+    RawTrB<D, 2 * TB, 0, VC>::run(other, ro.tr, tr[2]);
+    RawTrB<D, TB, 0, VC>::run(other, ro.tr, tr[1]);
+    RawTrB<D, 0, 0, VC>::run(other, ro.tr, tr[0]);
+    lds_done(tr[2]);
+    lds_done(tr[1]);
+    lds_done(tr[0]);
+    pair_barrier();                                         // B
+    if (i + 1 < cnt) issue(xn);
+#pragma unroll
+    for (int u = 0; u < 2; ++u) {
+      float half[8];
+#pragma unroll
+      for (int e = 0; e < 8; ++e) half[e] = a[8 * u + e];
+      u32x4 pk[3];
+      split8(half, pk);
+#pragma unroll
+      for (int s = 2; s >= 0; --s)
+#pragma unroll
+        for (int p = 0; p <= s; ++p)
+#pragma unroll
+          for (int t = 0; t < NT; ++t)
+            acc[t] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, tr[p][u * NT + t]),
+                                                             __builtin_bit_cast(bf16x8, pk[s - p]), acc[t], 0, 0, 0);
+    }
+  }
+  wait_loads<0>();
+  store_block<F32, D>((w ? dk : dv) + gy * 32 * D, acc, w ? scale : 1.0f, COARSE ? addl[w] : nullptr);
 }
 
 // ---------------------------------------------------------------------------
@@ -1419,20 +1250,12 @@ static void launch_tiles_t(const BwdArgs& A, hipStream_t stream) {
         A.q, A.dout, A.k, A.v, A.idx, A.ld, A.dqp, A.dq, nb, A.m, rows, scale, scale_log2);
     bwd_dkdv_tr128_kernel<COARSE><<<(unsigned)rows, kWave, nb * sizeof(int32_t), stream>>>(
         A.k, A.v, A.q, A.dout, A.bits, A.bias, A.dkp, A.dvp, A.dk, A.dv, nb, rows, scale, scale_log2);
-  } else if constexpr (Cfg::kKChunks <= 4 && Cfg::kVChunks <= 4) {
-    bwd_dq_stream_kernel<DT, D, COARSE, W><<<wgs, W * kWave, smem_dq, stream>>>(
-        A.q, A.dout, A.k_row, A.v_row, A.k_t, A.idx, A.ld, A.dqp, A.dq, nb, A.m, rows, scale,
-        scale_log2);
-    bwd_dkdv_stream_kernel<DT, D, COARSE, 1><<<(unsigned)rows, kWave, nb * sizeof(int32_t), stream>>>(
-        A.k, A.v, A.q_row, A.g_row, A.q_t, A.g_t, A.bits, A.ld, A.dkp, A.dvp, A.dk, A.dv, nb, rows,
-        scale, scale_log2);
   } else {
-    bwd_dq_kernel<DT, D, COARSE><<<wgs, W * kWave, smem_dq, stream>>>(
-        A.q, A.dout, A.k_row, A.v_row, A.k_t, A.idx, A.ld, A.dqp, A.dq, nb, A.m, rows, scale,
-        scale_log2);
-    bwd_dkdv_kernel<DT, D, COARSE, 1><<<(unsigned)rows, kWave, nb * sizeof(int32_t), stream>>>(
-        A.k, A.v, A.q_row, A.g_row, A.q_t, A.g_t, A.bits, A.ld, A.dkp, A.dvp, A.dk, A.dv, nb, rows,
-        scale, scale_log2);
+    bwd_dq_split_kernel<D, COARSE><<<(unsigned)rows, 2 * kWave, 2 * A.m * sizeof(uint16_t), stream>>>(
+        A.q_pl, A.g_pl, A.k_pl, A.v_pl, A.idx, A.ld, A.dqp, static_cast<float*>(A.dq), nb, A.m, scale, scale_log2);
+    bwd_dkdv_split_kernel<D, COARSE><<<(unsigned)rows, 2 * kWave, 2 * nb * sizeof(uint16_t), stream>>>(
+        A.k_pl, A.v_pl, A.q_pl, A.g_pl, A.bits, A.ld, A.dkp, A.dvp, static_cast<float*>(A.dk),
+        static_cast<float*>(A.dv), nb, scale, scale_log2);
   }
 }
 
@@ -1460,20 +1283,13 @@ static void launch_bwd_t(const BwdArgs& A, hipStream_t stream) {
 
 hipError_t launch_bwd(const BwdArgs& A, hipStream_t stream) {
   hipError_t e = hipSuccess;
-  if (A.dtype == BF16) {
-    // the tile passes read raw tiles of Q, K, V and G = dZ: only the pooled
-    // rows of the coarse term
-    if (A.coarse && !A.pooled_in)
-      e = launch_pool(A.q, A.k, A.v, A.qp, A.kp, A.vp, nullptr, A.bh, A.n, A.d, A.dtype, stream);
-  } else {
-    // pooled rows (unless given) and packed operands of Q, K, V and G = dZ
-    const bool pool = A.coarse && !A.pooled_in;
-    const PackJob jobs[4] = {{A.q, pool ? A.qp : nullptr, A.q_row, A.q_t},
-                             {A.k, pool ? A.kp : nullptr, A.k_row, A.k_t},
-                             {A.v, pool ? A.vp : nullptr, A.v_row, nullptr},
-                             {A.dout, nullptr, A.g_row, A.g_t}};
-    e = launch_pack(jobs, 4, A.bh, A.n, A.d, A.dtype, stream);
-  }
+  // the pooled rows of the coarse term, unless given; the bfloat16 tile passes
+  // read raw tiles of Q, K, V and G = dZ, the float32 ones their planes
+  if (A.coarse && !A.pooled_in)
+    e = launch_pool(A.q, A.k, A.v, A.qp, A.kp, A.vp, A.bh, A.n, A.d, A.dtype, stream);
+  if (e == hipSuccess && A.dtype == F32)
+    e = launch_split(static_cast<const float*>(A.q), static_cast<const float*>(A.k), static_cast<const float*>(A.v),
+                     static_cast<const float*>(A.dout), A.q_pl, A.k_pl, A.v_pl, A.g_pl, A.bh, A.n, A.d, stream);
   if (e != hipSuccess) return e;
   if (A.dtype == BF16) {
     if (A.d == 32) launch_bwd_t<BF16, 32>(A, stream);

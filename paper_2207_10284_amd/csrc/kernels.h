@@ -29,39 +29,16 @@ mra_status_t forward_enqueue(const void* q, const void* k, const void* v, void* 
 // error (mra_last_hip_error) and returns MRA_ERR_HIP.
 mra_status_t hip_error_status(hipError_t e);
 
-// Packed K/V (written by the pooling pass, read by the tile pass): for every
-// head and 32-key block y, the tile's matrix-core operands in lane order, 16
-// bytes per lane and instruction, 32*d elements per block. The K part (all
-// blocks) comes first, then the V part.
-//  K, chunk s*64 + 32h + j: K[j][(d/2)h + e*s .. +e-1], e = 8 (bf16) or 4 (f32)
-//  V bf16, chunk (u*NT + t)*64 + 32h + j, NT = d/32: the 8 values
-//        V[16u + 8(s/4) + 4h + s%4][32t + j], s = 0..7 (u = 0, 1)
-//  V f32, chunk (t*4 + a)*64 + 32h + j: V[8a + 4h + kk][32t + j], kk = 0..3
-
-// One tensor of a packing launch: src [bh, n, d] of dtype; each output may be
-// NULL: pooled (block means, [bh, n/32, d] f32), row_layout (the K part's
-// layout above) and t_layout (the V part's layout above), each bh*n*d
-// elements of dtype.
-struct PackJob {
-  const void* src;
-  float* pooled;
-  void* row_layout;
-  void* t_layout;
-};
-struct PackJobs {
-  PackJob job[4];
-};
-
-// Up to four packing jobs in one launch (jobs with src NULL do nothing).
-hipError_t launch_pack(const PackJob* jobs, int njobs, long long bh, int n, int d, int dtype,
-                       hipStream_t stream);
+// q, k, v, g ([bh, n, d] float32) as three bfloat16 planes each (bwd.hip): per
+// 32-row block the hi, mid and lo tiles (32 x d, row-major) one after the
+// other, 6 bytes per element.
+hipError_t launch_split(const float* q, const float* k, const float* v, const float* g, void* qpl,
+                        void* kpl, void* vpl, void* gpl, long long bh, int n, int d, hipStream_t stream);
 
 // Block-means of q/k/v ([bh, n, d], dtype) into qp/kp/vp ([bh, n/32, d] f32);
-// a NULL output skips that tensor. If kvpacked is not NULL (k, v, kp, vp
-// given), the packed copies of k and v are written too.
+// a NULL output skips that tensor.
 hipError_t launch_pool(const void* q, const void* k, const void* v, float* qp, float* kp,
-                       float* vp, void* kvpacked, long long bh, int n, int d, int dtype,
-                       hipStream_t stream);
+                       float* vp, long long bh, int n, int d, int dtype, hipStream_t stream);
 
 // S = qp kp^T / sqrt(d) per head, float64 accumulation, [bh, nb, nb] f32.
 hipError_t launch_coarse(const float* qp, const float* kp, float* S, long long bh, int nb, int d,
@@ -97,22 +74,20 @@ hipError_t launch_select_term_fused(const float* qp, const float* kp, int32_t* i
 
 // Selected 32x32 tiles, merge with the low-resolution term (or none if cmax is
 // NULL) and normalise into out [bh, n, d] of dtype; if lse is not NULL, each
-// query's natural log normaliser into lse [bh, n] f32. K and V are read from
-// kvpacked when it is not NULL, else from the row-major k and v.
-hipError_t launch_tile(const void* q, const void* k, const void* v, const void* kvpacked,
-                       const int32_t* idx, const float* cmax, const float* csum,
-                       const float* cvec, void* out, float* lse, long long bh, int n, int d,
-                       int m, int dtype, hipStream_t stream);
+// query's natural log normaliser into lse [bh, n] f32.
+hipError_t launch_tile(const void* q, const void* k, const void* v, const int32_t* idx,
+                       const float* cmax, const float* csum, const float* cvec, void* out, float* lse,
+                       long long bh, int n, int d, int m, int dtype, hipStream_t stream);
 
 // Gradient pass (bwd.hip) of one MRA-2 forward with the selection held fixed.
 // Inputs q, k, v, out (Z), dout (G) [bh, n, d] of dtype; lse [bh, n] f32 (the
 // forward's natural log normalisers); idx [bh, n/32, m] (entries outside
 // [0, n/32) ignored, the others distinct); coarse = false for the
 // sparse-only variant. Outputs dq, dk, dv [bh, n, d] of dtype. The remaining
-// pointers are workspace: pooled rows (coarse only) [bh, nb, d] f32; packed
-// operand copies (row / transposed layout above) of bh*n*d elements of
-// dtype (float32 only: the bfloat16 passes read raw tiles); ld [bh*nb, 64] f32 (per block-row: 32 log normalisers in log2 units,
-// then 32 deltas); bias [bh*n] x 16 bytes (bfloat16 only, else
+// pointers are workspace: pooled rows (coarse only) [bh, nb, d] f32; the
+// planes of q, k, v and dout (launch_split; float32 only: the bfloat16 passes
+// read raw tiles); ld [bh*nb, 64] f32 (per block-row: 32 log normalisers in
+// log2 units, then 32 deltas); bias [bh*n] x 16 bytes (bfloat16 only, else
 // NULL: per query the bfloat16 triples hi + mid + lo of -L_i/c and of
 // -delta_i, the A operand that adds both to the column pass's products);
 // bits [bh*nb, ceil(nb/32)] u32; gh, dqp, dkp, dvp [bh, nb, d] f32 and W, dS
@@ -127,7 +102,7 @@ struct BwdArgs {
   bool coarse;
   bool pooled_in;                 // qp, kp, vp hold the block means already
   float *qp, *kp, *vp;
-  void *q_row, *q_t, *k_row, *k_t, *v_row, *g_row, *g_t;
+  void *q_pl, *k_pl, *v_pl, *g_pl;
   float* ld;
   uint32_t* bias;
   uint32_t* bits;

@@ -9,13 +9,11 @@
 // segments, so every HBM line fetched is fully used; two threads per chunk
 // keep enough waves in flight to fill the GPU. No LDS, no barriers.
 //
-// For float32 passes that read packed operands (the forward at d = 128, the
-// gradient passes) K and V (and Q, dZ) are also written in the tile kernels'
-// matrix-core operand order ("packed", layout in kernels.h), so every operand
-// load is one contiguous 1 KB wave access; that configuration pools in one
-// launch that stages blocks through LDS so the packed writes stay contiguous.
+// The float32 gradient passes read Q, K, V and dZ as bfloat16 planes, which
+// split_kernel writes.
 #include "common.h"
 #include "kernels.h"
+#include "tile_ops.h"
 
 namespace mra {
 
@@ -75,142 +73,42 @@ __global__ __launch_bounds__(256) void pool_kernel(const void* __restrict__ x0,
   }
 }
 
-// Up to four tensors in one launch (blockIdx.y selects the job): for each,
-// the block means (same row order as pool_kernel, so the same bits) and any of
-// the two packed copies: the row layout (the "K" part of kvpacked) and the
-// transposed layout (the "V" part), layouts in kernels.h. Whole 32-row blocks
-// are staged through LDS so that both the reads and the packed writes are
-// contiguous 16-byte chunks across lanes.
-template <int DT, int D>
-__global__ __launch_bounds__(256) void pool_pack_kernel(PackJobs jobs, long long nblocks) {
-  using elem = typename std::conditional<DT == BF16, uint16_t, float>::type;
-  constexpr int kPer = DT == BF16 ? 8 : 4;         // elements per chunk
-  constexpr int CPR = D / kPer;                    // chunks per row
-  constexpr int CPB = kBlock * CPR;                // chunks per block
-  constexpr int NBLK = CPB >= 1024 ? 1 : 1024 / CPB; // blocks per workgroup pass (16 KB)
-  constexpr int NT = D / 32;
-  __shared__ __attribute__((aligned(16))) u32x4 tile[NBLK * CPB];
-  const elem* te = reinterpret_cast<const elem*>(tile);
-  const PackJob job = jobs.job[blockIdx.y];
-  const u32x4* src = reinterpret_cast<const u32x4*>(job.src);
-  float* pooled = job.pooled;
-  u32x4* rowl = reinterpret_cast<u32x4*>(job.row_layout);
-  u32x4* tl = reinterpret_cast<u32x4*>(job.t_layout);
-  if (src == nullptr) return;                      // empty job (whole workgroup)
-  const int tid = threadIdx.x;
-
-  for (long long b0 = (long long)blockIdx.x * NBLK; b0 < nblocks; b0 += (long long)gridDim.x * NBLK) {
-    const int nblk = (int)min((long long)NBLK, nblocks - b0);
+// float32 tensors as three bfloat16 planes (split2), one thread per eight
+// consecutive elements: reads 32 bytes, writes 16 to each plane. HBM-bound:
+// 10 bytes per element.
+__global__ __launch_bounds__(256) void split_kernel(const float* __restrict__ x0, const float* __restrict__ x1,
+                                                    const float* __restrict__ x2, const float* __restrict__ x3,
+                                                    u32x4* __restrict__ y0, u32x4* __restrict__ y1,
+                                                    u32x4* __restrict__ y2, u32x4* __restrict__ y3,
+                                                    long long chunks, int cpb) {
+  const int which = blockIdx.y;
+  const float* x = which == 0 ? x0 : (which == 1 ? x1 : (which == 2 ? x2 : x3));
+  u32x4* y = which == 0 ? y0 : (which == 1 ? y1 : (which == 2 ? y2 : y3));
+  const long long t = (long long)blockIdx.x * 256 + threadIdx.x;
+  if (t >= chunks) return;
+  const f32x4* src = reinterpret_cast<const f32x4*>(x) + 2 * t;
+  const f32x4 a = src[0], b = src[1];
+  const float v[8] = {a[0], a[1], a[2], a[3], b[0], b[1], b[2], b[3]};
+  u32x4 pl[3];
+  split8(v, pl);
+  const long long blk = t / cpb;                   // cpb: chunks of a 32-row block (4 d)
+  u32x4* out = y + blk * 3 * cpb + (t - blk * cpb);
 #pragma unroll
-    for (int ci = tid; ci < NBLK * CPB; ci += 256)
-      if (ci < nblk * CPB) tile[ci] = src[b0 * CPB + ci];
-    __syncthreads();
-    // block means: one thread per (block, column chunk); rows 0..15 and
-    // 16..31 summed in order, then added (pool_kernel's arithmetic)
-    if (pooled != nullptr) {
-      for (int pc = tid; pc < nblk * CPR; pc += 256) {
-        const int bl = pc / CPR, c = pc % CPR;
-        float acc[2][kPer];
-#pragma unroll
-        for (int hh = 0; hh < 2; ++hh)
-#pragma unroll
-          for (int e = 0; e < kPer; ++e) acc[hh][e] = 0.0f;
-#pragma unroll
-        for (int hh = 0; hh < 2; ++hh)
-#pragma unroll 8
-          for (int r = 16 * hh; r < 16 * hh + 16; ++r) {
-            const u32x4 w = tile[bl * CPB + r * CPR + c];
-            if constexpr (DT == BF16) {
-#pragma unroll
-              for (int e = 0; e < 4; ++e) {
-                acc[hh][2 * e] += bf16_to_f32(w[e] & 0xFFFFu);
-                acc[hh][2 * e + 1] += bf16_to_f32(w[e] >> 16);
-              }
-            } else {
-#pragma unroll
-              for (int e = 0; e < 4; ++e) acc[hh][e] += __uint_as_float(w[e]);
-            }
-          }
-        constexpr float inv = 1.0f / kBlock;
-        f32x4* out = reinterpret_cast<f32x4*>(pooled + (b0 + bl) * D + c * kPer);
-#pragma unroll
-        for (int q = 0; q < kPer / 4; ++q) {
-          f32x4 o;
-#pragma unroll
-          for (int e = 0; e < 4; ++e) o[e] = (acc[0][4 * q + e] + acc[1][4 * q + e]) * inv;
-          out[q] = o;
-        }
-      }
-    }
-    // row layout: chunk s*64 + 32h + j holds X[j][(d/2)h + kPer*s .. +kPer-1]
-    if (rowl != nullptr) {
-#pragma unroll
-      for (int oc = tid; oc < NBLK * CPB; oc += 256) {
-        if (oc >= nblk * CPB) continue;
-        const int bl = oc / CPB, k = oc % CPB;
-        const elem* tb = te + bl * kBlock * D;
-        const int sk = k / 64, h = (k % 64) / 32, j = k % 32;
-        rowl[(b0 + bl) * CPB + k] = *reinterpret_cast<const u32x4*>(tb + j * D + (D / 2) * h + kPer * sk);
-      }
-    }
-    if (tl != nullptr) {
-#pragma unroll
-      for (int oc = tid; oc < NBLK * CPB; oc += 256) {
-        if (oc >= nblk * CPB) continue;
-        const int bl = oc / CPB, k = oc % CPB;
-        const elem* tb = te + bl * kBlock * D;
-        u32x4 o;
-        if constexpr (DT == BF16) {
-          // chunk (u*NT + t)*64 + 32h + j: X[16u + 8(s/4) + 4h + s%4][32t + j], s = 0..7
-          const int u = k / (64 * NT), t = (k / 64) % NT, h = (k % 64) / 32, j = k % 32;
-          const int dim = 32 * t + j;
-#pragma unroll
-          for (int s2 = 0; s2 < 4; ++s2) {
-            const int key = 16 * u + 8 * (s2 >> 1) + 4 * h + 2 * (s2 & 1);
-            o[s2] = (uint32_t)tb[key * D + dim] | ((uint32_t)tb[(key + 1) * D + dim] << 16);
-          }
-        } else {
-          // chunk (t*4 + a)*64 + 32h + j: X[8a + 4h + kk][32t + j], kk = 0..3
-          const int t = k / 256, a = (k / 64) % 4, h = (k % 64) / 32, j = k % 32;
-          const int dim = 32 * t + j;
-#pragma unroll
-          for (int kk = 0; kk < 4; ++kk) o[kk] = __float_as_uint(tb[(8 * a + 4 * h + kk) * D + dim]);
-        }
-        tl[(b0 + bl) * CPB + k] = o;
-      }
-    }
-    __syncthreads();
-  }
+  for (int q = 0; q < 3; ++q) out[q * cpb] = pl[q];
 }
 
-hipError_t launch_pack(const PackJob* jobs, int njobs, long long bh, int n, int d, int dtype,
-                       hipStream_t stream) {
-  PackJobs J{};
-  for (int i = 0; i < njobs && i < 4; ++i) J.job[i] = jobs[i];
-  const long long nblocks = bh * (n / kBlock);
-  const int cpb = kBlock * d / (dtype == BF16 ? 8 : 4);
-  const long long nblk = cpb >= 1024 ? 1 : 1024 / cpb;
-  const long long wgs = (nblocks + nblk - 1) / nblk;
-  const dim3 g((unsigned)(wgs < 65536 ? wgs : 65536), (unsigned)njobs);
-  // only float32 passes read packed copies (bfloat16 tiles are read raw)
-  if (dtype != F32) return hipErrorInvalidValue;
-#define MRA_PACK(D_) pool_pack_kernel<F32, D_><<<g, 256, 0, stream>>>(J, nblocks)
-  if (d == 32) MRA_PACK(32); else if (d == 64) MRA_PACK(64); else MRA_PACK(128);
-#undef MRA_PACK
+hipError_t launch_split(const float* q, const float* k, const float* v, const float* g, void* qpl,
+                        void* kpl, void* vpl, void* gpl, long long bh, int n, int d, hipStream_t stream) {
+  const int cpb = kBlock * d / 8;
+  const long long chunks = bh * (n / kBlock) * cpb;
+  const dim3 grid((unsigned)((chunks + 255) / 256), 4);
+  split_kernel<<<grid, 256, 0, stream>>>(q, k, v, g, static_cast<u32x4*>(qpl), static_cast<u32x4*>(kpl),
+                                         static_cast<u32x4*>(vpl), static_cast<u32x4*>(gpl), chunks, cpb);
   return hipGetLastError();
 }
 
 hipError_t launch_pool(const void* q, const void* k, const void* v, float* qp, float* kp,
-                       float* vp, void* kvpacked, long long bh, int n, int d, int dtype,
-                       hipStream_t stream) {
-  if (kvpacked != nullptr) {
-    // the forward's configuration: Q, K, V pooled and K, V packed in one launch
-    const size_t half = (size_t)bh * n * d * (dtype == BF16 ? 2 : 4);
-    const PackJob jobs[3] = {{k, kp, kvpacked, nullptr},
-                             {v, vp, nullptr, static_cast<char*>(kvpacked) + half},
-                             {q, qp, nullptr, nullptr}};
-    return launch_pack(jobs, 3, bh, n, d, dtype, stream);
-  }
+                       float* vp, long long bh, int n, int d, int dtype, hipStream_t stream) {
   const int per = dtype == BF16 ? 8 : 4;
   const long long chunks = bh * (n / kBlock) * (d / per);
   const int threads = 256;

@@ -9,7 +9,7 @@
 // result is merged with the block-row's low-resolution term (M_x, c_x, L_x)
 // and normalised.
 //
-// Matrix-core layout (v_mfma_f32_32x32x16_bf16; 32x32x2_f32 for float32):
+// Matrix-core layout (v_mfma_f32_32x32x16_bf16):
 //  * S is formed transposed, S^T = K_y Q_x^T, so lane l holds query l%32 and
 //    16 of its 32 key scores (keys 8(r/4) + 4(l/32) + r%4 in register r).
 //    That is already the B-operand layout of O^T += V_y^T P^T up to a fixed
@@ -17,20 +17,21 @@
 //    row max crosses the two half-waves.
 //  * The contraction index over d is permuted too: lane half h = l/32 takes
 //    the contiguous half [h*d/2, (h+1)*d/2) of each Q and K row.
-//  * In the packed copies of K and V written by the pooling pass (layout in
-//    kernels.h) every operand of a tile (K_y, and V_y^T, the A operand of the
-//    second product) is one 16-byte chunk per lane, 1 KB contiguous per wave.
+//  * float32 operands (Q, K, V and the weights) are split in registers into
+//    three bfloat16 planes whose sum they are, and each product is the six
+//    plane products that matter (tile_ops.h). The float32 matrix instructions
+//    (64 cycles for 32x32x2) bounded the tile: 4096 cycles of them at d = 64
+//    against 1730 for the plane products, plus about 2000 of vector work, half
+//    of it the splitting. Measured before -> after: 16 heads x 4096 x 32,
+//    budget 8 (small-4096): 47.5 -> 38.9 us; 24 heads x 4096 x 64, budget 16:
+//    127 -> 93.6 us; 32 heads x 1504 x 128, budget 8: 84 (plus 11 for the
+//    copies of K and V in operand order that it needed) -> 66 us. A product's
+//    error against float64 falls from 2.0e-7 to 6.5e-8 (d = 128).
 //
-// Two kernels share that per-row arithmetic (struct TileRow), so their results
-// are bit-identical:
-//  * tile_stream_kernel (raw K/V rows: bfloat16, and float32 with d <= 64;
-//    packed K/V, tiles up to 8 KB): the next selected tile is copied HBM/L2 ->
-//    a wave-private LDS slot with direct-to-LDS loads while the current one is
-//    computed from registers.
-//  * tile_kernel: raw float32 K/V with d = 128 (K rows read directly, V_y
-//    through a wave-private LDS tile stored transposed with the key
-//    permutation applied), and packed K/V with larger tiles (next tile's loads
-//    in flight in registers).
+// tile_stream_kernel copies the next selected tile's rows HBM/L2 -> a
+// wave-private LDS slot with direct-to-LDS loads while the current one is
+// computed from registers. float32 rows of 128 columns are shared by two waves.
+//
 // The softmax reference is set once per row (restart on overflow). Workgroup order
 // is remapped so each XCD processes a contiguous range of heads and keeps
 // their K/V tiles in its L2.
@@ -66,22 +67,33 @@ __device__ __forceinline__ float tile_max(const f32x16& s) {
 }
 
 // Accumulator state and arithmetic of one block-row (32 queries) in one wave.
-template <int DT, int D, bool COARSE>
+// HALVES = 2 (float32, rows of 2 D columns): a pair of waves shares the row,
+// each holding D of the columns (its part of Q, K, V and the output).
+template <int DT, int D, bool COARSE, int HALVES>
 struct TileRow {
   using Cfg = TileCfg<DT, D>;
   using elem = typename Cfg::elem;
-  static constexpr int NT = Cfg::kNT, KC = Cfg::kKChunks;
+  static constexpr int NT = Cfg::kNT, KC = Cfg::kKChunks, PITCH = D * HALVES;
+  static constexpr int QP = DT == BF16 ? 1 : 3, QC = D / 16;
   f32x16 o[NT];
   float mrun, lrun, sl2;
   bool first;                                      // no reference yet
-  u32x4 qf[KC];
+  u32x4 qf[QP][QC];                                // Q_x; float32: its bfloat16 planes
 
-  // Q_x as the B operand: each lane reads d/2 contiguous elements of one row.
+  // Q_x as the B operand: each lane reads d/2 contiguous elements of one row
+  // (Q: the wave's first column).
   __device__ __forceinline__ void init(const elem* Q, int x, float scale_log2) {
     const int lane = lane_id(), jq = lane & 31, h = lane >> 5;
-    const u32x4* qrow = reinterpret_cast<const u32x4*>(Q + (long long)(x * 32 + jq) * D + (D / 2) * h);
+    const u32x4* qrow = reinterpret_cast<const u32x4*>(Q + (long long)(x * 32 + jq) * PITCH + (D / 2) * h);
+    if constexpr (DT == BF16) {
 #pragma unroll
-    for (int s = 0; s < KC; ++s) qf[s] = qrow[s];
+      for (int s = 0; s < KC; ++s) qf[0][s] = qrow[s];
+    } else {
+      u32x4 raw[KC];
+#pragma unroll
+      for (int s = 0; s < KC; ++s) raw[s] = qrow[s];
+      split_chunks(raw, qf);
+    }
 #pragma unroll
     for (int t = 0; t < NT; ++t)
 #pragma unroll
@@ -92,9 +104,26 @@ struct TileRow {
     first = true;
   }
 
-  // S^T = K_y Q_x^T
+  // S^T = K_y Q_x^T (HALVES = 2: over this wave's columns)
   __device__ __forceinline__ f32x16 scores(const u32x4 (&kf)[KC]) const {
-    return mfma_abt<DT, KC>(kf, qf);
+    if constexpr (DT == BF16) {
+      return mfma_abt<KC>(kf, qf[0]);
+    } else {
+      u32x4 kp[3][QC];
+      split_chunks(kf, kp);
+      f32x16 c;
+#pragma unroll
+      for (int r = 0; r < 16; ++r) c[r] = 0.0f;
+#pragma unroll
+      for (int p = 2; p >= 0; --p)                 // the smallest products first
+#pragma unroll
+        for (int q = 2 - p; q >= 0; --q)
+#pragma unroll
+          for (int k = 0; k < QC; ++k)
+            c = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, kp[p][k]),
+                                                        __builtin_bit_cast(bf16x8, qf[q][k]), c, 0, 0, 0);
+      return c;
+    }
   }
 
   // Max of this tile's scores for this lane's query, in log2 units (lanes l
@@ -143,15 +172,12 @@ struct TileRow {
   }
 
   // Softmax weights of one tile and O^T += V_y^T P^T. `va(c)` yields the
-  // 16-byte A-operand chunk c of V_y^T for this lane. With use == false (a
-  // block id outside [0, nb)) the weights are zero: the matrix-core
-  // instructions still run, consuming the tile's operands on every path,
-  // which keeps the compiler's load-counter waits tight. Returns false if
-  // some weight of the row may have exceeded the cap (the caller then restarts
+  // 16-byte A-operand chunk c of V_y^T for this lane. Returns false if some
+  // weight of the row may have exceeded the cap (the caller then restarts
   // the row); with check == false the caller guarantees it cannot.
   template <class VA>
-  __device__ __forceinline__ bool accumulate(const f32x16& s, bool use, bool check, VA va) {
-    if (first && use) {                              // wave-uniform: the row's first tile
+  __device__ __forceinline__ bool accumulate(const f32x16& s, bool check, VA va) {
+    if (first) {                              // wave-uniform: the row's first tile
       mrun = tile_ref(s) + kRefMargin;
       first = false;
     }
@@ -159,21 +185,11 @@ struct TileRow {
     if constexpr (DT == BF16) {
       uint32_t pk[8];
       t = weights_bf16(s, pk);
-      if (!use) {
-#pragma unroll
-        for (int rr = 0; rr < 8; ++rr) pk[rr] = 0u;
-        t = 0.0f;
-      }
       mfma_acc_bf16<NT>(o, pk, va);
     } else {
       float p[16];
       t = weights_f32(s, p);
-      if (!use) {
-#pragma unroll
-        for (int r = 0; r < 16; ++r) p[r] = 0.0f;
-        t = 0.0f;
-      }
-      mfma_acc_f32<NT>(o, p, va);
+      mfma_acc_split<NT>(o, p, va);
     }
     lrun += t;
     return !check || __ballot(!(t <= kWeightCap)) == 0;
@@ -183,7 +199,7 @@ struct TileRow {
   // if lse is not NULL also each query's log normaliser, ln of the row sum of
   // A^ (natural units).
   // cmaxg, csumg, cv: the block-row's coarse-term maximum, sum and vector
-  // (its D floats, in LDS or global memory)
+  // (its D floats, in LDS or global memory); Out: the wave's first column
   __device__ __forceinline__ void finish(elem* Out, float* lse, int x, long long g, float cmaxg,
                                          float csumg, const float* cv) {
     const int lane = lane_id(), jq = lane & 31, h = lane >> 5;
@@ -199,7 +215,7 @@ struct TileRow {
     if (lse != nullptr && h == 0) lse[g * 32 + jq] = (log2f(den) + Mt) * kLn2;
     const float inv = 1.0f / den;
     const float ao = af * inv, bv = bc * inv;       // z = o * ao + cvec * bv
-    elem* orow = Out + (long long)(x * 32 + jq) * D;
+    elem* orow = Out + (long long)(x * 32 + jq) * PITCH;
     u32x2 pend = {0u, 0u};                          // bf16: the even group's 4 values
 #pragma unroll
     for (int t = 0; t < NT; ++t) {
@@ -237,177 +253,6 @@ struct TileRow {
     }
   }
 };
-
-// ---------------------------------------------------------------------------
-// One wave per block-row.
-template <int DT, int D, bool COARSE, bool PACKED>
-__global__ __launch_bounds__((TileCfg<DT, D>::kWaves * kWave)) void tile_kernel(
-    const void* __restrict__ qv, const void* __restrict__ kv, const void* __restrict__ vv,
-    const int32_t* __restrict__ idx, const float* __restrict__ cmax,
-    const float* __restrict__ csum, const float* __restrict__ cvec, void* __restrict__ outv,
-    float* __restrict__ lse, int n, int nb, int m, long long rows, float scale_log2) {
-  using Cfg = TileCfg<DT, D>;
-  using elem = typename Cfg::elem;
-  constexpr int W = Cfg::kWaves, PITCH = Cfg::kPitch, NT = Cfg::kNT;
-  constexpr int VC = Cfg::kVChunks, KC = Cfg::kKChunks;
-  __shared__ __attribute__((aligned(16))) elem vt_all[PACKED ? 1 : W][PACKED ? 8 : D * PITCH];
-
-  const int w = wave_uniform(threadIdx.x / kWave);
-  const int lane = lane_id();
-  const int jq = lane & 31, h = lane >> 5;
-  const long long wg = xcd_remap(blockIdx.x, gridDim.x);
-  const long long g = wg * W + w;                    // global block-row
-  if (g >= rows) return;                             // no workgroup barriers below
-  const long long bh = g / nb;
-  const int x = (int)(g - bh * nb);
-  const long long hoff = bh * (long long)n * D;
-  const elem* K = reinterpret_cast<const elem*>(kv) + hoff;
-  extern __shared__ int32_t sidx_all[];
-  int32_t* myidx = sidx_all + w * m;
-  // Q_x's loads are issued first, so their latency overlaps the staging of
-  // the selection list
-  TileRow<DT, D, COARSE> row;
-  row.init(reinterpret_cast<const elem*>(qv) + hoff, x, scale_log2);
-  m = stage_selection(idx + g * m, m, nb, myidx);  // valid entries only, in order
-  auto clampy = [&](int y) { return (y < 0 || y >= nb) ? 0 : y; };
-  auto valid = [&](int y) { return y >= 0 && y < nb; };
-
-  if constexpr (PACKED) {
-    auto load_kpacked = [&](int y, u32x4 (&kf)[KC]) {
-      const u32x4* kt = reinterpret_cast<const u32x4*>(kv) + ((bh * nb + y) * KC) * 64 + lane;
-#pragma unroll
-      for (int c = 0; c < KC; ++c) kf[c] = kt[c * 64];
-    };
-    auto load_vpacked = [&](int y, u32x4 (&vf)[VC]) {
-      const u32x4* vt = reinterpret_cast<const u32x4*>(vv) + ((bh * nb + y) * VC) * 64 + lane;
-#pragma unroll
-      for (int c = 0; c < VC; ++c) vf[c] = vt[c * 64];
-    };
-    // Two register buffers: tile i+1 loads while tile i is computed. Loads
-    // are issued unconditionally (past the last tile they re-read the last
-    // tile, a cache hit) so every path leaves the same loads in flight.
-    auto pass = [&](bool check) -> bool {
-      u32x4 kA[KC], vA[VC], kB[KC], vB[VC];
-      if (m > 0) {
-        const int y0 = clampy(wave_uniform(myidx[0]));
-        load_kpacked(y0, kA);
-        load_vpacked(y0, vA);
-      }
-      for (int i = 0; i < m; i += 2) {
-        const int ya = wave_uniform(myidx[i]);
-        const int yb = wave_uniform(myidx[min(i + 1, m - 1)]);
-        load_kpacked(clampy(yb), kB);
-        load_vpacked(clampy(yb), vB);
-        if (!row.accumulate(row.scores(kA), valid(ya), check, [&](int c) { return vA[c]; })) return false;
-        if (i + 1 >= m) break;
-        const int yc = clampy(wave_uniform(myidx[min(i + 2, m - 1)]));
-        load_kpacked(yc, kA);
-        load_vpacked(yc, vA);
-        if (!row.accumulate(row.scores(kB), valid(yb), check, [&](int c) { return vB[c]; })) return false;
-      }
-      return true;
-    };
-    if (!pass(true)) {
-      // some weight grew too large: again, relative to the row's exact max
-      float mx = -INFINITY;
-      for (int i = 0; i < m; ++i) {
-        const int yy = wave_uniform(myidx[i]);
-        if (!valid(yy)) continue;
-        u32x4 kf[KC];
-        load_kpacked(yy, kf);
-        mx = __builtin_elementwise_maximum(mx, row.tile_ref(row.scores(kf)));
-      }
-      row.restart(mx);
-      pass(false);
-    }
-  } else {
-    elem* vt = vt_all[w];
-    const elem* V = reinterpret_cast<const elem*>(vv) + hoff;
-    auto load_k = [&](int y, u32x4 (&kc)[KC]) {
-      const u32x4* krow = reinterpret_cast<const u32x4*>(K + (long long)(y * 32 + jq) * D + (D / 2) * h);
-#pragma unroll
-      for (int s = 0; s < KC; ++s) kc[s] = krow[s];
-    };
-    auto pass = [&](bool check) -> bool {
-    for (int i = 0; i < m; ++i) {
-      const int y = wave_uniform(myidx[i]);
-      if (!valid(y)) continue;
-      u32x4 kc[KC];
-      load_k(y, kc);
-      // V_y -> LDS transposed, keys in the operand order of the packed layout
-      if constexpr (DT == BF16) {
-        // key 16u + 8a + 4hh + kk goes to position 16u + 8hh + 4a + kk
-#pragma unroll
-        for (int gi = lane; gi < D; gi += kWave) {
-          const int c = gi % (D / 8), kg = gi / (D / 8);
-          const elem* vsrc = V + (long long)(y * 32 + 4 * kg) * D + 8 * c;
-          const u32x4 r0 = *reinterpret_cast<const u32x4*>(vsrc);
-          const u32x4 r1 = *reinterpret_cast<const u32x4*>(vsrc + D);
-          const u32x4 r2 = *reinterpret_cast<const u32x4*>(vsrc + 2 * D);
-          const u32x4 r3 = *reinterpret_cast<const u32x4*>(vsrc + 3 * D);
-          const int pos0 = 16 * (kg >> 2) + 8 * (kg & 1) + 4 * ((kg >> 1) & 1);
-#pragma unroll
-          for (int e = 0; e < 8; ++e) {
-            const int sh = (e & 1) * 16;
-            u32x2 pr;
-            pr[0] = ((r0[e >> 1] >> sh) & 0xFFFFu) | (((r1[e >> 1] >> sh) & 0xFFFFu) << 16);
-            pr[1] = ((r2[e >> 1] >> sh) & 0xFFFFu) | (((r3[e >> 1] >> sh) & 0xFFFFu) << 16);
-            *reinterpret_cast<u32x2*>(vt + (8 * c + e) * PITCH + pos0) = pr;
-          }
-        }
-      } else {
-        // key 8a + 4hh + kk goes to position 16hh + 4a + kk
-#pragma unroll
-        for (int gi = lane; gi < 2 * D; gi += kWave) {
-          const int c = gi % (D / 4), kg = gi / (D / 4);
-          const float* vsrc = V + (long long)(y * 32 + 4 * kg) * D + 4 * c;
-          const f32x4 r0 = *reinterpret_cast<const f32x4*>(vsrc);
-          const f32x4 r1 = *reinterpret_cast<const f32x4*>(vsrc + D);
-          const f32x4 r2 = *reinterpret_cast<const f32x4*>(vsrc + 2 * D);
-          const f32x4 r3 = *reinterpret_cast<const f32x4*>(vsrc + 3 * D);
-          const int pos0 = 16 * (kg & 1) + 4 * (kg >> 1);
-#pragma unroll
-          for (int e = 0; e < 4; ++e) {
-            const f32x4 col = {r0[e], r1[e], r2[e], r3[e]};
-            *reinterpret_cast<f32x4*>(vt + (4 * c + e) * PITCH + pos0) = col;
-          }
-        }
-      }
-      const f32x16 s = row.scores(kc);
-      wave_lds_sync();
-      bool ok;
-      if constexpr (DT == BF16) {
-        ok = row.accumulate(s, true, check, [&](int c) {
-          const int u = c / NT, t = c % NT;
-          return *reinterpret_cast<const u32x4*>(vt + (32 * t + jq) * PITCH + 16 * u + 8 * h);
-        });
-      } else {
-        ok = row.accumulate(s, true, check, [&](int c) {
-          const int t = c / 4, a = c % 4;
-          return *reinterpret_cast<const u32x4*>(vt + (32 * t + jq) * PITCH + 16 * h + 4 * a);
-        });
-      }
-      wave_lds_sync();                               // reads done before the next overwrite
-      if (!ok) return false;
-    }
-    return true;
-    };
-    if (!pass(true)) {
-      float mx = -INFINITY;
-      for (int i = 0; i < m; ++i) {
-        const int yy = wave_uniform(myidx[i]);
-        if (!valid(yy)) continue;
-        u32x4 kf[KC];
-        load_k(yy, kf);
-        mx = __builtin_elementwise_maximum(mx, row.tile_ref(row.scores(kf)));
-      }
-      row.restart(mx);
-      pass(false);
-    }
-  }
-  row.finish(reinterpret_cast<elem*>(outv) + hoff, lse, x, g, COARSE ? cmax[g] : 0.0f, COARSE ? csum[g] : 0.0f,
-             COARSE ? cvec + g * D : nullptr);
-}
 
 // ---------------------------------------------------------------------------
 // Raw K/V tiles in LDS (bfloat16, d <= 64). A 32-row tile of K (or V) is 4 KB
@@ -498,16 +343,17 @@ __device__ __forceinline__ int f32v_copy_offset(int i, int lane) {
 }
 
 // The K copies (KPB-periodic lane offsets, as copy_raw_tiles_buf) and the V
-// copies of a raw float32 tile (period 1 for d = 32, 2 for d = 64).
-template <int I>
+// copies of a raw float32 tile (period 1 for d = 32, 2 for d = 64). STEP: source
+// bytes between copies (1 KB; 2 KB where the tile is half of its rows).
+template <int I, int STEP>
 __device__ __forceinline__ void copy_raw_f32_buf(i32x4 krs, i32x4 vrs, unsigned ktile, unsigned vtile,
                                                  const unsigned (&koff)[4], const unsigned (&voff)[2], lptr_t ks,
                                                  lptr_t vs) {
   if constexpr (I > 0) {
-    copy_raw_f32_buf<I - 1>(krs, vrs, ktile, vtile, koff, voff, ks, vs);
+    copy_raw_f32_buf<I - 1, STEP>(krs, vrs, ktile, vtile, koff, voff, ks, vs);
     constexpr int i = I - 1;
-    buffer_load_lds16(krs, ks + i * 1024, koff[i & 3], ktile + i * 1024);
-    buffer_load_lds16(vrs, vs + i * 1024, voff[i & 1], vtile + i * 1024);
+    buffer_load_lds16(krs, ks + i * 1024, koff[i & 3], ktile + i * STEP);
+    buffer_load_lds16(vrs, vs + i * 1024, voff[i & 1], vtile + i * STEP);
   }
 }
 
@@ -533,34 +379,28 @@ struct RawF32TrChunks {
 // while the current one is computed from registers. Prefetching into LDS
 // instead of registers leaves room for four waves per SIMD.
 constexpr int kStreamWaves = 4;
-constexpr int kStreamSlots = 1;
 
-// Wait until at most `keep` tiles of CH loads each are still in flight (the
-// load counter counts down in issue order, so the older tiles have landed).
-template <int CH>
-__device__ __forceinline__ void wait_tiles_in_flight(int keep) {
-  if (keep <= 0) asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
-  else if (keep == 1) asm volatile("s_waitcnt vmcnt(%0)" ::"n"(CH) : "memory");
-  else asm volatile("s_waitcnt vmcnt(%0)" ::"n"(2 * CH) : "memory");
-}
-
-template <int DT, int D, bool COARSE, int WAVES, int SLOTS>
+// HALVES = 2 (float32 rows of 128 columns): the workgroup's two waves share one
+// block-row, each working on 64 of the columns like the d = 64 kernel, with one
+// exchange per tile: the scores are the sum of the two waves' products.
+template <int DT, int D, bool COARSE, int WAVES, int HALVES>
 __global__ __launch_bounds__(WAVES * kWave) void tile_stream_kernel(
     const void* __restrict__ qv, const void* __restrict__ kv, const void* __restrict__ vv,
     const int32_t* __restrict__ idx, const float* __restrict__ cmax,
     const float* __restrict__ csum, const float* __restrict__ cvec, void* __restrict__ outv,
-    float* __restrict__ lse, int n, int nb, int m, long long row0, long long rows, float scale_log2) {
+    float* __restrict__ lse, int n, int nb, int m, long long row0, long long rows, int in_step, float scale_log2) {
   using Cfg = TileCfg<DT, D>;
   using elem = typename Cfg::elem;
   constexpr int KC = Cfg::kKChunks, VC = Cfg::kVChunks, CH = Cfg::kChunks;
   static_assert(CH <= 16, "operands of a tile are held in registers");
-  static_assert(SLOTS >= 1 && SLOTS <= 3, "tiles in flight per wave");
-  static_assert(DT == BF16 || D <= 64, "raw tiles: bfloat16, or float32 with d <= 64");
+  static_assert(DT == BF16 || D <= 64, "raw tiles: bfloat16, or float32 with at most 64 columns per wave");
+  static_assert(HALVES == 1 || (HALVES == 2 && DT == F32 && WAVES == 2), "a pair of waves per row");
+  constexpr int DR = D * HALVES;                     // columns of a row
   constexpr bool F32RAW = DT == F32;
   constexpr int D2 = F32RAW ? 2 * D : D;             // the bfloat16 geometry of the K tile
   // the slots are their own LDS object, apart from the selection lists, so
   // reading a list does not wait for loads in flight into a slot
-  __shared__ __attribute__((aligned(16))) u32x4 slot_all[WAVES][SLOTS][CH * 64];
+  __shared__ __attribute__((aligned(16))) u32x4 slot_all[WAVES][CH * 64];
   // Tiles of 8 KB per part (two waves per SIMD) fetch the coarse term's
   // vector into LDS while the tiles run (its maximum and sum are loaded then
   // too): with two waves per SIMD, reading it after the last tile exposed its
@@ -568,40 +408,51 @@ __global__ __launch_bounds__(WAVES * kWave) void tile_stream_kernel(
   // it, and the extra load at the row's start cost more than it saved.
   constexpr bool kTermAhead = COARSE && D2 >= 128;
   __shared__ __attribute__((aligned(16))) float cvl[WAVES][kTermAhead ? add_lds_floats(D) : 1];
+  __shared__ __attribute__((aligned(16))) float ex[HALVES == 2 ? 2 : 1][2][HALVES == 2 ? 16 * kWave : 1];
   extern __shared__ int32_t sidx_all[];
 
   const int w = wave_uniform(threadIdx.x / kWave);
   const int lane = lane_id();
   const long long wg = xcd_remap(blockIdx.x, gridDim.x);
-  const long long g = row0 + wg * WAVES + w;         // global block-row (rows row0 .. rows - 1)
-  if (g >= rows) return;                             // no workgroup barriers below
+  // global block-row (rows row0 .. rows - 1); a pair's workgroup has one row
+  const long long g = HALVES == 2 ? row0 + wg : row0 + wg * WAVES + w;
+  if (g >= rows) return;                             // a pair: both waves; else no barriers below
+  const int col0 = HALVES == 2 ? w * D : 0;          // this wave's first column
   float cmaxg = 0.0f, csumg = 0.0f;
   if constexpr (kTermAhead) {
-    prefetch_vec_lds<D>(cvec + g * D, (__attribute__((address_space(3))) char*)cvl[w]);
+    prefetch_vec_lds<D>(cvec + g * DR + col0, (__attribute__((address_space(3))) char*)cvl[w]);
     cmaxg = cmax[g];
     csumg = csum[g];
   }
   const long long bh = g / nb;
   const int x = (int)(g - bh * nb);
-  const long long hoff = bh * (long long)n * D;
+  const long long hoff = bh * (long long)n * DR + col0;
   int32_t* myidx = sidx_all + w * m;
   // Q_x's loads are issued first, so their latency overlaps the staging of
   // the selection list
-  TileRow<DT, D, COARSE> row;
+  TileRow<DT, D, COARSE, HALVES> row;
   row.init(reinterpret_cast<const elem*>(qv) + hoff, x, scale_log2);
   m = stage_selection(idx + g * m, m, nb, myidx);  // valid entries only, in order
+  wait_loads<0>();                                 // Q_x too (the list's loads came after it)
   // the head's K and V rows (tile y at byte y * 32 d e)
-  const char* kslab = static_cast<const char*>(kv) + (size_t)bh * nb * KC * 1024;
-  const char* vslab = static_cast<const char*>(vv) + (size_t)bh * nb * VC * 1024;
+  constexpr unsigned TILE = KC * 1024u * HALVES;
+  static_assert(KC == VC, "tiles of K and V");
+  const char* kslab = static_cast<const char*>(kv) + (size_t)bh * nb * TILE;
+  const char* vslab = static_cast<const char*>(vv) + (size_t)bh * nb * TILE;
   // this lane's source offsets for the copies (see copy_raw_tiles_buf) and its
   // LDS read offsets (K chunk c; V^T column tile t)
   constexpr int NT = TileCfg<DT, D>::kNT;
   constexpr int KPB = D2 == 128 ? 4 : (D2 == 64 ? 2 : 1);  // period of the K copy offsets
+  // a byte of this wave's (half) tile -> its byte in the whole rows
+  auto in_rows = [&](int b) {
+    return HALVES == 1 ? b : (b / (2 * D2)) * (2 * D2 * HALVES) + b % (2 * D2) + col0 * (int)sizeof(elem);
+  };
   unsigned koffq[4];                                 // K source offsets of copies i mod 4
 #pragma unroll
-  for (int q = 0; q < 4; ++q) koffq[q] = raw_copy_offset<D2, raw_swz_k<D2>>(q % KPB, lane) - (q % KPB) * 1024;
-  const i32x4 krs = buffer_rsrc(kslab, (unsigned)nb * KC * 1024u);
-  const i32x4 vrs = buffer_rsrc(vslab, (unsigned)nb * VC * 1024u);
+  for (int q = 0; q < 4; ++q)
+    koffq[q] = in_rows(raw_copy_offset<D2, raw_swz_k<D2>>(q % KPB, lane)) - (q % KPB) * 1024 * HALVES;
+  const i32x4 krs = buffer_rsrc(kslab, (unsigned)nb * TILE);
+  const i32x4 vrs = buffer_rsrc(vslab, (unsigned)nb * TILE);
   const int h = lane >> 5, j = lane & 31, i16 = lane & 15;
   int kread[KC], vread[NT];
 #pragma unroll
@@ -609,7 +460,7 @@ __global__ __launch_bounds__(WAVES * kWave) void tile_stream_kernel(
   unsigned voff0 = 0, voffq[2] = {0u, 0u};
   if constexpr (F32RAW) {
 #pragma unroll
-    for (int q = 0; q < 2; ++q) voffq[q] = f32v_copy_offset<D>(q, lane) - q * 1024;
+    for (int q = 0; q < 2; ++q) voffq[q] = in_rows(f32v_copy_offset<D>(q, lane)) - q * 1024 * HALVES;
 #pragma unroll
     for (int t = 0; t < NT; ++t) vread[t] = KC * 1024 + f32v_offset<D>(4 * h, 32 * t + j);
   } else {
@@ -619,40 +470,45 @@ __global__ __launch_bounds__(WAVES * kWave) void tile_stream_kernel(
       vread[t] = KC * 1024 +
                  raw_offset<D, raw_swz_v<D>>(4 * h + i16 / 4, 32 * t + 16 * ((lane >> 4) & 1) + 4 * (i16 & 3));
   }
-  auto issue = [&](int y, int sidx) {
-    unsigned char* slot = reinterpret_cast<unsigned char*>(slot_all[w][sidx]);
+  auto issue = [&](int y) {
+    unsigned char* slot = reinterpret_cast<unsigned char*>(slot_all[w]);
     auto* ks = (__attribute__((address_space(3))) char*)slot;
     auto* vs = (__attribute__((address_space(3))) char*)(slot + KC * 1024);
     if constexpr (F32RAW)
-      copy_raw_f32_buf<KC>(krs, vrs, (unsigned)y * KC * 1024u, (unsigned)y * VC * 1024u, koffq, voffq, ks, vs);
+      copy_raw_f32_buf<KC, 1024 * HALVES>(krs, vrs, (unsigned)y * TILE, (unsigned)y * TILE, koffq, voffq, ks, vs);
     else
-      copy_raw_tiles_buf<KC>(krs, vrs, (unsigned)y * KC * 1024u, (unsigned)y * VC * 1024u, koffq, voff0, ks, vs);
+      copy_raw_tiles_buf<KC>(krs, vrs, (unsigned)y * TILE, (unsigned)y * TILE, koffq, voff0, ks, vs);
   };
-  // entries outside [0, nb) are skipped
-  auto next_valid = [&](int j, int& y) {
-    for (; j < m; ++j) {
-      y = wave_uniform(myidx[j]);
-      if (y >= 0 && y < nb) break;
-    }
-    return j;
-  };
-  // Tiles are numbered in the order they are used; tile t goes to slot
-  // t % SLOTS, and up to SLOTS of them are in flight.
-  auto pass = [&](bool check) -> bool {
-    int yn = 0;
-    int ni = next_valid(0, yn);                      // next list entry to load
-    int issued = 0, used = 0;
+  // the tile's scores: for a pair the sum of the two waves' products, the same
+  // in both (two buffers in turn, so one barrier per tile orders them)
+  int exb = 0;
+  auto whole_scores = [&](const u32x4 (&kf)[KC]) -> f32x16 {
+    f32x16 s = row.scores(kf);
+    if constexpr (HALVES == 2) {
+      f32x4* mine = reinterpret_cast<f32x4*>(ex[exb][w]) + lane;
+      const uint32_t theirs = lds_addr(ex[exb][1 - w]) + 16u * lane;
 #pragma unroll
-    for (int t = 0; t < SLOTS; ++t)
-      if (ni < m) {
-        issue(yn, t);
-        ++issued;
-        ni = next_valid(ni + 1, yn);
-      }
-    while (used < issued) {
-      wait_tiles_in_flight<CH>(issued - used - 1);   // tile `used` is in its slot
+      for (int q = 0; q < 4; ++q) mine[64 * q] = f32x4{s[4 * q], s[4 * q + 1], s[4 * q + 2], s[4 * q + 3]};
+      asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");
+      u32x4 t[4];
+      lds_read_chunks<4>(theirs, t);
+      lds_done(t);
+#pragma unroll
+      for (int r = 0; r < 16; ++r) s[r] += __uint_as_float(t[r / 4][r % 4]);
+      exb ^= 1;
+    }
+    return s;
+  };
+  // The list holds valid blocks only. The entry after the next is read before
+  // the wait for a tile, so the refill is issued as soon as the slot is read.
+  auto pass = [&](bool check) -> bool {
+    if (m > 0) issue(list_entry(myidx));
+    for (int i = 0; i < m; ++i) {
+      const bool more = i + 1 < m;                   // wave-uniform
+      const int yn = more ? list_entry(myidx + i + 1) : 0;
+      wait_loads<0>();                               // tile i is in the slot
       u32x4 kf[KC], vf[VC];
-      const uint32_t base = lds_addr(slot_all[w][used % SLOTS]);
+      const uint32_t base = lds_addr(slot_all[w]);
 #pragma unroll
       for (int c = 0; c < KC; ++c) kf[c] = lds_read16<0>(base + kread[c]);
       uint32_t va[NT];
@@ -662,15 +518,10 @@ __global__ __launch_bounds__(WAVES * kWave) void tile_stream_kernel(
       else RawTrChunks<D, 0, VC>::run(va, vf);
       lds_done(kf);
       lds_done(vf);
-      asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");  // operands in registers
-      ++used;
-      if (ni < m) {                                  // refill the slot just read
-        issue(yn, issued % SLOTS);
-        ++issued;
-        ni = next_valid(ni + 1, yn);
-      }
-      if (!row.accumulate(row.scores(kf), true, check, [&](int c) { return vf[c]; })) {
-        asm volatile("s_waitcnt vmcnt(0)" ::: "memory");  // the slots are idle again
+      if (more) issue(yn);                           // refill the slot just read
+      if (in_step) wait_loads<0>();                  // launched in rounds: see launch_stream_c
+      if (!row.accumulate(whole_scores(kf), check, [&](int c) { return vf[c]; })) {
+        wait_loads<0>();                             // the slot is idle again
         return false;
       }
     }
@@ -680,94 +531,75 @@ __global__ __launch_bounds__(WAVES * kWave) void tile_stream_kernel(
     // some weight grew too large: again, relative to the row's exact max
     float mx = -INFINITY;
     for (int i = 0; i < m; ++i) {
-      const int yy = wave_uniform(myidx[i]);
-      if (yy < 0 || yy >= nb) continue;
+      const int yy = list_entry(myidx + i);
       u32x4 kf[KC];
-      load_rows<DT, D>(reinterpret_cast<const elem*>(kslab + (size_t)yy * KC * 1024), kf);
-      mx = __builtin_elementwise_maximum(mx, row.tile_ref(row.scores(kf)));
+      const u32x4* krow = reinterpret_cast<const u32x4*>(reinterpret_cast<const elem*>(kslab + (size_t)yy * TILE) +
+                                                         (long long)j * DR + col0 + (D / 2) * h);
+#pragma unroll
+      for (int c = 0; c < KC; ++c) kf[c] = krow[c];
+      mx = __builtin_elementwise_maximum(mx, row.tile_ref(whole_scores(kf)));
     }
     row.restart(mx);
     pass(false);
   }
   if constexpr (kTermAhead) {
-    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");  // the coarse-term vector is in LDS
-    row.finish(reinterpret_cast<elem*>(outv) + hoff, lse, x, g, cmaxg, csumg, cvl[w]);
+    wait_loads<0>();                                 // the coarse-term vector is in LDS
+    row.finish(reinterpret_cast<elem*>(outv) + hoff, w == 0 || HALVES == 1 ? lse : nullptr, x, g, cmaxg, csumg, cvl[w]);
   } else {
-    row.finish(reinterpret_cast<elem*>(outv) + hoff, lse, x, g, COARSE ? cmax[g] : 0.0f,
-               COARSE ? csum[g] : 0.0f, COARSE ? cvec + g * D : nullptr);
+    row.finish(reinterpret_cast<elem*>(outv) + hoff, w == 0 || HALVES == 1 ? lse : nullptr, x, g,
+               COARSE ? cmax[g] : 0.0f, COARSE ? csum[g] : 0.0f, COARSE ? cvec + g * DR + col0 : nullptr);
   }
 }
 
 // ---------------------------------------------------------------------------
-// Raw K/V tiles of up to 8 KB (bfloat16; float32 with d <= 64) stream through
-// LDS.
+// Raw K/V tiles of up to 8 KB per wave stream through LDS.
 //
 // Where a head's K and V exceed an XCD's L2 (4 MB), the pass is launched one
 // occupancy round of block-rows at a time: every block-row of a launch starts
 // together and walks its (ascending) selection in step with its neighbours,
 // so the blocks the XCD's resident rows touch at any moment stay close
 // together and more of them hit L2. Within one launch, later rows start as
-// earlier ones finish and the rows drift apart over the head. Heads that fit
-// L2 are launched whole (a launch per round costs more than it saves there).
-template <int DT, int D, bool COARSE>
+// earlier ones finish and the rows drift apart over the head. For the same
+// reason a wave there waits for its refill as soon as it is issued (in_step):
+// that costs the overlap of copy and arithmetic within a wave, which the other
+// waves of the SIMD provide, and keeps the rows closer together: 16 heads of
+// 32768 x 128 bfloat16, budget 32: 490 us with the wait, 548 without. Heads that
+// fit L2 are launched whole (a launch per round costs more than it saves there)
+// and without the wait.
+template <int DT, int D, bool COARSE, int HALVES>
 static void launch_stream_c(const void* q, const void* k, const void* v, const int32_t* idx,
                             const float* cmax, const float* csum, const float* cvec, void* out,
                             float* lse, long long bh, int n, int m, float scale_log2, hipStream_t stream) {
+  constexpr int W = HALVES == 2 ? 2 : kStreamWaves, R = W / HALVES;   // waves, block-rows per workgroup
   const int nb = n / kBlock;
   const long long rows = bh * nb;
-  const size_t smem = (size_t)kStreamWaves * m * sizeof(int32_t);  // per-wave selection lists
-  auto kernel = tile_stream_kernel<DT, D, COARSE, kStreamWaves, kStreamSlots>;
-  const size_t head_kv = (size_t)2 * n * D * (DT == BF16 ? 2 : 4);
-  long long chunk = head_kv > kL2PerXcd ? resident_items(kernel, kStreamWaves * kWave, smem, kStreamWaves) : 0;
+  const size_t smem = (size_t)W * m * sizeof(int32_t);     // per-wave selection lists
+  auto kernel = tile_stream_kernel<DT, D, COARSE, W, HALVES>;
+  const size_t head_kv = (size_t)2 * n * D * HALVES * (DT == BF16 ? 2 : 4);
+  long long chunk = head_kv > kL2PerXcd ? resident_items(kernel, W * kWave, smem, R) : 0;
   if (chunk <= 0) chunk = rows;
   for (long long r0 = 0; r0 < rows; r0 += chunk) {
     const long long r1 = r0 + chunk < rows ? r0 + chunk : rows;
-    const unsigned blocks = (unsigned)((r1 - r0 + kStreamWaves - 1) / kStreamWaves);
-    kernel<<<blocks, kStreamWaves * kWave, smem, stream>>>(q, k, v, idx, cmax, csum, cvec, out, lse, n, nb,
-                                                           m, r0, r1, scale_log2);
+    const unsigned blocks = (unsigned)((r1 - r0 + R - 1) / R);
+    kernel<<<blocks, W * kWave, smem, stream>>>(q, k, v, idx, cmax, csum, cvec, out, lse, n, nb, m, r0, r1,
+                                                chunk < rows, scale_log2);
   }
 }
 
-template <int DT, int D>
+template <int DT, int D, int HALVES = 1>
 static void launch_stream(const void* q, const void* k, const void* v, const int32_t* idx,
                           const float* cmax, const float* csum, const float* cvec, void* out,
                           float* lse, long long bh, int n, int m, float scale_log2, hipStream_t stream) {
   if (cmax)
-    launch_stream_c<DT, D, true>(q, k, v, idx, cmax, csum, cvec, out, lse, bh, n, m, scale_log2, stream);
+    launch_stream_c<DT, D, true, HALVES>(q, k, v, idx, cmax, csum, cvec, out, lse, bh, n, m, scale_log2, stream);
   else
-    launch_stream_c<DT, D, false>(q, k, v, idx, cmax, csum, cvec, out, lse, bh, n, m, scale_log2, stream);
+    launch_stream_c<DT, D, false, HALVES>(q, k, v, idx, cmax, csum, cvec, out, lse, bh, n, m, scale_log2, stream);
 }
 
-// float32 tiles of d = 128 (16 KB): the packed copy, or the raw rows
-template <bool PACKED>
-static void launch_tile_f32_128(const void* q, const void* k, const void* v, const int32_t* idx,
-                                const float* cmax, const float* csum, const float* cvec, void* out,
-                                float* lse, long long bh, int n, int m, float scale_log2, hipStream_t stream) {
-  constexpr int W = TileCfg<F32, 128>::kWaves;
-  const int nb = n / kBlock;
-  const long long rows = bh * nb;
-  const unsigned blocks = (unsigned)((rows + W - 1) / W);
-  const size_t smem = (size_t)W * m * sizeof(int32_t);     // per-wave selection lists
-  if (cmax)
-    tile_kernel<F32, 128, true, PACKED><<<blocks, W * kWave, smem, stream>>>(q, k, v, idx, cmax, csum, cvec, out, lse, n, nb, m, rows, scale_log2);
-  else
-    tile_kernel<F32, 128, false, PACKED><<<blocks, W * kWave, smem, stream>>>(q, k, v, idx, cmax, csum, cvec, out, lse, n, nb, m, rows, scale_log2);
-}
-
-hipError_t launch_tile(const void* q, const void* k, const void* v, const void* kvpacked,
-                       const int32_t* idx, const float* cmax, const float* csum,
-                       const float* cvec, void* out, float* lse, long long bh, int n, int d,
-                       int m, int dtype, hipStream_t stream) {
+hipError_t launch_tile(const void* q, const void* k, const void* v, const int32_t* idx,
+                       const float* cmax, const float* csum, const float* cvec, void* out, float* lse,
+                       long long bh, int n, int d, int m, int dtype, hipStream_t stream) {
   const float scale_log2 = (float)(1.4426950408889634 / sqrt((double)d));
-  if (kvpacked) {
-    // only float32 tiles of d = 128 are read from the packed copy
-    if (dtype != F32 || d != 128) return hipErrorInvalidValue;
-    const size_t half = (size_t)bh * n * d * 4;
-    const void* kpk = kvpacked;
-    const void* vpk = static_cast<const char*>(kvpacked) + half;
-    launch_tile_f32_128<true>(q, kpk, vpk, idx, cmax, csum, cvec, out, lse, bh, n, m, scale_log2, stream);
-    return hipGetLastError();
-  }
   if (dtype == BF16) {
     if (d == 32) launch_stream<BF16, 32>(q, k, v, idx, cmax, csum, cvec, out, lse, bh, n, m, scale_log2, stream);
     else if (d == 64) launch_stream<BF16, 64>(q, k, v, idx, cmax, csum, cvec, out, lse, bh, n, m, scale_log2, stream);
@@ -775,7 +607,7 @@ hipError_t launch_tile(const void* q, const void* k, const void* v, const void* 
   } else {
     if (d == 32) launch_stream<F32, 32>(q, k, v, idx, cmax, csum, cvec, out, lse, bh, n, m, scale_log2, stream);
     else if (d == 64) launch_stream<F32, 64>(q, k, v, idx, cmax, csum, cvec, out, lse, bh, n, m, scale_log2, stream);
-    else launch_tile_f32_128<false>(q, k, v, idx, cmax, csum, cvec, out, lse, bh, n, m, scale_log2, stream);
+    else launch_stream<F32, 64, 2>(q, k, v, idx, cmax, csum, cvec, out, lse, bh, n, m, scale_log2, stream);
   }
   return hipGetLastError();
 }

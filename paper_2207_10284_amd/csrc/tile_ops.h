@@ -1,21 +1,28 @@
-// Matrix-core operands and products of one 32x32 tile (v_mfma_f32_32x32x16_bf16;
-// 32x32x2_f32 for float32), shared by the forward tile pass and the two
-// gradient passes.
+// Matrix-core operands and products of one 32x32 tile (v_mfma_f32_32x32x16_bf16),
+// shared by the forward tile pass and the two gradient passes.
 //
 // Operand layouts (bf16: 8 elements per 16-byte chunk, f32: 4):
 //  * Row layout, 32 rows x d: lane (h, j) = (l/32, l%32) holds row j,
-//    columns (d/2)h + e*s .. +e-1 in chunk s (KC chunks). Read straight from
-//    row-major memory, or from the packed "K layout" (chunk s*64 + lane, 1 KB
-//    per chunk and wave).
-//  * Transposed layout, d rows x 32 (the A operand of C^T += X^T P^T): the
-//    packed "V layout" (kernels.h), VC chunks per lane, which orders the 32
-//    contraction indices exactly as the B-operand registers of a tile product
-//    hold them.
+//    columns (d/2)h + e*s .. +e-1 in chunk s (KC chunks).
+//  * Transposed layout, d rows x 32 (the A operand of C^T += X^T P^T), VC chunks
+//    per lane, ordered as the B-operand registers of a tile product hold the 32
+//    contraction indices: bf16 chunk u*NT + t (NT = d/32) of lane (h, j) is
+//    X[16u + 8(s/4) + 4h + s%4][32t + j], s = 0..7; f32 chunk t*4 + a is
+//    X[8a + 4h + kk][32t + j], kk = 0..3.
 //  * A product C = A B^T of two row-layout operands leaves, in lane l,
 //    column l%32 of C (B's row) and its rows 8(r/4) + 4(l/32) + r%4 in
 //    register r. Those 16 values are directly the B operand of the next
 //    product over the same index (mfma_acc_*), so weights never move between
 //    lanes.
+//
+// float32 on the bfloat16 matrix cores: a float32 value is the sum of three
+// bfloat16 values (hi: its upper half, mid: the remainder rounded, lo: what is
+// left, at most eight bits), so a float32 product is the sum of the products of
+// the planes. The six with plane indices p + q <= 2 are formed, the smallest
+// first, and the other three (at most 2^-23 of the product each) dropped. Six
+// 32x32x16 products of 32 cycles do the work of eight 32x32x2 float32 products of
+// 64. Measured against float64 over d = 128: error 6.5e-8 of the result's root
+// mean square, 2.0e-7 for the float32 instruction, whose every step rounds.
 #pragma once
 
 #include "common.h"
@@ -26,8 +33,6 @@ typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
 
 template <int DT, int D>
 struct TileCfg {
-  static constexpr int kWaves = (DT == F32 && D == 128) ? 2 : 4;
-  static constexpr int kPitch = DT == BF16 ? 40 : 36;           // LDS row pitch, elements
   static constexpr int kNT = D / 32;                            // output tiles over d
   // 16-byte transposed-layout chunks per lane per tile
   static constexpr int kVChunks = DT == BF16 ? 2 * kNT : 4 * kNT;
@@ -47,24 +52,16 @@ __device__ __forceinline__ void load_rows(const typename TileCfg<DT, D>::elem* r
   for (int s = 0; s < TileCfg<DT, D>::kKChunks; ++s) f[s] = p[s];
 }
 
-// C = A B^T over the d columns, both in the row layout.
-template <int DT, int KC>
+// C = A B^T over the d columns, both in the row layout (bfloat16).
+template <int KC>
 __device__ __forceinline__ f32x16 mfma_abt(const u32x4 (&a)[KC], const u32x4 (&b)[KC]) {
   f32x16 s;
 #pragma unroll
   for (int r = 0; r < 16; ++r) s[r] = 0.0f;
-  if constexpr (DT == BF16) {
 #pragma unroll
-    for (int k = 0; k < KC; ++k)
-      s = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, a[k]),
-                                                  __builtin_bit_cast(bf16x8, b[k]), s, 0, 0, 0);
-  } else {
-#pragma unroll
-    for (int k = 0; k < KC; ++k)
-#pragma unroll
-      for (int e = 0; e < 4; ++e)
-        s = __builtin_amdgcn_mfma_f32_32x32x2f32(__uint_as_float(a[k][e]), __uint_as_float(b[k][e]), s, 0, 0, 0);
-  }
+  for (int k = 0; k < KC; ++k)
+    s = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, a[k]),
+                                                __builtin_bit_cast(bf16x8, b[k]), s, 0, 0, 0);
   return s;
 }
 
@@ -83,34 +80,106 @@ __device__ __forceinline__ void mfma_acc_bf16(f32x16 (&o)[NT], const uint32_t (&
   }
 }
 
-// The same for float32 weights p (one per register).
-template <int NT, class XA>
-__device__ __forceinline__ void mfma_acc_f32(f32x16 (&o)[NT], const float (&p)[16], XA xa) {
-#pragma unroll
-  for (int tt = 0; tt < NT; ++tt)
-#pragma unroll
-    for (int a = 0; a < 4; ++a) {
-      const u32x4 v4 = xa(tt * 4 + a);
-#pragma unroll
-      for (int e = 0; e < 4; ++e)
-        o[tt] = __builtin_amdgcn_mfma_f32_32x32x2f32(__uint_as_float(v4[e]), p[4 * a + e], o[tt], 0, 0, 0);
-    }
+// Two float32 values as three bfloat16 pairs whose sums they are (finite
+// inputs): hi the upper halves (truncated, so nothing overflows), mid the
+// remainder rounded, lo the rest, which has at most eight significant bits.
+// A remainder x - hi is one dot product of the pair with (-1, 0) or (0, -1);
+// the two constants are kept in registers, since the compiler encodes the first
+// as the inline constant -1.0, which the instruction does not read as that pair.
+__device__ __forceinline__ void split2(float x, float y, uint32_t& hi, uint32_t& mid, uint32_t& lo) {
+  uint32_t px = 0x0000BF80u, py = 0xBF800000u;
+  asm("" : "+s"(px), "+s"(py));
+  const bf16x2 pick_x = __builtin_bit_cast(bf16x2, px), pick_y = __builtin_bit_cast(bf16x2, py);
+  hi = __builtin_amdgcn_perm(__float_as_uint(y), __float_as_uint(x), 0x07060302u);
+  const bf16x2 h2 = __builtin_bit_cast(bf16x2, hi);
+  const float rx = __builtin_amdgcn_fdot2_f32_bf16(h2, pick_x, x, false);
+  const float ry = __builtin_amdgcn_fdot2_f32_bf16(h2, pick_y, y, false);
+  bf16x2 m2, l2;
+  m2[0] = (__bf16)rx;
+  m2[1] = (__bf16)ry;
+  l2[0] = (__bf16)__builtin_amdgcn_fdot2_f32_bf16(m2, pick_x, rx, false);
+  l2[1] = (__bf16)__builtin_amdgcn_fdot2_f32_bf16(m2, pick_y, ry, false);
+  mid = __builtin_bit_cast(uint32_t, m2);
+  lo = __builtin_bit_cast(uint32_t, l2);
 }
 
-// C consecutive 1 KB chunks HBM/L2 -> LDS, 16 bytes per lane each; chunk c is
-// addressed through the load's immediate offset, which moves the global and
-// the LDS address alike.
-template <int C>
-__device__ __forceinline__ void load_chunks_lds(const __attribute__((address_space(1))) char* src,
-                                                __attribute__((address_space(3))) char* dst) {
-  if constexpr (C > 0) {
-    load_chunks_lds<C - 1>(src, dst);
-    __builtin_amdgcn_global_load_lds(src, dst, 16, (C - 1) * 1024, 0);
+// Eight values as the three planes of a 16-byte operand chunk.
+__device__ __forceinline__ void split8(const float (&v)[8], u32x4 (&pl)[3]) {
+#pragma unroll
+  for (int q = 0; q < 4; ++q) {
+    uint32_t h, m, l;
+    split2(v[2 * q], v[2 * q + 1], h, m, l);
+    pl[0][q] = h;
+    pl[1][q] = m;
+    pl[2][q] = l;
+  }
+}
+
+// The float32 row-layout chunks f (four columns each) of a block as bfloat16
+// planes in the bfloat16 row layout (eight columns per chunk): a lane's chunks
+// 2k and 2k + 1 are the eight columns of plane chunk k.
+template <int KC>
+__device__ __forceinline__ void split_chunks(const u32x4 (&f)[KC], u32x4 (&pl)[3][KC / 2]) {
+#pragma unroll
+  for (int k = 0; k < KC / 2; ++k) {
+    float v[8];
+#pragma unroll
+    for (int e = 0; e < 8; ++e) v[e] = __uint_as_float(f[2 * k + e / 4][e % 4]);
+    u32x4 c[3];
+    split8(v, c);
+#pragma unroll
+    for (int q = 0; q < 3; ++q) pl[q][k] = c[q];
+  }
+}
+
+// The same for float32 weights p (one per register): weights and X as
+// bfloat16 planes, the products of the planes with p + q <= 2, the smallest
+// first. `xa(c)` yields the float32 transposed-layout chunk c = 4t + a of X;
+// chunks a = 2u and 2u + 1 are the eight rows of the bfloat16 chunk (u, t).
+template <int NT, class XA>
+__device__ __forceinline__ void mfma_acc_split(f32x16 (&o)[NT], const float (&p)[16], XA xa) {
+#pragma unroll
+  for (int u = 0; u < 2; ++u) {
+    float v[8];
+#pragma unroll
+    for (int e = 0; e < 8; ++e) v[e] = p[8 * u + e];
+    u32x4 pk[3];
+    split8(v, pk);
+#pragma unroll
+    for (int t = 0; t < NT; ++t) {
+      const u32x4 x0 = xa(4 * t + 2 * u), x1 = xa(4 * t + 2 * u + 1);
+#pragma unroll
+      for (int e = 0; e < 4; ++e) {
+        v[e] = __uint_as_float(x0[e]);
+        v[4 + e] = __uint_as_float(x1[e]);
+      }
+      u32x4 xp[3];
+      split8(v, xp);
+#pragma unroll
+      for (int s = 2; s >= 0; --s)
+#pragma unroll
+        for (int q = 0; q <= s; ++q)
+          o[t] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, xp[q]),
+                                                         __builtin_bit_cast(bf16x8, pk[s - q]), o[t], 0, 0, 0);
+    }
   }
 }
 
 __device__ __forceinline__ void wait_lds_reads() {
   asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+}
+
+// Wait until at most N vector-memory loads are outstanding (they complete in
+// issue order, so the older ones have landed). The builtin, unlike an asm
+// s_waitcnt, tells the compiler's own wait insertion what has landed: without
+// that, operands loaded before a loop cost a wait for every copy in flight in
+// each of its iterations.
+template <int N>
+__device__ __forceinline__ void wait_loads() {
+  static_assert(N >= 0 && N < 64, "six bits");
+  asm volatile("" ::: "memory");
+  __builtin_amdgcn_s_waitcnt((N & 15) | ((N >> 4) << 14) | 0x0F70);   // vmcnt; the other counters free
+  asm volatile("" ::: "memory");
 }
 
 // Slot reads are issued as inline assembly: the compiler cannot tell the
@@ -173,7 +242,19 @@ __device__ __forceinline__ u32x2 lds_read2st64(uint32_t addr) {
   return v;
 }
 
-typedef const __attribute__((address_space(1))) char* gptr_t;
+// Entry of a block list in LDS, in one asm block with its wait: for an
+// ordinary read the compiler may first wait for every copy in flight to LDS.
+__device__ __forceinline__ int list_entry(const int32_t* p) {
+  int v;
+  asm volatile("ds_read_b32 %0, %1\n\ts_waitcnt lgkmcnt(0)" : "=v"(v) : "v"(lds_addr(p)) : "memory");
+  return wave_uniform(v);
+}
+__device__ __forceinline__ int list_entry(const uint16_t* p) {
+  int v;
+  asm volatile("ds_read_u16 %0, %1\n\ts_waitcnt lgkmcnt(0)" : "=v"(v) : "v"(lds_addr(p)) : "memory");
+  return wave_uniform(v);
+}
+
 typedef __attribute__((address_space(3))) char* lptr_t;
 
 // Raw bfloat16 tiles in LDS (d <= 64): a 32-row tile of consecutive rows
@@ -228,15 +309,15 @@ constexpr int add_lds_floats(int d) { return d < 64 ? 64 : d; }
 // ids from LDS keeps them off the vector-memory counter, so prefetched loads
 // stay in flight; dropping entries outside [0, nb) here (the padding of a
 // head-wide selection, for instance) keeps them out of the loop.
-__device__ __forceinline__ int stage_selection(const int32_t* __restrict__ row, int m, int nb,
-                                               int32_t* dst) {
+template <class T>
+__device__ __forceinline__ int stage_selection(const int32_t* __restrict__ row, int m, int nb, T* dst) {
   const int lane = lane_id();
   int cnt = 0;
   for (int i0 = 0; i0 < m; i0 += kWave) {
     const int y = i0 + lane < m ? row[i0 + lane] : -1;
     const bool ok = y >= 0 && y < nb;
     const uint64_t mk = __ballot(ok);
-    if (ok) dst[cnt + __popcll(mk & lanemask_lt())] = y;
+    if (ok) dst[cnt + __popcll(mk & lanemask_lt())] = (T)y;
     cnt += __popcll(mk);
   }
   wave_lds_sync();
