@@ -285,3 +285,41 @@ def test_backward_long_sequence_full_head(gpu):
     for name in ("dq", "dk", "dv"):
         assert worst[name] <= GRAD_TOL[w.dtype], (name, worst)
         assert worst[name + "_row"] <= GRAD_ROW_TOL[w.dtype], (name, worst)
+
+
+@pytest.mark.parametrize("n,m", [(8224, 3), (9216, 288)])
+def test_backward_columns_by_list_length(gpu, n, m):
+    """Heads at bfloat16 d = 128 whose Q and dZ exceed an XCD's L2 (n > 8192)
+    take the column blocks by falling list length: every block-row is worked on
+    once, whatever the lists (257 blocks with few entries, some columns in no
+    list; 288 blocks all of one length), and the gradients are the bits of the
+    same heads taken one by one in a call of their own."""
+    print("columns by length", n, m, flush=True)
+    q, k, v = inputs.random_qkv(4100 + n, 1, 2, n, 128, "bf16")
+    g = inputs.round_to_bf16(np.random.Generator(np.random.PCG64(n)).standard_normal(q.shape))
+    tq, tk, tv, tg = (dev(a, "bf16") for a in (q, k, v, g))
+    nb = n // 32
+    idx = torch.empty(1, 2, nb, m, dtype=torch.int32, device="cuda")
+    lse = torch.empty(1, 2, n, device="cuda")
+    out = gpu.attention_forward(tq, tk, tv, m, idx_out=idx, lse_out=lse)
+    grads = gpu.attention_backward(tq, tk, tv, out, tg, lse, idx)
+    h = 1
+    one = [t[:, h:h + 1].clone() for t in (tq, tk, tv, out, tg, lse, idx)]
+    alone = gpu.attention_backward(*one)
+    for a, b in zip(grads, alone):
+        assert torch.equal(a[:, h:h + 1], b)
+    # dV against float64 on the head: dV = A^T dZ
+    f = lambda t: t[0].double()
+    qd, kd, vd, gd = (f(one[i])[0] for i in (0, 1, 2, 4))
+    mean = lambda t: t.view(nb, 32, 128).mean(1)
+    S = mean(qd) @ mean(kd).T / 128 ** 0.5
+    keep = torch.zeros(nb, nb, dtype=torch.bool, device="cuda").scatter_(1, one[6][0, 0].long(), True)
+    dvr = torch.zeros_like(vd)
+    for x in range(nb):
+        rows = slice(32 * x, 32 * x + 32)
+        P = qd[rows] @ kd.T / 128 ** 0.5
+        L = torch.where(keep[x].repeat_interleave(32), P, S[x].repeat_interleave(32).expand(32, -1))
+        dvr += torch.softmax(L, -1).T @ gd[rows]
+    err = float((f(alone[2])[0] - dvr).abs().max() / dvr.abs().max())
+    print("  dv err", err, flush=True)
+    assert err <= GRAD_TOL["bf16"]
