@@ -1,16 +1,19 @@
-"""Build libmra.so (the HIP kernels and the C ABI) in-tree for gfx950.
+"""Build libmra.so (the HIP kernels and the C ABI, gfx950) and _binding.so (the
+torch binding of ops.py's calls, host code) in-tree.
 
     python -m paper_2207_10284_amd.build
 
 Sources compile in parallel into <repo>/_build/, then link into
-paper_2207_10284_amd/libmra.so.
+paper_2207_10284_amd/.
 """
 from __future__ import annotations
 
 import concurrent.futures as cf
+import importlib.util
 import os
 import subprocess
 import sys
+import sysconfig
 
 PKG = os.path.dirname(os.path.abspath(__file__))
 ROOT = os.path.dirname(PKG)
@@ -18,6 +21,7 @@ CSRC = os.path.join(PKG, "csrc")
 INCLUDE = os.path.join(ROOT, "include")
 BUILD = os.path.join(ROOT, "_build")
 LIB = os.path.join(PKG, "libmra.so")
+BINDING = os.path.join(PKG, "_binding.so")
 SOURCES = ["api.cpp", "pool.hip", "coarse.hip", "select.hip", "select_global.hip", "tile.hip",
            "bwd.hip", "multilevel.hip", "noalloc.hip"]
 
@@ -44,10 +48,30 @@ def _compile(src: str) -> str:
     return obj
 
 
+def _build_binding() -> str:
+    """The torch binding: host code against the installed torch's headers; it
+    takes libmra's entry points by address, so it does not link to it."""
+    torch = os.path.dirname(importlib.util.find_spec("torch").origin)
+    inc = [os.path.join(torch, "include"), os.path.join(torch, "include", "torch", "csrc", "api", "include"),
+           "/opt/rocm/include", sysconfig.get_paths()["include"]]
+    tmp = BINDING + ".tmp"
+    cmd = ["g++", "-O2", "-std=c++17", "-fPIC", "-shared", "-fvisibility=hidden", "-D__HIP_PLATFORM_AMD__=1",
+           "-DUSE_ROCM", "-I", INCLUDE, *(f for d in inc for f in ("-isystem", d)), os.path.join(CSRC, "binding.cpp"),
+           "-L", os.path.join(torch, "lib"), "-lc10", "-lc10_hip", "-ltorch_cpu", "-ltorch", "-ltorch_python",
+           "-o", tmp]
+    r = subprocess.run(cmd, capture_output=True, text=True)
+    if r.returncode != 0:
+        raise RuntimeError(f"compile failed: {' '.join(cmd)}\n{r.stdout}\n{r.stderr}")
+    os.replace(tmp, BINDING)
+    return BINDING
+
+
 def build(verbose: bool = False) -> str:
     os.makedirs(BUILD, exist_ok=True)
-    with cf.ThreadPoolExecutor(max_workers=min(8, len(SOURCES))) as ex:
+    with cf.ThreadPoolExecutor(max_workers=8) as ex:
+        binding = ex.submit(_build_binding)
         objs = list(ex.map(_compile, SOURCES))
+        binding.result()
     tmp = LIB + ".tmp"
     cmd = [HIPCC, "-shared", "-fPIC", f"--offload-arch={ARCH}", *objs, "-o", tmp]
     r = subprocess.run(cmd, capture_output=True, text=True)
@@ -55,7 +79,7 @@ def build(verbose: bool = False) -> str:
         raise RuntimeError(f"link failed: {' '.join(cmd)}\n{r.stdout}\n{r.stderr}")
     os.replace(tmp, LIB)
     if verbose:
-        print(f"built {LIB}")
+        print(f"built {LIB} and {BINDING}")
     return LIB
 
 

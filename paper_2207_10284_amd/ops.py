@@ -3,7 +3,9 @@
 Argument marshalling only: every function checks tensor placement, dtype and
 shape, allocates outputs with torch (device memory is plumbing here), and
 calls the library on the current torch stream. All arithmetic runs in the HIP
-kernels. There is no fallback: if the library is not built, ``load`` raises.
+kernels. The forward calls and ``mra_attention`` do this in native code
+(csrc/binding.cpp). There is no fallback: if the library or the binding is not
+built, ``load`` raises.
 
 Shapes: q, k, v are [B, H, n, d] tensors on a ROCm device, float32 or
 bfloat16, contiguous; n is a multiple of 32 and d is 32, 64 or 128.
@@ -53,6 +55,7 @@ SIGNATURES = {
 }
 
 _lib = None
+_native = None          # csrc/binding.cpp, bound to _lib
 
 
 class MraError(RuntimeError):
@@ -75,8 +78,22 @@ def load(path: str = LIB_PATH):
         for name, (res, args) in SIGNATURES.items():
             fn = getattr(lib, name)
             fn.restype, fn.argtypes = res, args
+        bind(lib)
         _lib = lib
     return _lib
+
+
+def bind(lib):
+    """Hand the library's entry points to the native binding."""
+    global _native
+    try:
+        from paper_2207_10284_amd import _binding
+    except ImportError as e:
+        raise RuntimeError(f"the torch binding is not built ({e}); run `python -m paper_2207_10284_amd.build` "
+                           "first") from e
+    _binding.bind({name: ctypes.cast(getattr(lib, name), ctypes.c_void_p).value for name in SIGNATURES},
+                  lambda fn, status: MraError(fn, status, lib))
+    _native = _binding
 
 
 def _call(name: str, *args):
@@ -216,7 +233,8 @@ def attention_forward(q, k, v, budget: int, out=None, idx_out=None, workspace=No
     """The whole MRA-2 forward pass. Returns the output Z ([B, H, n, d], input
     dtype); the selection is written to ``idx_out`` and each query's log
     normaliser (float32 [B, H, n]) to ``lse_out`` when given."""
-    return _forward("mra_attention_forward", q, k, v, budget, out, idx_out, workspace, lse_out)
+    load()
+    return _native.forward(0, q, k, v, budget, False, out, idx_out, workspace, lse_out)
 
 
 def attention_forward_noalloc(q, k, v, budget: int, out=None, idx_out=None, lse_out=None):
@@ -241,26 +259,8 @@ def sparse_attention_forward(q, k, v, budget: int, out=None, idx_out=None, works
     """The sparse-only variant MRA-2-s (Sec. 5): softmax over the selected
     blocks only, no low-resolution term; budget >= 1. Same arguments and
     result as ``attention_forward``."""
-    return _forward("mra_sparse_attention_forward", q, k, v, budget, out, idx_out, workspace, lse_out)
-
-
-def _forward(entry, q, k, v, budget, out, idx_out, workspace, lse_out):
-    ref = _check_qkv(q, k, v)
-    B, H, n, d = ref.shape
-    nb = n // BLOCK
-    if out is None:
-        out = torch.empty_like(ref)
-    if idx_out is not None:
-        _check_idx(idx_out, B, H, nb, budget, ref.device)
-    if lse_out is not None:
-        _check_f32(lse_out, (B, H, n), "lse_out")
-    need = forward_workspace_bytes(B, H, n, d, budget, ref.dtype)
-    if workspace is None:
-        workspace = torch.empty(max(need, 1), device=ref.device, dtype=torch.uint8)
-    _call(entry, _ptr(q), _ptr(k), _ptr(v), _ptr(out), _ptr(idx_out), _ptr(lse_out),
-          _ptr(workspace), workspace.numel() * workspace.element_size(),
-          B, H, n, d, BLOCK, budget, _dtype_code(ref), _stream(ref.device))
-    return out
+    load()
+    return _native.forward(1, q, k, v, budget, False, out, idx_out, workspace, lse_out)
 
 
 def forward_global_workspace_bytes(B: int, H: int, n: int, d: int, dtype=torch.bfloat16) -> int:
@@ -274,22 +274,8 @@ def attention_forward_global(q, k, v, budget: int, prior_diagonal: bool = False,
     plus the diagonal with ``prior_diagonal``). Returns Z; the selection
     (int32 [B, H, nb, nb], rows padded with -1) goes to ``idx_out`` and the
     log normalisers to ``lse_out`` when given."""
-    ref = _check_qkv(q, k, v)
-    B, H, n, d = ref.shape
-    nb = n // BLOCK
-    if out is None:
-        out = torch.empty_like(ref)
-    if idx_out is not None:
-        _check_idx(idx_out, B, H, nb, nb, ref.device)
-    if lse_out is not None:
-        _check_f32(lse_out, (B, H, n), "lse_out")
-    need = forward_global_workspace_bytes(B, H, n, d, ref.dtype)
-    if workspace is None:
-        workspace = torch.empty(max(need, 1), device=ref.device, dtype=torch.uint8)
-    _call("mra_attention_forward_global", _ptr(q), _ptr(k), _ptr(v), _ptr(out), _ptr(idx_out), _ptr(lse_out),
-          _ptr(workspace), workspace.numel() * workspace.element_size(),
-          B, H, n, d, BLOCK, budget, int(bool(prior_diagonal)), _dtype_code(ref), _stream(ref.device))
-    return out
+    load()
+    return _native.forward(2, q, k, v, budget, bool(prior_diagonal), out, idx_out, workspace, lse_out)
 
 
 def forward_multilevel_workspace_bytes(B: int, H: int, n: int, d: int, coarse_block: int, budget1: int,
@@ -475,6 +461,19 @@ class MraAttention(torch.autograd.Function):
         return dq, dk, dv, None, None, None
 
 
+_VARIANTS = {"mra2": 0, "mra2s": 1, "global": 2}
+
+
 def mra_attention(q, k, v, budget: int, variant: str = "mra2", prior_diagonal: bool = False):
-    """Differentiable MRA-2 attention (see ``MraAttention``)."""
+    """Differentiable MRA-2 attention (see ``MraAttention``, whose native
+    counterpart runs here; under functorch transforms, tracing or compilation,
+    and for tensor subclasses, the Python function itself)."""
+    if (type(q) in _PLAIN and type(k) in _PLAIN and type(v) in _PLAIN and variant in _VARIANTS
+            and not torch._C._are_functorch_transforms_active() and torch._C._get_tracing_state() is None
+            and not torch.compiler.is_compiling()):
+        load()
+        return _native.mra_attention(q, k, v, budget, _VARIANTS[variant], bool(prior_diagonal))
     return MraAttention.apply(q, k, v, budget, variant, prior_diagonal)
+
+
+_PLAIN = (torch.Tensor, torch.nn.Parameter)
