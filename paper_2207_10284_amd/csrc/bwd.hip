@@ -47,10 +47,6 @@ namespace mra {
 constexpr int kBwdRows = 16;              // waves (block-rows) per workgroup of the row pass
 constexpr int kBwdTileWaves = 4;          // waves per workgroup of the tile passes
 constexpr int kBwdCols = 16;              // column blocks per workgroup of the column pass
-// Raw-tile slots per wave of the bfloat16 gradient passes: one (the next tile
-// is copied once the current one is in registers) measured faster than two.
-constexpr int kDqSlots = 1;
-constexpr int kDkdvSlots = 1;
 
 template <int DT>
 __device__ __forceinline__ float elem_lo(uint32_t w) {
@@ -628,11 +624,41 @@ struct RawTrB {
   }
 };
 
+// Adds the accumulators of waves 1 .. SPLIT - 1 to wave 0's through LDS: `slot`
+// (w) is wave w's own LDS region of 32 x d floats, idle by now. Every wave calls
+// it; only wave 0's acc is the sum afterwards.
+template <int SPLIT, int NT, class Slot>
+__device__ __forceinline__ void add_parts(f32x16 (&acc)[NT], int w, Slot slot) {
+  const int lane = lane_id();
+  if (w != 0) {
+    f32x4* to = reinterpret_cast<f32x4*>(slot(w)) + lane;
+#pragma unroll
+    for (int t = 0; t < NT; ++t)
+#pragma unroll
+      for (int q = 0; q < 4; ++q)
+        to[(4 * t + q) * kWave] = f32x4{acc[t][4 * q], acc[t][4 * q + 1], acc[t][4 * q + 2], acc[t][4 * q + 3]};
+  }
+  __syncthreads();
+  if (w != 0) return;
+#pragma unroll
+  for (int p = 1; p < SPLIT; ++p) {
+    const f32x4* from = reinterpret_cast<const f32x4*>(slot(p)) + lane;
+#pragma unroll
+    for (int t = 0; t < NT; ++t)
+#pragma unroll
+      for (int q = 0; q < 4; ++q) {
+        const f32x4 v = from[(4 * t + q) * kWave];
+#pragma unroll
+        for (int e = 0; e < 4; ++e) acc[t][4 * q + e] += v[e];
+      }
+  }
+}
+
 // dQ (bf16, d <= 64): one wave per block-row; a slot holds the raw tiles K_y
-// and V_y (K^T is read transposed from the K tile). SLOTS tiles in flight per
-// wave: with one slot the next tile is copied once the current one is in
-// registers.
-template <int D, bool COARSE, int WAVES, int SLOTS>
+// and V_y (K^T is read transposed from the K tile). The next tile is copied once
+// the current one is in registers. SPLIT > 1: the workgroup's waves share one
+// block-row, wave p taking the tiles p, p + SPLIT, ...
+template <int D, bool COARSE, int WAVES, int SPLIT>
 __global__ __launch_bounds__(WAVES * kWave) void bwd_dq_tr_kernel(
     const void* __restrict__ qin, const void* __restrict__ gin, const void* __restrict__ kin,
     const void* __restrict__ vin, const int32_t* __restrict__ idx,
@@ -642,17 +668,18 @@ __global__ __launch_bounds__(WAVES * kWave) void bwd_dq_tr_kernel(
   using elem = typename Cfg::elem;
   using R = RawB<D>;
   constexpr int KC = Cfg::kKChunks, VC = Cfg::kVChunks, NT = Cfg::kNT;
-  constexpr int TB = R::TB, N = 2 * KC;                     // loads per tile
+  constexpr int TB = R::TB;
   constexpr int SLOT = 2 * TB;
   static_assert(KC == R::KC && KC <= 4 && VC <= 4, "raw tiles of d <= 64");
-  static_assert(SLOTS == 1 || SLOTS == 2, "tiles in flight per wave");
-  __shared__ __attribute__((aligned(16))) unsigned char slots[WAVES][SLOTS][SLOT];
+  static_assert(SPLIT == 1 || SPLIT == WAVES, "a workgroup per row");
+  __shared__ __attribute__((aligned(16))) unsigned char slots[WAVES][SLOT];
   __shared__ __attribute__((aligned(16))) float addl[WAVES][COARSE ? add_lds_floats(D) : 1];
   extern __shared__ int32_t sidx_all[];
   const int w = wave_uniform(threadIdx.x / kWave);
   const int lane = lane_id(), jq = lane & 31;
-  const long long g = xcd_remap(blockIdx.x, gridDim.x) * (long long)WAVES + w;
-  if (g >= rows) return;                                    // no workgroup barriers below
+  const long long wg = xcd_remap(blockIdx.x, gridDim.x);
+  const long long g = SPLIT > 1 ? wg : wg * WAVES + w;
+  if (g >= rows) return;                                    // a shared row: all waves; else no barriers below
   const long long bh = g / nb;
   if constexpr (COARSE) prefetch_vec_lds<D>(dqp + g * D, (lptr_t)addl[w]);
   // the row's operands are requested before its list, whose wait covers them
@@ -661,7 +688,11 @@ __global__ __launch_bounds__(WAVES * kWave) void bwd_dq_tr_kernel(
   load_rows<BF16, D>(reinterpret_cast<const elem*>(gin) + g * 32 * D, gf);
   const float lq = ld[g * 64 + jq], dl = ld[g * 64 + 32 + jq];
   int32_t* myidx = sidx_all + w * m;
-  const int cnt = stage_selection(idx + g * m, m, nb, myidx);
+  int cnt = stage_selection(idx + g * m, m, nb, myidx);
+  if constexpr (SPLIT > 1) {
+    myidx += w;
+    cnt = (cnt - w + SPLIT - 1) / SPLIT;
+  }
   wait_loads<0>();
   f32x16 acc[NT];
 #pragma unroll
@@ -673,18 +704,15 @@ __global__ __launch_bounds__(WAVES * kWave) void bwd_dq_tr_kernel(
   ro.init();
   const i32x4 krs = buffer_rsrc(static_cast<const char*>(kin) + (size_t)bh * nb * TB, (unsigned)nb * TB);
   const i32x4 vrs = buffer_rsrc(static_cast<const char*>(vin) + (size_t)bh * nb * TB, (unsigned)nb * TB);
-  const uint32_t a0 = lds_addr(slots[w][0]);
-  auto issue = [&](int y, int sl) {
-    const lptr_t dst = (lptr_t)slots[w][sl];
+  const uint32_t base = lds_addr(slots[w]);
+  auto issue = [&](int y) {
+    const lptr_t dst = (lptr_t)slots[w];
     copy_raw_pair_buf<KC, R::KP>(krs, vrs, (unsigned)y * TB, (unsigned)y * TB, ro.cp, dst, dst + TB);
   };
-#pragma unroll
-  for (int t = 0; t < SLOTS; ++t)
-    if (cnt > t) issue(list_entry(myidx + t), t);
+  if (cnt > 0) issue(list_entry(myidx));
   for (int i = 0; i < cnt; ++i) {
-    if (SLOTS == 2 && i + 1 < cnt) wait_loads<N>();         // tile i landed, i+1 may not have
-    else wait_loads<0>();
-    const uint32_t base = a0 + (uint32_t)((i % SLOTS) * SLOT);
+    const int yn = i + 1 < cnt ? list_entry(myidx + SPLIT * (i + 1)) : 0;
+    wait_loads<0>();                                        // tile i landed
     u32x4 kf[KC], vf[KC], tf[VC];
     raw_rows<0>(base, ro.rr, kf);
     raw_rows<TB>(base, ro.rr, vf);
@@ -692,7 +720,7 @@ __global__ __launch_bounds__(WAVES * kWave) void bwd_dq_tr_kernel(
     lds_done(kf);
     lds_done(vf);
     lds_done(tf);
-    if (i + SLOTS < cnt) issue(list_entry(myidx + i + SLOTS), i % SLOTS);
+    if (i + 1 < cnt) issue(yn);
     const f32x16 s = mfma_abt<KC>(kf, qf);
     const f32x16 pv = mfma_abt<KC>(vf, gf);
     float ds[16];
@@ -704,6 +732,10 @@ __global__ __launch_bounds__(WAVES * kWave) void bwd_dq_tr_kernel(
     mfma_acc_bf16<NT>(acc, pk, [&](int c) { return tf[c]; });
   }
   wait_loads<0>();
+  if constexpr (SPLIT > 1) {
+    add_parts<SPLIT>(acc, w, [&](int p) { return slots[p]; });
+    if (w != 0) return;
+  }
   store_block<BF16, D>(reinterpret_cast<elem*>(dq) + g * 32 * D, acc, scale, COARSE ? addl[w] : nullptr);
 }
 
@@ -714,33 +746,33 @@ __global__ __launch_bounds__(WAVES * kWave) void bwd_dq_tr_kernel(
 // B: ones at the positions of the first or of the second triple), so the
 // products come out as Q_i.K_j - L_i/c and G_i.V_j - delta_i, and each lane
 // needs one 16-byte read for the 16 queries it holds.
-template <int D, bool COARSE, int WAVES, int SLOTS>
-__global__ __launch_bounds__(WAVES * kWave) void bwd_dkdv_tr_kernel(
+// SPLIT > 1: SPLIT waves share the column block, wave p taking the entries p,
+// p + SPLIT, ... of its list.
+template <int D, bool COARSE, int SPLIT>
+__global__ __launch_bounds__(SPLIT * kWave) void bwd_dkdv_tr_kernel(
     const void* __restrict__ kin, const void* __restrict__ vin, const void* __restrict__ qin,
     const void* __restrict__ gin, const uint32_t* __restrict__ bits,
     const uint32_t* __restrict__ bias, const float* __restrict__ dkp, const float* __restrict__ dvp,
-    void* __restrict__ dk, void* __restrict__ dv, int nb, long long rows, float scale,
-    float scale_log2) {
+    void* __restrict__ dk, void* __restrict__ dv, int nb, float scale, float scale_log2) {
   using Cfg = TileCfg<BF16, D>;
   using elem = typename Cfg::elem;
   using R = RawB<D>;
   constexpr int KC = Cfg::kKChunks, VC = Cfg::kVChunks, NT = Cfg::kNT;
   constexpr int TB = R::TB, RB = 32 * 16;                   // bytes of a raw tile, of a block-row's bias operands
-  constexpr int N = 2 * KC + 2;                             // loads per tile
   constexpr int SLOT = 2 * TB + RB;
   static_assert(KC == R::KC && KC <= 4 && VC <= 4, "raw tiles of d <= 64");
-  static_assert(SLOTS == 1 || SLOTS == 2, "tiles in flight per wave");
-  __shared__ __attribute__((aligned(16))) unsigned char slots[WAVES][SLOTS][SLOT];
-  __shared__ __attribute__((aligned(16))) float addl[WAVES][2][COARSE ? add_lds_floats(D) : 1];
+  __shared__ __attribute__((aligned(16))) unsigned char slots[SPLIT][SLOT];
+  __shared__ __attribute__((aligned(16))) float addl[2][COARSE ? add_lds_floats(D) : 1];
   extern __shared__ int32_t sidx_all[];
   const int w = wave_uniform(threadIdx.x / kWave);
   const int lane = lane_id();
-  const long long gy = xcd_remap(blockIdx.x, gridDim.x) * (long long)WAVES + w;
-  if (gy >= rows) return;                                   // no workgroup barriers below
+  const long long gy = xcd_remap(blockIdx.x, gridDim.x);    // one workgroup per column block
   const long long bh = gy / nb;
   if constexpr (COARSE) {
-    prefetch_vec_lds<D>(dkp + gy * D, (lptr_t)addl[w][0]);
-    prefetch_vec_lds<D>(dvp + gy * D, (lptr_t)addl[w][1]);
+    if (w == 0) {
+      prefetch_vec_lds<D>(dkp + gy * D, (lptr_t)addl[0]);
+      prefetch_vec_lds<D>(dvp + gy * D, (lptr_t)addl[1]);
+    }
   }
   const int y = (int)(gy - bh * nb);
   const long long hb = bh * nb;
@@ -752,7 +784,11 @@ __global__ __launch_bounds__(WAVES * kWave) void bwd_dkdv_tr_kernel(
   load_rows<BF16, D>(reinterpret_cast<const elem*>(vin) + gy * 32 * D, vf);
   // block-rows whose selection holds y, ascending
   int32_t* myx = sidx_all + w * nb;
-  const int cnt = column_list(bits, hb, nbw, y, nb, myx);
+  int cnt = column_list(bits, hb, nbw, y, nb, myx);
+  if constexpr (SPLIT > 1) {
+    myx += w;
+    cnt = (cnt - w + SPLIT - 1) / SPLIT;
+  }
   wait_loads<0>();
   f32x16 ak[NT], av[NT];
 #pragma unroll
@@ -769,21 +805,18 @@ __global__ __launch_bounds__(WAVES * kWave) void bwd_dkdv_tr_kernel(
   const i32x4 qrs = buffer_rsrc(static_cast<const char*>(qin) + (size_t)hb * TB, (unsigned)nb * TB);
   const i32x4 grs = buffer_rsrc(static_cast<const char*>(gin) + (size_t)hb * TB, (unsigned)nb * TB);
   const i32x4 brs = buffer_rsrc(reinterpret_cast<const char*>(bias) + (size_t)hb * RB, (unsigned)nb * RB);
-  const uint32_t a0 = lds_addr(slots[w][0]);
+  const uint32_t base = lds_addr(slots[w]);
   const uint32_t boff = (uint32_t)(2 * TB) + 16u * (lane & 31);   // this lane's query's bias operand
-  auto issue = [&](int x, int sl) {
-    const lptr_t dst = (lptr_t)slots[w][sl];
+  auto issue = [&](int x) {
+    const lptr_t dst = (lptr_t)slots[w];
     copy_raw_pair_buf<KC, R::KP>(qrs, grs, (unsigned)x * TB, (unsigned)x * TB, ro.cp, dst, dst + TB);
     mra_raw_buffer_load_lds(brs, dst + 2 * TB, 4, lane * 4, x * RB, 0, 0);
     mra_raw_buffer_load_lds(brs, dst + 2 * TB + 256, 4, lane * 4, x * RB + 256, 0, 0);
   };
-#pragma unroll
-  for (int t = 0; t < SLOTS; ++t)
-    if (cnt > t) issue(list_entry(myx + t), t);
+  if (cnt > 0) issue(list_entry(myx));
   for (int i = 0; i < cnt; ++i) {
-    if (SLOTS == 2 && i + 1 < cnt) wait_loads<N>();         // tile i landed, i+1 may not have
-    else wait_loads<0>();
-    const uint32_t base = a0 + (uint32_t)((i % SLOTS) * SLOT);
+    const int xn = i + 1 < cnt ? list_entry(myx + SPLIT * (i + 1)) : 0;
+    wait_loads<0>();                                        // tile i landed
     u32x4 qa[KC], ga[KC], qt[VC], gtc[VC], ba[1];
     raw_rows<0>(base, ro.rr, qa);
     raw_rows<TB>(base, ro.rr, ga);
@@ -795,7 +828,7 @@ __global__ __launch_bounds__(WAVES * kWave) void bwd_dkdv_tr_kernel(
     lds_done(qt);
     lds_done(gtc);
     lds_done(ba);
-    if (i + SLOTS < cnt) issue(list_entry(myx + i + SLOTS), i % SLOTS);
+    if (i + 1 < cnt) issue(xn);
     const f32x16 s = mfma_abt_from<KC>(qa, kf, ba[0], ones_l);   // lane: key, 16 queries
     const f32x16 pv = mfma_abt_from<KC>(ga, vf, ba[0], ones_d);
     float a[16], ds[16];
@@ -811,8 +844,15 @@ __global__ __launch_bounds__(WAVES * kWave) void bwd_dkdv_tr_kernel(
     mfma_acc_bf16<NT>(ak, pd8, [&](int c) { return qt[c]; });
   }
   wait_loads<0>();
-  store_block<BF16, D>(reinterpret_cast<elem*>(dk) + gy * 32 * D, ak, scale, COARSE ? addl[w][0] : nullptr);
-  store_block<BF16, D>(reinterpret_cast<elem*>(dv) + gy * 32 * D, av, 1.0f, COARSE ? addl[w][1] : nullptr);
+  if constexpr (SPLIT > 1) {
+    auto slot = [&](int p) { return slots[p]; };
+    add_parts<SPLIT>(ak, w, slot);
+    __syncthreads();                                        // wave 0 has read them
+    add_parts<SPLIT>(av, w, slot);
+    if (w != 0) return;
+  }
+  store_block<BF16, D>(reinterpret_cast<elem*>(dk) + gy * 32 * D, ak, scale, COARSE ? addl[0] : nullptr);
+  store_block<BF16, D>(reinterpret_cast<elem*>(dv) + gy * 32 * D, av, 1.0f, COARSE ? addl[1] : nullptr);
 }
 
 // bfloat16, d = 128: raw 8 KB tiles of 32 rows x 256 bytes under the same
@@ -1375,14 +1415,22 @@ static void launch_tiles_t(const BwdArgs& A, hipStream_t stream) {
   const size_t smem_dq = (size_t)kBwdTileWaves * A.m * sizeof(int32_t);
   constexpr int W = kBwdTileWaves;
   if constexpr (DT == BF16 && Cfg::kKChunks <= 4 && Cfg::kVChunks <= 4) {
-    bwd_dq_tr_kernel<D, COARSE, W, kDqSlots><<<wgs, W * kWave, smem_dq, stream>>>(
-        A.q, A.dout, A.k, A.v, A.idx, A.ld, A.dqp, A.dq, nb, A.m, rows, scale, scale_log2);
-    // one wave per workgroup in every column pass: column lists differ in
-    // length (a workgroup keeps its resources until its longest list is
-    // done), rows all have m tiles
-    bwd_dkdv_tr_kernel<D, COARSE, 1, kDkdvSlots><<<(unsigned)rows, kWave, nb * sizeof(int32_t), stream>>>(
-        A.k, A.v, A.q, A.dout, A.bits, A.bias, A.dkp, A.dvp, A.dk, A.dv, nb, rows, scale,
-        scale_log2);
+    // one column block per workgroup in every column pass: column lists differ in
+    // length (a workgroup keeps its resources until its longest list is done),
+    // rows all have m tiles
+    const int split = row_split(rows, A.m);
+#define MRA_DQ(S) \
+  bwd_dq_tr_kernel<D, COARSE, S == 1 ? W : S, S><<<S == 1 ? wgs : (unsigned)rows, (S == 1 ? W : S) * kWave, \
+      (S == 1 ? W : S) * A.m * sizeof(int32_t), stream>>>( \
+      A.q, A.dout, A.k, A.v, A.idx, A.ld, A.dqp, A.dq, nb, A.m, rows, scale, scale_log2)
+#define MRA_DKDV(S) \
+  bwd_dkdv_tr_kernel<D, COARSE, S><<<(unsigned)rows, S * kWave, S * nb * sizeof(int32_t), stream>>>( \
+      A.k, A.v, A.q, A.dout, A.bits, A.bias, A.dkp, A.dvp, A.dk, A.dv, nb, scale, scale_log2)
+    if (split == 4) { MRA_DQ(4); MRA_DKDV(4); }
+    else if (split == 2) { MRA_DQ(2); MRA_DKDV(2); }
+    else { MRA_DQ(1); MRA_DKDV(1); }
+#undef MRA_DQ
+#undef MRA_DKDV
   } else if constexpr (DT == BF16 && D == 128) {
     auto kernel = bwd_dq_tr128_kernel<COARSE, W>;
     // in rounds, where a head's K and V exceed an XCD's L2, with the waves kept

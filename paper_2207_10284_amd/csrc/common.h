@@ -10,6 +10,7 @@ namespace mra {
 
 constexpr int kBlock = 32;          // MRA-2 coarse block size b (R = {32, 1})
 constexpr int kWave = 64;
+constexpr int kCus = 256;           // MI355X
 constexpr float kLog2e = 1.4426950408889634f;
 constexpr float kLn2 = 0.6931471805599453f;
 
@@ -152,6 +153,22 @@ inline long long resident_items(Kernel kernel, int threads, size_t smem, int ite
       hipOccupancyMaxActiveBlocksPerMultiprocessor(&wgs, kernel, threads, smem) != hipSuccess)
     return 0;
   return (long long)cus * wgs * items_per_wg;
+}
+
+// Waves that share a block-row (or column block) of up to m tiles in the tile
+// passes, so that few rows still occupy the chip: four up to one row per CU, two
+// up to four rows per CU. Every wave of a row holds its fixed operand and stages
+// its list and the sums are added at the end, so beyond that it costs more than
+// it gives. Measured per call (GPU time, us; 1, 2 and 4 waves per row):
+//   16 rows, float32 d = 64, 4 tiles, forward:      21.5  17.0  16.4
+//   192 rows, bfloat16 d = 64, 8 tiles, training:   48.1  40.0  38.8
+//   256 rows, bfloat16 d = 64, 16 tiles, training:  64.7  48.9  44.5
+//   768 rows, bfloat16 d = 64, 16 tiles, training:  70.9  63.6  69.1
+//   1024 rows, bfloat16 d = 64, 16 tiles, forward:  25.2  23.8  26.6
+//   1536 rows, bfloat16 d = 64, 8 tiles, training:  66.6  70.0  81.2
+inline int row_split(long long rows, int m) {
+  if (m < 2 || rows > 4 * kCus) return 1;
+  return rows <= kCus && m >= 3 ? 4 : 2;
 }
 
 // Make LDS writes of this wave visible to the wave's other lanes.

@@ -383,7 +383,11 @@ constexpr int kStreamWaves = 4;
 // HALVES = 2 (float32 rows of 128 columns): the workgroup's two waves share one
 // block-row, each working on 64 of the columns like the d = 64 kernel, with one
 // exchange per tile: the scores are the sum of the two waves' products.
-template <int DT, int D, bool COARSE, int WAVES, int HALVES>
+//
+// SPLIT > 1: the workgroup's SPLIT waves share one block-row, wave p taking the
+// tiles p, p + SPLIT, ... of its list with a reference of its own; the sums are
+// brought to one reference and added through LDS at the end.
+template <int DT, int D, bool COARSE, int WAVES, int HALVES, int SPLIT>
 __global__ __launch_bounds__(WAVES * kWave) void tile_stream_kernel(
     const void* __restrict__ qv, const void* __restrict__ kv, const void* __restrict__ vv,
     const int32_t* __restrict__ idx, const float* __restrict__ cmax,
@@ -395,6 +399,7 @@ __global__ __launch_bounds__(WAVES * kWave) void tile_stream_kernel(
   static_assert(CH <= 16, "operands of a tile are held in registers");
   static_assert(DT == BF16 || D <= 64, "raw tiles: bfloat16, or float32 with at most 64 columns per wave");
   static_assert(HALVES == 1 || (HALVES == 2 && DT == F32 && WAVES == 2), "a pair of waves per row");
+  static_assert(SPLIT == 1 || (SPLIT == WAVES && HALVES == 1), "a workgroup per row");
   constexpr int DR = D * HALVES;                     // columns of a row
   constexpr bool F32RAW = DT == F32;
   constexpr int D2 = F32RAW ? 2 * D : D;             // the bfloat16 geometry of the K tile
@@ -409,14 +414,16 @@ __global__ __launch_bounds__(WAVES * kWave) void tile_stream_kernel(
   constexpr bool kTermAhead = COARSE && D2 >= 128;
   __shared__ __attribute__((aligned(16))) float cvl[WAVES][kTermAhead ? add_lds_floats(D) : 1];
   __shared__ __attribute__((aligned(16))) float ex[HALVES == 2 ? 2 : 1][2][HALVES == 2 ? 16 * kWave : 1];
+  __shared__ float ml[SPLIT > 1 ? SPLIT : 1][2][SPLIT > 1 ? kWave : 1];
   extern __shared__ int32_t sidx_all[];
 
   const int w = wave_uniform(threadIdx.x / kWave);
   const int lane = lane_id();
   const long long wg = xcd_remap(blockIdx.x, gridDim.x);
-  // global block-row (rows row0 .. rows - 1); a pair's workgroup has one row
-  const long long g = HALVES == 2 ? row0 + wg : row0 + wg * WAVES + w;
-  if (g >= rows) return;                             // a pair: both waves; else no barriers below
+  // global block-row (rows row0 .. rows - 1); one per workgroup where waves share it
+  const long long g = HALVES == 2 || SPLIT > 1 ? row0 + wg : row0 + wg * WAVES + w;
+  if (g >= rows) return;                             // waves that share a row: all; else no barriers below
+  const int part = SPLIT > 1 ? w : 0;                // this wave's tiles: part, part + SPLIT, ...
   const int col0 = HALVES == 2 ? w * D : 0;          // this wave's first column
   float cmaxg = 0.0f, csumg = 0.0f;
   if constexpr (kTermAhead) {
@@ -433,6 +440,10 @@ __global__ __launch_bounds__(WAVES * kWave) void tile_stream_kernel(
   TileRow<DT, D, COARSE, HALVES> row;
   row.init(reinterpret_cast<const elem*>(qv) + hoff, x, scale_log2);
   m = stage_selection(idx + g * m, m, nb, myidx);  // valid entries only, in order
+  if constexpr (SPLIT > 1) {
+    myidx += part;
+    m = (m - part + SPLIT - 1) / SPLIT;
+  }
   wait_loads<0>();                                 // Q_x too (the list's loads came after it)
   // the head's K and V rows (tile y at byte y * 32 d e)
   constexpr unsigned TILE = KC * 1024u * HALVES;
@@ -505,7 +516,7 @@ __global__ __launch_bounds__(WAVES * kWave) void tile_stream_kernel(
     if (m > 0) issue(list_entry(myidx));
     for (int i = 0; i < m; ++i) {
       const bool more = i + 1 < m;                   // wave-uniform
-      const int yn = more ? list_entry(myidx + i + 1) : 0;
+      const int yn = more ? list_entry(myidx + SPLIT * (i + 1)) : 0;
       wait_loads<0>();                               // tile i is in the slot
       u32x4 kf[KC], vf[VC];
       const uint32_t base = lds_addr(slot_all[w]);
@@ -531,7 +542,7 @@ __global__ __launch_bounds__(WAVES * kWave) void tile_stream_kernel(
     // some weight grew too large: again, relative to the row's exact max
     float mx = -INFINITY;
     for (int i = 0; i < m; ++i) {
-      const int yy = list_entry(myidx + i);
+      const int yy = list_entry(myidx + SPLIT * i);
       u32x4 kf[KC];
       const u32x4* krow = reinterpret_cast<const u32x4*>(reinterpret_cast<const elem*>(kslab + (size_t)yy * TILE) +
                                                          (long long)j * DR + col0 + (D / 2) * h);
@@ -541,6 +552,49 @@ __global__ __launch_bounds__(WAVES * kWave) void tile_stream_kernel(
     }
     row.restart(mx);
     pass(false);
+  }
+  if constexpr (SPLIT > 1) {
+    // every wave's (reference, sum) and the accumulators of waves 1 .. SPLIT - 1
+    // (a slot holds 32 x d floats)
+    const float l = halves_sum(row.lrun);
+    ml[w][0][lane] = row.mrun;
+    ml[w][1][lane] = l;
+    if (w != 0) {
+      f32x4* to = reinterpret_cast<f32x4*>(slot_all[w]) + lane;
+#pragma unroll
+      for (int t = 0; t < NT; ++t)
+#pragma unroll
+        for (int q = 0; q < 4; ++q)
+          to[(4 * t + q) * kWave] = f32x4{row.o[t][4 * q], row.o[t][4 * q + 1], row.o[t][4 * q + 2], row.o[t][4 * q + 3]};
+    }
+    __syncthreads();
+    if (w != 0) return;
+    float M = row.mrun;
+#pragma unroll
+    for (int p = 1; p < SPLIT; ++p) M = fmaxf(M, ml[p][0][lane]);
+    auto factor = [&](float ref) { return ref == -INFINITY ? 0.0f : exp2f(ref - M); };   // no tile: no weight
+    const float a0 = factor(row.mrun);
+    float lt = l * a0;
+#pragma unroll
+    for (int t = 0; t < NT; ++t)
+#pragma unroll
+      for (int r = 0; r < 16; ++r) row.o[t][r] *= a0;
+#pragma unroll
+    for (int p = 1; p < SPLIT; ++p) {
+      const float a = factor(ml[p][0][lane]);
+      lt = fmaf(ml[p][1][lane], a, lt);
+      const f32x4* from = reinterpret_cast<const f32x4*>(slot_all[p]) + lane;
+#pragma unroll
+      for (int t = 0; t < NT; ++t)
+#pragma unroll
+        for (int q = 0; q < 4; ++q) {
+          const f32x4 v = from[(4 * t + q) * kWave];
+#pragma unroll
+          for (int e = 0; e < 4; ++e) row.o[t][4 * q + e] = fmaf(v[e], a, row.o[t][4 * q + e]);
+        }
+    }
+    row.mrun = M;
+    row.lrun = h == 0 ? lt : 0.0f;                   // finish() adds the halves
   }
   if constexpr (kTermAhead) {
     wait_loads<0>();                                 // the coarse-term vector is in LDS
@@ -566,17 +620,21 @@ __global__ __launch_bounds__(WAVES * kWave) void tile_stream_kernel(
 // 32768 x 128 bfloat16, budget 32: 490 us with the wait, 548 without. Heads that
 // fit L2 are launched whole (a launch per round costs more than it saves there)
 // and without the wait.
-template <int DT, int D, bool COARSE, int HALVES>
-static void launch_stream_c(const void* q, const void* k, const void* v, const int32_t* idx,
+//
+// Where the block-rows alone leave most of the chip idle, two or four waves
+// share a row (row_split).
+template <int DT, int D, bool COARSE, int HALVES, int SPLIT>
+static void launch_stream_s(const void* q, const void* k, const void* v, const int32_t* idx,
                             const float* cmax, const float* csum, const float* cvec, void* out,
                             float* lse, long long bh, int n, int m, float scale_log2, hipStream_t stream) {
-  constexpr int W = HALVES == 2 ? 2 : kStreamWaves, R = W / HALVES;   // waves, block-rows per workgroup
+  // waves, block-rows per workgroup
+  constexpr int W = SPLIT > 1 ? SPLIT : (HALVES == 2 ? 2 : kStreamWaves), R = SPLIT > 1 ? 1 : W / HALVES;
   const int nb = n / kBlock;
   const long long rows = bh * nb;
   const size_t smem = (size_t)W * m * sizeof(int32_t);     // per-wave selection lists
-  auto kernel = tile_stream_kernel<DT, D, COARSE, W, HALVES>;
+  auto kernel = tile_stream_kernel<DT, D, COARSE, W, HALVES, SPLIT>;
   const size_t head_kv = (size_t)2 * n * D * HALVES * (DT == BF16 ? 2 : 4);
-  long long chunk = head_kv > kL2PerXcd ? resident_items(kernel, W * kWave, smem, R) : 0;
+  long long chunk = SPLIT == 1 && head_kv > kL2PerXcd ? resident_items(kernel, W * kWave, smem, R) : 0;
   if (chunk <= 0) chunk = rows;
   for (long long r0 = 0; r0 < rows; r0 += chunk) {
     const long long r1 = r0 + chunk < rows ? r0 + chunk : rows;
@@ -584,6 +642,20 @@ static void launch_stream_c(const void* q, const void* k, const void* v, const i
     kernel<<<blocks, W * kWave, smem, stream>>>(q, k, v, idx, cmax, csum, cvec, out, lse, n, nb, m, r0, r1,
                                                 chunk < rows, scale_log2);
   }
+}
+
+template <int DT, int D, bool COARSE, int HALVES>
+static void launch_stream_c(const void* q, const void* k, const void* v, const int32_t* idx,
+                            const float* cmax, const float* csum, const float* cvec, void* out,
+                            float* lse, long long bh, int n, int m, float scale_log2, hipStream_t stream) {
+  if constexpr (HALVES == 1) {
+    const int split = row_split(bh * (n / kBlock), m);
+    if (split == 4)
+      return launch_stream_s<DT, D, COARSE, 1, 4>(q, k, v, idx, cmax, csum, cvec, out, lse, bh, n, m, scale_log2, stream);
+    if (split == 2)
+      return launch_stream_s<DT, D, COARSE, 1, 2>(q, k, v, idx, cmax, csum, cvec, out, lse, bh, n, m, scale_log2, stream);
+  }
+  launch_stream_s<DT, D, COARSE, HALVES, 1>(q, k, v, idx, cmax, csum, cvec, out, lse, bh, n, m, scale_log2, stream);
 }
 
 template <int DT, int D, int HALVES = 1>

@@ -323,3 +323,15 @@ def test_backward_columns_by_list_length(gpu, n, m):
     err = float((f(alone[2])[0] - dvr).abs().max() / dvr.abs().max())
     print("  dv err", err, flush=True)
     assert err <= GRAD_TOL["bf16"]
+
+
+@pytest.mark.parametrize("d", [32, 64])
+@pytest.mark.parametrize("B,H,n,m", [(1, 1, 512, 1), (1, 1, 512, 2), (1, 1, 512, 3), (1, 2, 2752, 5), (1, 8, 4096, 2),
+                                     (1, 9, 4096, 2)])
+def test_backward_rows_shared_by_waves(gpu, d, B, H, n, m):
+    """bfloat16 gradients with one, two and four waves per block-row and column
+    block (both sides of the lines at 256 and 1024 of them), lists shorter than
+    the waves that share them included."""
+    _say("shared rows backward", d, B, H, n, m)
+    q, k, v, g = _case(900 + n + m, B, H, n, d, "bf16", m)
+    _check(gpu, "mra2", q, k, v, g, m, "bf16", heads=[(0, 0), (0, H - 1)])

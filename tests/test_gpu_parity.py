@@ -331,3 +331,40 @@ def test_workload_full_size(gpu, name):
     record("MRA-2", name, w.dtype, w.B * w.H, w.B * w.H * w.nb, st, TOL[w.dtype], differ)
     _say(f"  {name}: max row rel err {st['row']:.3e} over {w.B * w.H * w.nb} block-rows, tie swaps {differ}")
     assert st["row"] <= TOL[w.dtype]
+
+
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
+@pytest.mark.parametrize("d", [32, 64, 128])
+@pytest.mark.parametrize("B,H,n,m", [(1, 1, 512, 1), (1, 1, 512, 2), (1, 1, 512, 3), (1, 1, 512, 5), (1, 2, 4096, 9),
+                                     (1, 3, 2752, 7), (1, 8, 4096, 3), (1, 9, 4096, 3)])
+def test_rows_shared_by_waves(gpu, dtype, d, B, H, n, m):
+    """16 to 1152 block-rows: one, two or four waves per row (by the number of
+    rows, at most one per tile), tiles that do not divide among the waves, and
+    both sides of the lines at 256 and 1024 rows."""
+    _say("shared rows", dtype, d, B, H, n, m)
+    q, k, v = inputs.random_qkv(5000 + n + m + d, B, H, n, d, dtype, scale=1.3)
+    _, _, err, _ = _forward_and_check(gpu, q, k, v, m, dtype)
+    _say("  err", err)
+
+
+@pytest.mark.parametrize("d", [32, 64, 128])
+def test_shared_rows_without_valid_entries(gpu, d):
+    """Rows whose list holds fewer valid entries than the waves that share it
+    (none, one, two of four): the waves without a tile add nothing."""
+    n = 256
+    q, k, v = inputs.random_qkv(5100 + d, 1, 1, n, d, "bf16")
+    idx = np.full((1, 1, 8, 4), -1, np.int32)
+    for x in range(1, 8):
+        idx[0, 0, x, :x % 4] = np.arange(x % 4) * 2
+    tq, tk, tv = (dev(a, "bf16") for a in (q, k, v))
+    M = torch.full((1, 1, 8), 0.5, device="cuda")
+    c = torch.full((1, 1, 8), 32.0, device="cuda")
+    L = torch.full((1, 1, 8, d), 16.0, device="cuda")
+    out = host(gpu.block_sddmm_spmm(tq, tk, tv, torch.from_numpy(idx).cuda(), M, c, L))[0, 0]
+    qd, kd, vd = (a[0, 0].astype(np.float64) for a in (q, k, v))
+    for x in range(8):
+        cols = np.concatenate([np.arange(32 * y, 32 * y + 32) for y in idx[0, 0, x] if y >= 0] or [np.arange(0)])
+        P = qd[32 * x:32 * x + 32] @ kd[cols].T / math.sqrt(d)
+        E = np.exp(P)
+        ref = (E @ vd[cols] + np.exp(0.5) * 16.0) / (E.sum(1, keepdims=True) + np.exp(0.5) * 32.0)
+        assert row_rel_err(out[32 * x:32 * x + 32], ref) <= TOL["bf16"], x
