@@ -624,6 +624,44 @@ struct RawTrB {
   }
 };
 
+// The operands of the coarse-term gradients of a column block (see
+// bwd_cols_kernel), for the passes that form them on their own: with few column
+// blocks per head a launch for them costs more than their sums.
+struct ColTerms {
+  const float *dS, *qp, *W, *gh;
+};
+constexpr int kOwnBlocks = 32;
+
+// out (LDS, D floats) = f sum_x A[x, y] B[x, :] over the head's nb <= kOwnBlocks
+// block-rows, in ascending order (one wave, lanes over the dims).
+template <int D>
+__device__ __forceinline__ void own_term(const float* __restrict__ A, const float* __restrict__ B, long long hb, int y,
+                                         int nb, float f, float* out) {
+  const int lane = lane_id();
+  constexpr int P = (D + kWave - 1) / kWave;
+  float acc[P];
+#pragma unroll
+  for (int p = 0; p < P; ++p) acc[p] = 0.0f;
+  constexpr int UB = 8;                                     // block-rows per batch of loads
+  for (int x0 = 0; x0 < nb; x0 += UB) {
+    float a[UB], b[UB][P];
+#pragma unroll
+    for (int u = 0; u < UB; ++u) {
+      const long long x = hb + min(x0 + u, nb - 1);
+      a[u] = x0 + u < nb ? A[x * nb + y] : 0.0f;
+#pragma unroll
+      for (int p = 0; p < P; ++p) b[u][p] = B[x * D + min(p * kWave + lane, D - 1)];
+    }
+#pragma unroll
+    for (int u = 0; u < UB; ++u)
+#pragma unroll
+      for (int p = 0; p < P; ++p) acc[p] = fmaf(a[u], b[u][p], acc[p]);
+  }
+#pragma unroll
+  for (int p = 0; p < P; ++p)
+    if (p * kWave + lane < D) out[p * kWave + lane] = acc[p] * f;
+}
+
 // Adds the accumulators of waves 1 .. SPLIT - 1 to wave 0's through LDS: `slot`
 // (w) is wave w's own LDS region of 32 x d floats, idle by now. Every wave calls
 // it; only wave 0's acc is the sum afterwards.
@@ -658,8 +696,11 @@ __device__ __forceinline__ void add_parts(f32x16 (&acc)[NT], int w, Slot slot) {
 // and V_y (K^T is read transposed from the K tile). The next tile is copied once
 // the current one is in registers. SPLIT > 1: the workgroup's waves share one
 // block-row, wave p taking the tiles p, p + SPLIT, ...
+// wg: the logical workgroup; slots, addl, lists: the workgroup's LDS (WAVES
+// slots of 2 tiles, WAVES vectors, WAVES lists of m entries).
 template <int D, bool COARSE, int WAVES, int SPLIT>
-__global__ __launch_bounds__(WAVES * kWave) void bwd_dq_tr_kernel(
+__device__ __forceinline__ void dq_tr_body(
+    long long wg, unsigned char* slots, float* addl, int32_t* lists,
     const void* __restrict__ qin, const void* __restrict__ gin, const void* __restrict__ kin,
     const void* __restrict__ vin, const int32_t* __restrict__ idx,
     const float* __restrict__ ld, const float* __restrict__ dqp, void* __restrict__ dq, int nb,
@@ -672,22 +713,19 @@ __global__ __launch_bounds__(WAVES * kWave) void bwd_dq_tr_kernel(
   constexpr int SLOT = 2 * TB;
   static_assert(KC == R::KC && KC <= 4 && VC <= 4, "raw tiles of d <= 64");
   static_assert(SPLIT == 1 || SPLIT == WAVES, "a workgroup per row");
-  __shared__ __attribute__((aligned(16))) unsigned char slots[WAVES][SLOT];
-  __shared__ __attribute__((aligned(16))) float addl[WAVES][COARSE ? add_lds_floats(D) : 1];
-  extern __shared__ int32_t sidx_all[];
   const int w = wave_uniform(threadIdx.x / kWave);
   const int lane = lane_id(), jq = lane & 31;
-  const long long wg = xcd_remap(blockIdx.x, gridDim.x);
   const long long g = SPLIT > 1 ? wg : wg * WAVES + w;
   if (g >= rows) return;                                    // a shared row: all waves; else no barriers below
   const long long bh = g / nb;
-  if constexpr (COARSE) prefetch_vec_lds<D>(dqp + g * D, (lptr_t)addl[w]);
+  float* add = addl + w * add_lds_floats(D);
+  if constexpr (COARSE) prefetch_vec_lds<D>(dqp + g * D, (lptr_t)add);
   // the row's operands are requested before its list, whose wait covers them
   u32x4 qf[KC], gf[KC];
   load_rows<BF16, D>(reinterpret_cast<const elem*>(qin) + g * 32 * D, qf);
   load_rows<BF16, D>(reinterpret_cast<const elem*>(gin) + g * 32 * D, gf);
   const float lq = ld[g * 64 + jq], dl = ld[g * 64 + 32 + jq];
-  int32_t* myidx = sidx_all + w * m;
+  int32_t* myidx = lists + w * m;
   int cnt = stage_selection(idx + g * m, m, nb, myidx);
   if constexpr (SPLIT > 1) {
     myidx += w;
@@ -704,9 +742,9 @@ __global__ __launch_bounds__(WAVES * kWave) void bwd_dq_tr_kernel(
   ro.init();
   const i32x4 krs = buffer_rsrc(static_cast<const char*>(kin) + (size_t)bh * nb * TB, (unsigned)nb * TB);
   const i32x4 vrs = buffer_rsrc(static_cast<const char*>(vin) + (size_t)bh * nb * TB, (unsigned)nb * TB);
-  const uint32_t base = lds_addr(slots[w]);
+  const uint32_t base = lds_addr(slots + w * SLOT);
   auto issue = [&](int y) {
-    const lptr_t dst = (lptr_t)slots[w];
+    const lptr_t dst = (lptr_t)(slots + w * SLOT);
     copy_raw_pair_buf<KC, R::KP>(krs, vrs, (unsigned)y * TB, (unsigned)y * TB, ro.cp, dst, dst + TB);
   };
   if (cnt > 0) issue(list_entry(myidx));
@@ -733,10 +771,23 @@ __global__ __launch_bounds__(WAVES * kWave) void bwd_dq_tr_kernel(
   }
   wait_loads<0>();
   if constexpr (SPLIT > 1) {
-    add_parts<SPLIT>(acc, w, [&](int p) { return slots[p]; });
+    add_parts<SPLIT>(acc, w, [&](int p) { return slots + p * SLOT; });
     if (w != 0) return;
   }
-  store_block<BF16, D>(reinterpret_cast<elem*>(dq) + g * 32 * D, acc, scale, COARSE ? addl[w] : nullptr);
+  store_block<BF16, D>(reinterpret_cast<elem*>(dq) + g * 32 * D, acc, scale, COARSE ? add : nullptr);
+}
+
+template <int D, bool COARSE, int WAVES>
+__global__ __launch_bounds__(WAVES * kWave) void bwd_dq_tr_kernel(
+    const void* __restrict__ qin, const void* __restrict__ gin, const void* __restrict__ kin,
+    const void* __restrict__ vin, const int32_t* __restrict__ idx,
+    const float* __restrict__ ld, const float* __restrict__ dqp, void* __restrict__ dq, int nb,
+    int m, long long rows, float scale, float scale_log2) {
+  __shared__ __attribute__((aligned(16))) unsigned char slots[WAVES * 2 * RawB<D>::TB];
+  __shared__ __attribute__((aligned(16))) float addl[COARSE ? WAVES * add_lds_floats(D) : 1];
+  extern __shared__ int32_t sidx_all[];
+  dq_tr_body<D, COARSE, WAVES, 1>(xcd_remap(blockIdx.x, gridDim.x), slots, addl, sidx_all, qin, gin, kin, vin, idx, ld,
+                                  dqp, dq, nb, m, rows, scale, scale_log2);
 }
 
 // dK, dV (bf16, d <= 64): one wave per column block; a slot holds the raw
@@ -748,8 +799,12 @@ __global__ __launch_bounds__(WAVES * kWave) void bwd_dq_tr_kernel(
 // needs one 16-byte read for the 16 queries it holds.
 // SPLIT > 1: SPLIT waves share the column block, wave p taking the entries p,
 // p + SPLIT, ... of its list.
-template <int D, bool COARSE, int SPLIT>
-__global__ __launch_bounds__(SPLIT * kWave) void bwd_dkdv_tr_kernel(
+// OWN: dK~_y and dV~_y are formed here instead of read (T: their operands).
+// gy: the column block; slots, addl, lists: the workgroup's LDS (SPLIT slots of
+// 2 tiles and the bias operands, two vectors, SPLIT lists of nb entries).
+template <int D, bool COARSE, int SPLIT, bool OWN>
+__device__ __forceinline__ void dkdv_tr_body(
+    long long gy, unsigned char* slots, float* addl, int32_t* lists, const ColTerms& T,
     const void* __restrict__ kin, const void* __restrict__ vin, const void* __restrict__ qin,
     const void* __restrict__ gin, const uint32_t* __restrict__ bits,
     const uint32_t* __restrict__ bias, const float* __restrict__ dkp, const float* __restrict__ dvp,
@@ -761,17 +816,13 @@ __global__ __launch_bounds__(SPLIT * kWave) void bwd_dkdv_tr_kernel(
   constexpr int TB = R::TB, RB = 32 * 16;                   // bytes of a raw tile, of a block-row's bias operands
   constexpr int SLOT = 2 * TB + RB;
   static_assert(KC == R::KC && KC <= 4 && VC <= 4, "raw tiles of d <= 64");
-  __shared__ __attribute__((aligned(16))) unsigned char slots[SPLIT][SLOT];
-  __shared__ __attribute__((aligned(16))) float addl[2][COARSE ? add_lds_floats(D) : 1];
-  extern __shared__ int32_t sidx_all[];
   const int w = wave_uniform(threadIdx.x / kWave);
   const int lane = lane_id();
-  const long long gy = xcd_remap(blockIdx.x, gridDim.x);    // one workgroup per column block
   const long long bh = gy / nb;
   if constexpr (COARSE) {
-    if (w == 0) {
-      prefetch_vec_lds<D>(dkp + gy * D, (lptr_t)addl[0]);
-      prefetch_vec_lds<D>(dvp + gy * D, (lptr_t)addl[1]);
+    if (!OWN && w == 0) {
+      prefetch_vec_lds<D>(dkp + gy * D, (lptr_t)addl);
+      prefetch_vec_lds<D>(dvp + gy * D, (lptr_t)(addl + add_lds_floats(D)));
     }
   }
   const int y = (int)(gy - bh * nb);
@@ -783,11 +834,15 @@ __global__ __launch_bounds__(SPLIT * kWave) void bwd_dkdv_tr_kernel(
   load_rows<BF16, D>(reinterpret_cast<const elem*>(kin) + gy * 32 * D, kf);
   load_rows<BF16, D>(reinterpret_cast<const elem*>(vin) + gy * 32 * D, vf);
   // block-rows whose selection holds y, ascending
-  int32_t* myx = sidx_all + w * nb;
+  int32_t* myx = lists + w * nb;
   int cnt = column_list(bits, hb, nbw, y, nb, myx);
   if constexpr (SPLIT > 1) {
     myx += w;
     cnt = (cnt - w + SPLIT - 1) / SPLIT;
+  }
+  if constexpr (OWN) {                                      // the first and the last wave, one quantity each
+    if (w == 0) own_term<D>(T.dS, T.qp, hb, y, nb, scale, addl);
+    if (w == SPLIT - 1) own_term<D>(T.W, T.gh, hb, y, nb, 1.0f, addl + add_lds_floats(D));
   }
   wait_loads<0>();
   f32x16 ak[NT], av[NT];
@@ -805,10 +860,10 @@ __global__ __launch_bounds__(SPLIT * kWave) void bwd_dkdv_tr_kernel(
   const i32x4 qrs = buffer_rsrc(static_cast<const char*>(qin) + (size_t)hb * TB, (unsigned)nb * TB);
   const i32x4 grs = buffer_rsrc(static_cast<const char*>(gin) + (size_t)hb * TB, (unsigned)nb * TB);
   const i32x4 brs = buffer_rsrc(reinterpret_cast<const char*>(bias) + (size_t)hb * RB, (unsigned)nb * RB);
-  const uint32_t base = lds_addr(slots[w]);
+  const uint32_t base = lds_addr(slots + w * SLOT);
   const uint32_t boff = (uint32_t)(2 * TB) + 16u * (lane & 31);   // this lane's query's bias operand
   auto issue = [&](int x) {
-    const lptr_t dst = (lptr_t)slots[w];
+    const lptr_t dst = (lptr_t)(slots + w * SLOT);
     copy_raw_pair_buf<KC, R::KP>(qrs, grs, (unsigned)x * TB, (unsigned)x * TB, ro.cp, dst, dst + TB);
     mra_raw_buffer_load_lds(brs, dst + 2 * TB, 4, lane * 4, x * RB, 0, 0);
     mra_raw_buffer_load_lds(brs, dst + 2 * TB + 256, 4, lane * 4, x * RB + 256, 0, 0);
@@ -845,14 +900,53 @@ __global__ __launch_bounds__(SPLIT * kWave) void bwd_dkdv_tr_kernel(
   }
   wait_loads<0>();
   if constexpr (SPLIT > 1) {
-    auto slot = [&](int p) { return slots[p]; };
+    auto slot = [&](int p) { return slots + p * SLOT; };
     add_parts<SPLIT>(ak, w, slot);
     __syncthreads();                                        // wave 0 has read them
     add_parts<SPLIT>(av, w, slot);
     if (w != 0) return;
   }
-  store_block<BF16, D>(reinterpret_cast<elem*>(dk) + gy * 32 * D, ak, scale, COARSE ? addl[0] : nullptr);
-  store_block<BF16, D>(reinterpret_cast<elem*>(dv) + gy * 32 * D, av, 1.0f, COARSE ? addl[1] : nullptr);
+  store_block<BF16, D>(reinterpret_cast<elem*>(dk) + gy * 32 * D, ak, scale, COARSE ? addl : nullptr);
+  store_block<BF16, D>(reinterpret_cast<elem*>(dv) + gy * 32 * D, av, 1.0f, COARSE ? addl + add_lds_floats(D) : nullptr);
+}
+
+template <int D, bool COARSE>
+__global__ __launch_bounds__(kWave) void bwd_dkdv_tr_kernel(
+    const void* __restrict__ kin, const void* __restrict__ vin, const void* __restrict__ qin,
+    const void* __restrict__ gin, const uint32_t* __restrict__ bits,
+    const uint32_t* __restrict__ bias, const float* __restrict__ dkp, const float* __restrict__ dvp,
+    void* __restrict__ dk, void* __restrict__ dv, int nb, float scale, float scale_log2) {
+  __shared__ __attribute__((aligned(16))) unsigned char slots[2 * RawB<D>::TB + 32 * 16];
+  __shared__ __attribute__((aligned(16))) float addl[COARSE ? 2 * add_lds_floats(D) : 1];
+  extern __shared__ int32_t sidx_all[];
+  dkdv_tr_body<D, COARSE, 1, false>(xcd_remap(blockIdx.x, gridDim.x), slots, addl, sidx_all, ColTerms{}, kin, vin, qin,
+                                    gin, bits, bias, dkp, dvp, dk, dv, nb, scale, scale_log2);
+}
+
+// Both passes of a call with few rows in one launch (they are independent, and
+// each alone leaves most of the chip idle): workgroups 0 .. rows - 1 the column
+// blocks, whose lists can be the longer ones, then the block-rows. Training step
+// (GPU time, before -> after; up to 32 blocks per head without the column pass):
+// 12 heads x 512 x 64: 39.0 -> 32.7 us, 48 heads: 47.7 -> 43.0, 12 heads x 2048:
+// 62.5 -> 58.4; float32 12 heads x 512 x 64: 77.6 -> 64.3, 4 heads x 2048 x 128:
+// 128 -> 110.
+template <int D, bool COARSE, int SPLIT, bool OWN>
+__global__ __launch_bounds__(SPLIT * kWave) void bwd_tiles_tr_kernel(
+    ColTerms T, const void* __restrict__ qin, const void* __restrict__ gin, const void* __restrict__ kin,
+    const void* __restrict__ vin, const int32_t* __restrict__ idx, const uint32_t* __restrict__ bits,
+    const float* __restrict__ ld, const uint32_t* __restrict__ bias, const float* __restrict__ dqp,
+    const float* __restrict__ dkp, const float* __restrict__ dvp, void* __restrict__ dq, void* __restrict__ dk,
+    void* __restrict__ dv, int nb, int m, int rows, float scale, float scale_log2) {
+  __shared__ __attribute__((aligned(16))) unsigned char slots[SPLIT * (2 * RawB<D>::TB + 32 * 16)];
+  __shared__ __attribute__((aligned(16))) float addl[COARSE ? SPLIT * add_lds_floats(D) : 1];
+  extern __shared__ int32_t sidx_all[];
+  const int b = blockIdx.x;
+  if (b < rows)
+    dkdv_tr_body<D, COARSE, SPLIT, OWN>(xcd_remap(b, rows), slots, addl, sidx_all, T, kin, vin, qin, gin, bits, bias,
+                                        dkp, dvp, dk, dv, nb, scale, scale_log2);
+  else
+    dq_tr_body<D, COARSE, SPLIT, SPLIT>(xcd_remap(b - rows, rows), slots, addl, sidx_all, qin, gin, kin, vin, idx, ld,
+                                        dqp, dq, nb, m, rows, scale, scale_log2);
 }
 
 // bfloat16, d = 128: raw 8 KB tiles of 32 rows x 256 bytes under the same
@@ -1120,20 +1214,30 @@ __device__ __forceinline__ void pair_barrier() { asm volatile("s_waitcnt lgkmcnt
 // keys: they exchange the other half's values (8 per lane), form
 // dP and add K_y^T dP over their 16 keys to a full 32 x d accumulator. The two
 // accumulators are added at the end.
-template <int D, bool COARSE>
-__global__ __launch_bounds__(2 * kWave) void bwd_dq_split_kernel(
+// A workgroup's LDS in the float32 passes: REC block-row records, ADD vectors of
+// coarse-term gradients (the dQ pass needs no record and one vector: at d = 128
+// that leaves room for a third workgroup per CU).
+template <int D, int REC, int ADD>
+struct SplitLds {
+  __attribute__((aligned(16))) unsigned char slot[2][3 * RawB<D>::TB];
+  __attribute__((aligned(16))) float ex[16 * kWave];
+  __attribute__((aligned(16))) float rec[REC ? REC : 1][REC ? 64 : 4];
+  __attribute__((aligned(16))) float addl[ADD][add_lds_floats(D)];
+};
+
+template <int D, bool COARSE, class Lds>
+__device__ __forceinline__ void dq_split_body(
+    long long g, Lds& S, uint16_t* list_all,
     const void* __restrict__ qpl, const void* __restrict__ gpl, const void* __restrict__ kpl,
     const void* __restrict__ vpl, const int32_t* __restrict__ idx, const float* __restrict__ ld,
     const float* __restrict__ dqp, float* __restrict__ dq, int nb, int m, float scale, float scale_log2) {
   using R = RawB<D>;
   constexpr int KC = R::KC, NT = R::NT, TB = R::TB;
-  __shared__ __attribute__((aligned(16))) unsigned char slot[2][3 * TB];
-  __shared__ __attribute__((aligned(16))) float ex[2][8 * kWave];
-  __shared__ __attribute__((aligned(16))) float addl[COARSE ? add_lds_floats(D) : 1];
-  extern __shared__ uint16_t list_all[];                    // [2][m]
+  auto& slot = S.slot;
+  float* const ex[2] = {S.ex, S.ex + 8 * kWave};
+  float* addl = S.addl[0];
   const int w = wave_uniform(threadIdx.x / kWave);
   const int lane = lane_id(), jq = lane & 31;
-  const long long g = xcd_remap(blockIdx.x, gridDim.x);     // one workgroup per block-row
   const long long bh = g / nb;
   if constexpr (COARSE)
     if (w == 0) prefetch_vec_lds<D>(dqp + g * D, (lptr_t)addl);
@@ -1240,30 +1344,30 @@ __global__ __launch_bounds__(2 * kWave) void bwd_dq_split_kernel(
 // dK, dV (float32): a pair of waves per column block y. Wave 0 forms
 // S = Q_x K_y^T, the weights A and dV^T += G_x^T A; wave 1 forms G_x V_y^T,
 // takes the weights from wave 0 and adds dK^T += Q_x^T dP.
-template <int D, bool COARSE>
-__global__ __launch_bounds__(2 * kWave) void bwd_dkdv_split_kernel(
+template <int D, bool COARSE, bool OWN, class Lds>
+__device__ __forceinline__ void dkdv_split_body(
+    long long gy, Lds& S, uint16_t* list_all, const ColTerms& T,
     const void* __restrict__ kpl, const void* __restrict__ vpl, const void* __restrict__ qpl,
     const void* __restrict__ gpl, const uint32_t* __restrict__ bits, const float* __restrict__ ld,
     const float* __restrict__ dkp, const float* __restrict__ dvp, float* __restrict__ dk,
     float* __restrict__ dv, int nb, float scale, float scale_log2) {
   using R = RawB<D>;
   constexpr int KC = R::KC, NT = R::NT, TB = R::TB, VC = 2 * NT;
-  __shared__ __attribute__((aligned(16))) unsigned char slot[2][3 * TB];
-  __shared__ __attribute__((aligned(16))) float ex[16 * kWave];
-  __shared__ __attribute__((aligned(16))) float rec[2][64];
-  __shared__ __attribute__((aligned(16))) float addl[2][COARSE ? add_lds_floats(D) : 1];
-  extern __shared__ uint16_t list_all[];                    // [2][nb]
+  auto& slot = S.slot;
+  auto& ex = S.ex;
+  auto& rec = S.rec;
+  auto& addl = S.addl;
   const int w = wave_uniform(threadIdx.x / kWave);
   const int lane = lane_id(), h = lane >> 5;
-  const long long gy = xcd_remap(blockIdx.x, gridDim.x);    // one workgroup per column block
   const long long bh = gy / nb, hb = bh * nb;
   const int y = (int)(gy - hb);
-  if constexpr (COARSE) prefetch_vec_lds<D>((w ? dkp : dvp) + gy * D, (lptr_t)addl[w]);
+  if constexpr (COARSE && !OWN) prefetch_vec_lds<D>((w ? dkp : dvp) + gy * D, (lptr_t)addl[w]);
   u32x4 fx[3][KC];                                          // K_y or V_y, requested before the list
   load_planes<D>(w ? vpl : kpl, gy, fx);
   // block-rows whose selection holds y, ascending (each wave keeps its own list)
   uint16_t* myx = list_all + w * nb;
   const int cnt = column_list(bits, hb, (nb + 31) / 32, y, nb, myx);
+  if constexpr (OWN) own_term<D>(w ? T.dS : T.W, w ? T.qp : T.gh, hb, y, nb, w ? scale : 1.0f, addl[w]);
   wait_loads<0>();
   f32x16 acc[NT];                                           // dV^T or dK^T
 #pragma unroll
@@ -1343,6 +1447,48 @@ __global__ __launch_bounds__(2 * kWave) void bwd_dkdv_split_kernel(
   store_block<F32, D>((w ? dk : dv) + gy * 32 * D, acc, w ? scale : 1.0f, COARSE ? addl[w] : nullptr);
 }
 
+template <int D, bool COARSE>
+__global__ __launch_bounds__(2 * kWave) void bwd_dq_split_kernel(
+    const void* __restrict__ qpl, const void* __restrict__ gpl, const void* __restrict__ kpl,
+    const void* __restrict__ vpl, const int32_t* __restrict__ idx, const float* __restrict__ ld,
+    const float* __restrict__ dqp, float* __restrict__ dq, int nb, int m, float scale, float scale_log2) {
+  __shared__ SplitLds<D, 0, 1> S;
+  extern __shared__ uint16_t list_all[];                    // [2][m]
+  dq_split_body<D, COARSE>(xcd_remap(blockIdx.x, gridDim.x), S, list_all, qpl, gpl, kpl, vpl, idx, ld, dqp, dq, nb, m,
+                           scale, scale_log2);
+}
+
+template <int D, bool COARSE>
+__global__ __launch_bounds__(2 * kWave) void bwd_dkdv_split_kernel(
+    const void* __restrict__ kpl, const void* __restrict__ vpl, const void* __restrict__ qpl,
+    const void* __restrict__ gpl, const uint32_t* __restrict__ bits, const float* __restrict__ ld,
+    const float* __restrict__ dkp, const float* __restrict__ dvp, float* __restrict__ dk,
+    float* __restrict__ dv, int nb, float scale, float scale_log2) {
+  __shared__ SplitLds<D, 2, 2> S;
+  extern __shared__ uint16_t list_all[];                    // [2][nb]
+  dkdv_split_body<D, COARSE, false>(xcd_remap(blockIdx.x, gridDim.x), S, list_all, ColTerms{}, kpl, vpl, qpl, gpl, bits,
+                                    ld, dkp, dvp, dk, dv, nb, scale, scale_log2);
+}
+
+// Both in one launch (as bwd_tiles_tr_kernel).
+template <int D, bool COARSE, bool OWN>
+__global__ __launch_bounds__(2 * kWave) void bwd_tiles_split_kernel(
+    ColTerms T, const void* __restrict__ qpl, const void* __restrict__ gpl, const void* __restrict__ kpl,
+    const void* __restrict__ vpl, const int32_t* __restrict__ idx, const uint32_t* __restrict__ bits,
+    const float* __restrict__ ld, const float* __restrict__ dqp, const float* __restrict__ dkp,
+    const float* __restrict__ dvp, float* __restrict__ dq, float* __restrict__ dk, float* __restrict__ dv, int nb, int m,
+    int rows, float scale, float scale_log2) {
+  __shared__ SplitLds<D, 2, 2> S;
+  extern __shared__ uint16_t list_all[];
+  const int b = blockIdx.x;
+  if (b < rows)
+    dkdv_split_body<D, COARSE, OWN>(xcd_remap(b, rows), S, list_all, T, kpl, vpl, qpl, gpl, bits, ld, dkp, dvp, dk, dv,
+                                    nb, scale, scale_log2);
+  else
+    dq_split_body<D, COARSE>(xcd_remap(b - rows, rows), S, list_all, qpl, gpl, kpl, vpl, idx, ld, dqp, dq, nb, m, scale,
+                             scale_log2);
+}
+
 // Column blocks of each head in the order of falling list length (order
 // [bh, nb]): first the lengths, one workgroup per head and 32 columns, a lane per
 // block-row and one ballot per column.
@@ -1404,8 +1550,20 @@ __global__ __launch_bounds__(256) void bwd_order_kernel(const uint16_t* __restri
 }
 
 // ---------------------------------------------------------------------------
+// Few rows: dQ and dK/dV share one launch (bfloat16 d = 128 excepted: its two
+// kernels fill their CUs' LDS and registers differently).
+template <int DT, int D>
+static bool tiles_in_one_launch(const BwdArgs& A) {
+  const long long rows = A.bh * (A.n / kBlock);
+  if (DT == BF16) return D <= 64 && row_split(rows, A.m) > 1;
+  return rows <= 4 * kCus;
+}
+
+// own: the column blocks form dK~ and dV~ themselves (with tiles_in_one_launch).
 template <int DT, int D, bool COARSE>
-static void launch_tiles_t(const BwdArgs& A, hipStream_t stream) {
+static void launch_tiles_t(const BwdArgs& A, bool own, hipStream_t stream) {
+  const ColTerms T = {A.dS, A.qp, A.W, A.gh};
+  const bool one_launch = tiles_in_one_launch<DT, D>(A);
   using Cfg = TileCfg<DT, D>;
   const int nb = A.n / kBlock;
   const long long rows = A.bh * nb;
@@ -1419,18 +1577,21 @@ static void launch_tiles_t(const BwdArgs& A, hipStream_t stream) {
     // length (a workgroup keeps its resources until its longest list is done),
     // rows all have m tiles
     const int split = row_split(rows, A.m);
-#define MRA_DQ(S) \
-  bwd_dq_tr_kernel<D, COARSE, S == 1 ? W : S, S><<<S == 1 ? wgs : (unsigned)rows, (S == 1 ? W : S) * kWave, \
-      (S == 1 ? W : S) * A.m * sizeof(int32_t), stream>>>( \
-      A.q, A.dout, A.k, A.v, A.idx, A.ld, A.dqp, A.dq, nb, A.m, rows, scale, scale_log2)
-#define MRA_DKDV(S) \
-  bwd_dkdv_tr_kernel<D, COARSE, S><<<(unsigned)rows, S * kWave, S * nb * sizeof(int32_t), stream>>>( \
-      A.k, A.v, A.q, A.dout, A.bits, A.bias, A.dkp, A.dvp, A.dk, A.dv, nb, scale, scale_log2)
-    if (split == 4) { MRA_DQ(4); MRA_DKDV(4); }
-    else if (split == 2) { MRA_DQ(2); MRA_DKDV(2); }
-    else { MRA_DQ(1); MRA_DKDV(1); }
-#undef MRA_DQ
-#undef MRA_DKDV
+    if (split == 1) {
+      bwd_dq_tr_kernel<D, COARSE, W><<<wgs, W * kWave, smem_dq, stream>>>(
+          A.q, A.dout, A.k, A.v, A.idx, A.ld, A.dqp, A.dq, nb, A.m, rows, scale, scale_log2);
+      bwd_dkdv_tr_kernel<D, COARSE><<<(unsigned)rows, kWave, nb * sizeof(int32_t), stream>>>(
+          A.k, A.v, A.q, A.dout, A.bits, A.bias, A.dkp, A.dvp, A.dk, A.dv, nb, scale, scale_log2);
+    } else {
+      const size_t lists = (size_t)split * (nb > A.m ? nb : A.m) * sizeof(int32_t);
+#define MRA_TILES(S, OWN) \
+  bwd_tiles_tr_kernel<D, COARSE, S, OWN><<<2 * (unsigned)rows, S * kWave, lists, stream>>>( \
+      T, A.q, A.dout, A.k, A.v, A.idx, A.bits, A.ld, A.bias, A.dqp, A.dkp, A.dvp, A.dq, A.dk, A.dv, nb, A.m, \
+      (int)rows, scale, scale_log2)
+      if (split == 4) { if (own) MRA_TILES(4, COARSE); else MRA_TILES(4, false); }
+      else { if (own) MRA_TILES(2, COARSE); else MRA_TILES(2, false); }
+#undef MRA_TILES
+    }
   } else if constexpr (DT == BF16 && D == 128) {
     auto kernel = bwd_dq_tr128_kernel<COARSE, W>;
     // in rounds, where a head's K and V exceed an XCD's L2, with the waves kept
@@ -1461,11 +1622,21 @@ static void launch_tiles_t(const BwdArgs& A, hipStream_t stream) {
     bwd_dkdv_tr128_kernel<COARSE><<<(unsigned)rows, kWave, nb * sizeof(int32_t), stream>>>(
         A.k, A.v, A.q, A.dout, A.bits, order, A.bias, A.dkp, A.dvp, A.dk, A.dv, nb, rows, scale, scale_log2);
   } else {
-    bwd_dq_split_kernel<D, COARSE><<<(unsigned)rows, 2 * kWave, 2 * A.m * sizeof(uint16_t), stream>>>(
-        A.q_pl, A.g_pl, A.k_pl, A.v_pl, A.idx, A.ld, A.dqp, static_cast<float*>(A.dq), nb, A.m, scale, scale_log2);
-    bwd_dkdv_split_kernel<D, COARSE><<<(unsigned)rows, 2 * kWave, 2 * nb * sizeof(uint16_t), stream>>>(
-        A.k_pl, A.v_pl, A.q_pl, A.g_pl, A.bits, A.ld, A.dkp, A.dvp, static_cast<float*>(A.dk),
-        static_cast<float*>(A.dv), nb, scale, scale_log2);
+    if (!one_launch) {
+      bwd_dq_split_kernel<D, COARSE><<<(unsigned)rows, 2 * kWave, 2 * A.m * sizeof(uint16_t), stream>>>(
+          A.q_pl, A.g_pl, A.k_pl, A.v_pl, A.idx, A.ld, A.dqp, static_cast<float*>(A.dq), nb, A.m, scale, scale_log2);
+      bwd_dkdv_split_kernel<D, COARSE><<<(unsigned)rows, 2 * kWave, 2 * nb * sizeof(uint16_t), stream>>>(
+          A.k_pl, A.v_pl, A.q_pl, A.g_pl, A.bits, A.ld, A.dkp, A.dvp, static_cast<float*>(A.dk),
+          static_cast<float*>(A.dv), nb, scale, scale_log2);
+    } else {
+      const size_t lists = (size_t)2 * (nb > A.m ? nb : A.m) * sizeof(uint16_t);
+#define MRA_TILES(OWN) \
+  bwd_tiles_split_kernel<D, COARSE, OWN><<<2 * (unsigned)rows, 2 * kWave, lists, stream>>>( \
+      T, A.q_pl, A.g_pl, A.k_pl, A.v_pl, A.idx, A.bits, A.ld, A.dqp, A.dkp, A.dvp, static_cast<float*>(A.dq), \
+      static_cast<float*>(A.dk), static_cast<float*>(A.dv), nb, A.m, (int)rows, scale, scale_log2)
+      if (own) MRA_TILES(COARSE); else MRA_TILES(false);
+#undef MRA_TILES
+    }
   }
 }
 
@@ -1479,15 +1650,18 @@ static void launch_bwd_t(const BwdArgs& A, hipStream_t stream) {
     bwd_rows_kernel<DT, D, true><<<wg_rows, kBwdRows * kWave, 0, stream>>>(
         A.dout, A.out, A.lse, A.idx, A.qp, A.kp, A.vp, A.ld, A.bias, A.bits, A.gh, A.W, A.dS, A.dqp, nb,
         A.m, scale);
-    const unsigned wg_cols = (unsigned)(A.bh * ((nb + kBwdCols - 1) / kBwdCols));
-    bwd_cols_kernel<D><<<wg_cols, ColsCfg<D>::kWaves * kWave, 0, stream>>>(
-        A.qp, A.gh, A.W, A.dS, A.dkp, A.dvp, nb, scale);
-    launch_tiles_t<DT, D, true>(A, stream);
+    const bool own = nb <= kOwnBlocks && tiles_in_one_launch<DT, D>(A);
+    if (!own) {
+      const unsigned wg_cols = (unsigned)(A.bh * ((nb + kBwdCols - 1) / kBwdCols));
+      bwd_cols_kernel<D><<<wg_cols, ColsCfg<D>::kWaves * kWave, 0, stream>>>(
+          A.qp, A.gh, A.W, A.dS, A.dkp, A.dvp, nb, scale);
+    }
+    launch_tiles_t<DT, D, true>(A, own, stream);
   } else {
     bwd_rows_kernel<DT, D, false><<<wg_rows, kBwdRows * kWave, 0, stream>>>(
         A.dout, A.out, A.lse, A.idx, A.qp, A.kp, A.vp, A.ld, A.bias, A.bits, A.gh, A.W, A.dS, A.dqp, nb,
         A.m, scale);
-    launch_tiles_t<DT, D, false>(A, stream);
+    launch_tiles_t<DT, D, false>(A, false, stream);
   }
 }
 

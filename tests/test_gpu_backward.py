@@ -335,3 +335,17 @@ def test_backward_rows_shared_by_waves(gpu, d, B, H, n, m):
     _say("shared rows backward", d, B, H, n, m)
     q, k, v, g = _case(900 + n + m, B, H, n, d, "bf16", m)
     _check(gpu, "mra2", q, k, v, g, m, "bf16", heads=[(0, 0), (0, H - 1)])
+
+
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
+@pytest.mark.parametrize("d", [32, 64, 128])
+@pytest.mark.parametrize("H,nb", [(1, 1), (3, 32), (2, 33), (31, 33), (32, 32), (1, 40)])
+def test_backward_in_one_launch(gpu, d, dtype, H, nb):
+    """Few rows: dQ and dK/dV in one launch, with the column blocks' coarse terms
+    formed there (up to 32 blocks per head) or by the column pass (from 33), and
+    both sides of 1024 rows (31 heads of 33 blocks make 1023, 32 of 32 make
+    1024)."""
+    m = min(3, nb)
+    _say("one launch", d, dtype, H, nb)
+    q, k, v, g = _case(700 + nb + H, 1, H, 32 * nb, d, dtype, m)
+    _check(gpu, "mra2", q, k, v, g, m, dtype, heads=[(0, 0), (0, H - 1)])
