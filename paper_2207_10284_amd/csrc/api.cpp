@@ -300,19 +300,30 @@ mra_status_t levels_forward(const void* q, const void* k, const void* v, void* o
   MRA_TRY(debug_fill(fills, stream));
 
   MRA_TRY(hip_status(mra::launch_pool(q, k, v, qp, kp, vp, s.bh, n, d, (int)dtype, st)));
+  mra::PoolUp P{};
+  mra::CoarseLevels C{};
+  C.levels = levels;
   for (int l = 0; l <= fin; ++l) {
-    float* Sl = const_cast<float*>(T.S[l]);
+    float *ql = l < fin ? f32(W.qp[l]) : qp, *kl = l < fin ? f32(W.kp[l]) : kp;
     if (l < fin) {
-      float *ql = f32(W.qp[l]), *kl = f32(W.kp[l]);
-      MRA_TRY(hip_status(mra::launch_pool_up(qp, kp, vp, ql, kl, f32(W.vp[l]), s.bh * T.nb[l], d, T.r[l], st)));
-      MRA_TRY(hip_status(mra::launch_coarse(ql, kl, Sl, s.bh, T.nb[l], d, st)));
-    } else {
-      MRA_TRY(hip_status(mra::launch_coarse(qp, kp, Sl, s.bh, nb, d, st)));
+      float* const dst[3] = {ql, kl, f32(W.vp[l])};
+      for (int t = 0; t < 3; ++t) P.dst[l][t] = dst[t];
+      P.rows[l] = s.bh * T.nb[l];
+      P.r[l] = T.r[l];
     }
-    if (l > 0)
-      MRA_TRY(hip_status(mra::launch_mask_candidates(Sl, idx[l - 1], s.bh, T.nb[l], T.nb[l - 1],
-                                                     T.r[l - 1] / T.r[l], budgets[l - 1], st)));
-    if (budgets[l] > 0) MRA_TRY(hip_status(mra::launch_select(Sl, idx[l], s.bh, T.nb[l], budgets[l], st)));
+    C.qp[l] = ql;
+    C.kp[l] = kl;
+    C.S[l] = const_cast<float*>(T.S[l]);
+    C.nb[l] = T.nb[l];
+  }
+  MRA_TRY(hip_status(mra::launch_pool_up(qp, kp, vp, P, fin, d, st)));
+  MRA_TRY(hip_status(mra::launch_coarse_levels(C, s.bh, d, st)));
+  for (int l = 0; l <= fin; ++l) {
+    if (budgets[l] == 0) continue;
+    if (l == 0) MRA_TRY(hip_status(mra::launch_select(T.S[0], idx[0], s.bh, T.nb[0], budgets[0], st)));
+    else
+      MRA_TRY(hip_status(mra::launch_select_among(T.S[l], idx[l], idx[l - 1], s.bh, T.nb[l], budgets[l], T.nb[l - 1],
+                                                  budgets[l - 1], st)));
   }
   MRA_TRY(hip_status(mra::launch_coarse_term_levels(T, cmax, csum, cvec, s.bh, d, st)));
   return hip_status(mra::launch_tile(q, k, v, idx[fin], cmax, csum, cvec, out, lse_out, s.bh,

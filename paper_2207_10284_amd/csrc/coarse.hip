@@ -17,13 +17,17 @@ namespace mra {
 constexpr int kCT = 64;    // output block edge
 
 template <int D>
-__global__ __launch_bounds__(256) void coarse_kernel(const float* __restrict__ qp,
-                                                      const float* __restrict__ kp,
-                                                      float* __restrict__ S, int nb, double scale) {
-  // flattened grid: (head, block row, block column), column fastest
+__global__ __launch_bounds__(256) void coarse_kernel(CoarseLevels C, double scale) {
+  // flattened grid: (level, head, block row, block column), column fastest
+  int l = 0;
+  while (l + 1 < C.levels && blockIdx.x >= C.first[l + 1]) ++l;
+  const float *qp = C.qp[l], *kp = C.kp[l];
+  float* S = C.S[l];
+  const int nb = C.nb[l];
+  const unsigned b = blockIdx.x - C.first[l];
   const int nt = (nb + kCT - 1) / kCT;
-  const long long bh = blockIdx.x / (nt * nt);
-  const int tile = (int)(blockIdx.x - bh * nt * nt);
+  const long long bh = b / (nt * nt);
+  const int tile = (int)(b - bh * nt * nt);
   const int x0 = (tile / nt) * kCT, y0 = (tile % nt) * kCT;
   const float* qh = qp + bh * nb * D;
   const float* kh = kp + bh * nb * D;
@@ -48,15 +52,29 @@ __global__ __launch_bounds__(256) void coarse_kernel(const float* __restrict__ q
   }
 }
 
+hipError_t launch_coarse_levels(CoarseLevels C, long long bh, int d, hipStream_t stream) {
+  const double scale = 1.0 / sqrt((double)d);
+  unsigned blocks = 0;
+  for (int l = 0; l < C.levels; ++l) {
+    const unsigned nt = (unsigned)(C.nb[l] + kCT - 1) / kCT;
+    C.first[l] = blocks;
+    blocks += (unsigned)bh * nt * nt;
+  }
+  if (d == 32) coarse_kernel<32><<<blocks, 256, 0, stream>>>(C, scale);
+  else if (d == 64) coarse_kernel<64><<<blocks, 256, 0, stream>>>(C, scale);
+  else coarse_kernel<128><<<blocks, 256, 0, stream>>>(C, scale);
+  return hipGetLastError();
+}
+
 hipError_t launch_coarse(const float* qp, const float* kp, float* S, long long bh, int nb, int d,
                          hipStream_t stream) {
-  const double scale = 1.0 / sqrt((double)d);
-  const long long nt = (nb + kCT - 1) / kCT;
-  const dim3 grid((unsigned)(bh * nt * nt));
-  if (d == 32) coarse_kernel<32><<<grid, 256, 0, stream>>>(qp, kp, S, nb, scale);
-  else if (d == 64) coarse_kernel<64><<<grid, 256, 0, stream>>>(qp, kp, S, nb, scale);
-  else coarse_kernel<128><<<grid, 256, 0, stream>>>(qp, kp, S, nb, scale);
-  return hipGetLastError();
+  CoarseLevels C{};
+  C.levels = 1;
+  C.qp[0] = qp;
+  C.kp[0] = kp;
+  C.S[0] = S;
+  C.nb[0] = nb;
+  return launch_coarse_levels(C, bh, d, stream);
 }
 
 }  // namespace mra

@@ -40,7 +40,20 @@ hipError_t launch_split(const float* q, const float* k, const float* v, const fl
 hipError_t launch_pool(const void* q, const void* k, const void* v, float* qp, float* kp,
                        float* vp, long long bh, int n, int d, int dtype, hipStream_t stream);
 
-// S = qp kp^T / sqrt(d) per head, float64 accumulation, [bh, nb, nb] f32.
+constexpr int kMaxLevels = 8;      // resolutions above 1 of one call
+
+// S = qp kp^T / sqrt(d) per head and level, float64 accumulation, [bh, nb, nb]
+// f32 (first: filled in by the launcher).
+struct CoarseLevels {
+  const float *qp[kMaxLevels], *kp[kMaxLevels];
+  float* S[kMaxLevels];
+  int nb[kMaxLevels];
+  unsigned first[kMaxLevels];
+  int levels;
+};
+hipError_t launch_coarse_levels(CoarseLevels C, long long bh, int d, hipStream_t stream);
+
+// The same for one level.
 hipError_t launch_coarse(const float* qp, const float* kp, float* S, long long bh, int nb, int d,
                          hipStream_t stream);
 
@@ -50,6 +63,11 @@ hipError_t launch_fill(void* p, size_t bytes, uint32_t pattern, hipStream_t stre
 // Top-m column blocks per row of S, ascending, into idx [bh, nb, m].
 hipError_t launch_select(const float* S, int32_t* idx, long long bh, int nb, int m,
                          hipStream_t stream);
+
+// The same among the children of the parent level's kept blocks parent_idx
+// [bh, nbp, mp] (nbp = nb / r <= 1024) of each row's parent row.
+hipError_t launch_select_among(const float* S, int32_t* idx, const int32_t* parent_idx, long long bh, int nb, int m,
+                               int nbp, int mp, hipStream_t stream);
 
 // Low-resolution term (cmax, csum, cvec) of the blocks not listed in idx.
 hipError_t launch_coarse_term(const float* S, const int32_t* idx, const float* vp, float* cmax,
@@ -111,21 +129,19 @@ struct BwdArgs {
 hipError_t launch_bwd(const BwdArgs& args, hipStream_t stream);
 
 // More resolutions R = {s_0 > ... > s_{L-1} = 32, 1} (multilevel.hip).
-// Scale-32r means [bh, nb/r, d] of the scale-32 means [bh, nb, d] (f32; a NULL
-// pair is skipped); rows_out = bh * nb / r.
-hipError_t launch_pool_up(const float* qp, const float* kp, const float* vp, float* qp0,
-                          float* kp0, float* vp0, long long rows_out, int d, int r,
+// Means of several levels from the scale-32 means [bh, nb, d] (f32): level l's
+// rows[l] = bh nb / r[l] rows of each tensor into dst[l][0 .. 2].
+struct PoolUp {
+  float* dst[kMaxLevels][3];
+  long long rows[kMaxLevels];
+  int r[kMaxLevels];
+};
+hipError_t launch_pool_up(const float* qp, const float* kp, const float* vp, const PoolUp& P, int levels, int d,
                           hipStream_t stream);
-// S [bh, nb, nb] of one level in place: -inf outside the children of the
-// parent level's kept blocks idx1 [bh, nb0, m1] (nb0 = nb / r <= 1024) of each
-// row's parent row.
-hipError_t launch_mask_candidates(float* S, const int32_t* idx1, long long bh, int nb, int nb0,
-                                  int r, int m1, hipStream_t stream);
 // The levels of R = {s_0 > ... > s_{L-1} = 32, 1}: per level l the coarse
 // logits S [bh, nb_l, nb_l], the kept blocks idx [bh, nb_l, m_l] (entries
 // outside [0, nb_l) ignored), the pooled values vp [bh, nb_l, d] and
 // r_l = s_l / 32.
-constexpr int kMaxLevels = 8;
 struct LevelTerm {
   const float* S[kMaxLevels];
   const int32_t* idx[kMaxLevels];

@@ -6,11 +6,11 @@
 //  * pool_up_kernel: the scale-s_l means Q~_l, K~_l, V~_l as means of
 //    s_l / b consecutive scale-b means (eq. recursive_pooling applied further
 //    up);
-//  * mask_kernel: after level l - 1's selection (per s_{l-1}-block-row), an
-//    s_l-block-row may only keep s_l-blocks inside its parent row's kept
-//    blocks: every other entry of its row of S~_l is set to -inf, so the
-//    per-row top-m selection of select.hip picks among the candidates only
-//    (the budget m_l never exceeds their number m_{l-1} s_{l-1} / s_l);
+//  * the selection among candidates (select.hip): after level l - 1's selection
+//    (per s_{l-1}-block-row), an s_l-block-row may only keep s_l-blocks inside its
+//    parent row's kept blocks; every other score counts as -inf there, so the
+//    per-row top-m selection picks among the candidates only (the budget m_l
+//    never exceeds their number m_{l-1} s_{l-1} / s_l);
 //  * coarse_term_levels_kernel: the low-resolution part of b-block-row x,
 //    relative to its largest coarse logit M: s_l e^{S~_l[X_l,Y] - M} V~_l,Y
 //    over, at every level l, the candidate blocks Y (all s_0-blocks at level
@@ -18,57 +18,31 @@
 //    X_l did not keep (each coarse block counts the columns it spans), in the
 //    (M, c, L) form the tile pass merges.
 //
-// The coarse logits at every scale, the selections and the tile pass are the
-// kernels of the two-level path.
+// The coarse logits at every scale (one launch), the selections and the tile pass
+// are the kernels of the two-level path. The means of all levels take one launch
+// too, and no launch only prepares another one's input (masking the scores in
+// place took a launch per level): four resolutions are 8 launches instead of 13,
+// 24 heads x 4096 x 64 float32 160 -> 143 us.
 #include "common.h"
 #include "kernels.h"
 
 namespace mra {
 
 // dst[row, :] = mean of src rows r*row .. r*row + r - 1 (float32, in order);
-// blockIdx.y picks one of three tensors (a NULL pair is skipped).
+// blockIdx.y picks one of three tensors, blockIdx.z the level.
 __global__ __launch_bounds__(256) void pool_up_kernel(const float* __restrict__ s0,
                                                        const float* __restrict__ s1,
-                                                       const float* __restrict__ s2,
-                                                       float* __restrict__ d0, float* __restrict__ d1,
-                                                       float* __restrict__ d2, long long rows_out,
-                                                       int d, int r) {
-  const int which = blockIdx.y;
+                                                       const float* __restrict__ s2, PoolUp P, int d) {
+  const int which = blockIdx.y, l = blockIdx.z, r = P.r[l];
   const float* src = which == 0 ? s0 : (which == 1 ? s1 : s2);
-  float* dst = which == 0 ? d0 : (which == 1 ? d1 : d2);
-  if (src == nullptr) return;
+  float* dst = P.dst[l][which];
   const long long t = (long long)blockIdx.x * blockDim.x + threadIdx.x;
-  if (t >= rows_out * d) return;
+  if (t >= P.rows[l] * d) return;
   const long long row = t / d;
   const int c = (int)(t - row * d);
   float acc = 0.0f;
   for (int i = 0; i < r; ++i) acc += src[(row * r + i) * d + c];
   dst[t] = acc / (float)r;
-}
-
-// One wave per block-row x of a level: S[x, y] = -inf unless y / r is in
-// idx1[x / r], the parent level's kept blocks (nb0 <= 1024 parent blocks).
-__global__ __launch_bounds__(64) void mask_kernel(float* __restrict__ S,
-                                                  const int32_t* __restrict__ idx1, int nb,
-                                                  int nb0, int r, int m1) {
-  __shared__ uint32_t bm[32];                               // nb0 <= 1024
-  const long long g = blockIdx.x;                           // global b-block-row
-  const long long bh = g / nb;
-  const int x = (int)(g - bh * nb);
-  const long long G0 = bh * nb0 + x / r;
-  const int lane = lane_id();
-  if (lane < 32) bm[lane] = 0u;
-  wave_lds_sync();
-  for (int i = lane; i < m1; i += kWave) {
-    const int Y = idx1[G0 * m1 + i];
-    if (Y >= 0 && Y < nb0) atomicOr(&bm[Y >> 5], 1u << (Y & 31));
-  }
-  wave_lds_sync();
-  float* row = S + g * nb;
-  for (int y = lane; y < nb; y += kWave) {
-    const int Y = y / r;
-    if (!((bm[Y >> 5] >> (Y & 31)) & 1u)) row[y] = -INFINITY;
-  }
 }
 
 constexpr int kMlWaves = 4;
@@ -225,18 +199,12 @@ __global__ __launch_bounds__(kMlWaves * kWave) void coarse_term_levels_kernel(
   }
 }
 
-hipError_t launch_pool_up(const float* qp, const float* kp, const float* vp, float* qp0,
-                          float* kp0, float* vp0, long long rows_out, int d, int r,
+hipError_t launch_pool_up(const float* qp, const float* kp, const float* vp, const PoolUp& P, int levels, int d,
                           hipStream_t stream) {
-  const long long n = rows_out * d;
-  const dim3 grid((unsigned)((n + 255) / 256), 3);
-  pool_up_kernel<<<grid, 256, 0, stream>>>(qp, kp, vp, qp0, kp0, vp0, rows_out, d, r);
-  return hipGetLastError();
-}
-
-hipError_t launch_mask_candidates(float* S, const int32_t* idx1, long long bh, int nb, int nb0,
-                                  int r, int m1, hipStream_t stream) {
-  mask_kernel<<<(unsigned)(bh * nb), kWave, 0, stream>>>(S, idx1, nb, nb0, r, m1);
+  long long most = 0;
+  for (int l = 0; l < levels; ++l) most = P.rows[l] > most ? P.rows[l] : most;
+  const dim3 grid((unsigned)((most * d + 255) / 256), 3, (unsigned)levels);
+  pool_up_kernel<<<grid, 256, 0, stream>>>(qp, kp, vp, P, d);
   return hipGetLastError();
 }
 

@@ -31,7 +31,7 @@
 
 namespace mra {
 
-enum RowsMode { kSelectOnly = 0, kTermOnly = 1, kFused = 2, kFusedSelect = 3 };
+enum RowsMode { kSelectOnly = 0, kTermOnly = 1, kFused = 2, kFusedSelect = 3, kSelectAmong = 4 };
 constexpr int kRows = 16;                 // block-rows (waves) per workgroup
 constexpr int kChunk = 64;                // score columns per register
 constexpr int kU = 8;                     // coarse-term steps per batch of V~ loads (two float4 of weights)
@@ -52,6 +52,15 @@ struct RowsSmem {
   size_t part_off, bytes;
 };
 
+// kSelectAmong: the candidates of row x are the children of its parent row's
+// kept blocks, idx [bh, nbp, mp] of the level above (nbp <= 1024 blocks per side,
+// r children each); only they take part, as if every other score were -inf.
+struct Parent {
+  const int32_t* idx;
+  int nbp, mp, r;
+};
+constexpr int kParentWords = 32;          // 1024 bits
+
 // The select-only mode uses no LDS. In the fused modes the region after the
 // score rows first holds the 16 query rows in float64 ([16][d], element c of
 // row r at c ^ 2r: pairs stay contiguous, and the 16-byte reads of the 16
@@ -64,6 +73,10 @@ __host__ __device__ constexpr int rows_qcol(int r, int c) { return c ^ ((r & 15)
 static RowsSmem rows_smem(int jmax, int nw, int mode, int d) {
   RowsSmem L{};
   if (mode == kSelectOnly) return L;
+  if (mode == kSelectAmong) {
+    L.bytes = (size_t)kRows * kParentWords * sizeof(uint32_t);
+    return L;
+  }
   L.part_off = ((size_t)kRows * rows_ldc(jmax) * sizeof(float) + 15) & ~size_t(15);
   const size_t part = mode == kTermOnly || mode == kFused ? (size_t)nw * 16 * 16 * sizeof(float) : 0;
   const size_t qd = mode == kFused || mode == kFusedSelect ? (size_t)kRows * rows_ldq(d) * sizeof(double) : 0;
@@ -76,7 +89,7 @@ __global__ __launch_bounds__(kRows / RPW * kWave) void rows_kernel(
     const float* __restrict__ S, const float* __restrict__ qp, const float* __restrict__ kp,
     int32_t* __restrict__ idx_out, const int32_t* __restrict__ idx_in,
     const float* __restrict__ vp, float* __restrict__ cmax, float* __restrict__ csum,
-    float* __restrict__ cvec, int nb, int m, int part_off, double scale) {
+    float* __restrict__ cvec, int nb, int m, int part_off, double scale, Parent parent) {
   constexpr int NW = kRows / RPW;                                  // waves per workgroup
   constexpr int NTH = NW * kWave;
   extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
@@ -203,6 +216,22 @@ __global__ __launch_bounds__(kRows / RPW * kWave) void rows_kernel(
         const int y = kChunk * j + lane;
         if (j < J && y < nb) s[i][j] = S[g * nb + y];
       }
+      if constexpr (MODE == kSelectAmong) {
+        uint32_t* bm = reinterpret_cast<uint32_t*>(smem) + row_of(i) * kParentWords;
+        const long long gp = bh * parent.nbp + (x0 + row_of(i)) / parent.r;
+        if (lane < kParentWords) bm[lane] = 0u;
+        wave_lds_sync();
+        for (int e = lane; e < parent.mp; e += kWave) {
+          const int Y = parent.idx[gp * parent.mp + e];
+          if (Y >= 0 && Y < parent.nbp) atomicOr(&bm[Y >> 5], 1u << (Y & 31));
+        }
+        wave_lds_sync();
+#pragma unroll
+        for (int j = 0; j < JMAX; ++j) {
+          const int Y = (kChunk * j + lane) / parent.r;
+          if (j < J && kChunk * j + lane < nb && !((bm[Y >> 5] >> (Y & 31)) & 1u)) s[i][j] = -INFINITY;
+        }
+      }
     }
   }
 
@@ -292,7 +321,7 @@ __global__ __launch_bounds__(kRows / RPW * kWave) void rows_kernel(
       }
     }
   }
-  if constexpr (MODE == kSelectOnly || MODE == kFusedSelect) return;
+  if constexpr (MODE == kSelectOnly || MODE == kFusedSelect || MODE == kSelectAmong) return;
 
   // ---- phase 3: max, weights (kept in s[]) and their sum over unselected blocks
 #pragma unroll
@@ -386,7 +415,8 @@ __global__ __launch_bounds__(kRows / RPW * kWave) void rows_kernel(
 template <int MODE, int JMAX>
 static void launch_rows_j(const float* S, const float* qp, const float* kp, int32_t* idx_out,
                           const int32_t* idx_in, const float* vp, float* cmax, float* csum,
-                          float* cvec, long long bh, int nb, int d, int m, hipStream_t stream) {
+                          float* cvec, long long bh, int nb, int d, int m, hipStream_t stream,
+                          const Parent& parent) {
   const long long groups = (nb + kRows - 1) / kRows;
   const unsigned blocks = (unsigned)(bh * groups);
   constexpr int RPW = JMAX <= 16 ? 2 : 1;
@@ -397,7 +427,7 @@ static void launch_rows_j(const float* S, const float* qp, const float* kp, int3
   // one's matrix-core phases overlap another's selection
 #define MRA_ROWS_LAUNCH(DD)                                                                     \
   rows_kernel<DD, MODE, JMAX, RPW><<<blocks, 64 * kRows / RPW, L.bytes, stream>>>(            \
-      S, qp, kp, idx_out, idx_in, vp, cmax, csum, cvec, nb, m, (int)L.part_off, scale)
+      S, qp, kp, idx_out, idx_in, vp, cmax, csum, cvec, nb, m, (int)L.part_off, scale, parent)
   switch (d) {
     case 32: MRA_ROWS_LAUNCH(32); break;
     case 64: MRA_ROWS_LAUNCH(64); break;
@@ -411,15 +441,16 @@ static void launch_rows_j(const float* S, const float* qp, const float* kp, int3
 template <int MODE>
 static hipError_t launch_rows(const float* S, const float* qp, const float* kp, int32_t* idx_out,
                               const int32_t* idx_in, const float* vp, float* cmax, float* csum,
-                              float* cvec, long long bh, int nb, int d, int m, hipStream_t stream) {
+                              float* cvec, long long bh, int nb, int d, int m, hipStream_t stream,
+                              const Parent& parent = Parent{}) {
   if (nb <= 128)
-    launch_rows_j<MODE, 2>(S, qp, kp, idx_out, idx_in, vp, cmax, csum, cvec, bh, nb, d, m, stream);
+    launch_rows_j<MODE, 2>(S, qp, kp, idx_out, idx_in, vp, cmax, csum, cvec, bh, nb, d, m, stream, parent);
   else if (nb <= 512)
-    launch_rows_j<MODE, 8>(S, qp, kp, idx_out, idx_in, vp, cmax, csum, cvec, bh, nb, d, m, stream);
+    launch_rows_j<MODE, 8>(S, qp, kp, idx_out, idx_in, vp, cmax, csum, cvec, bh, nb, d, m, stream, parent);
   else if (nb <= 1024)
-    launch_rows_j<MODE, 16>(S, qp, kp, idx_out, idx_in, vp, cmax, csum, cvec, bh, nb, d, m, stream);
+    launch_rows_j<MODE, 16>(S, qp, kp, idx_out, idx_in, vp, cmax, csum, cvec, bh, nb, d, m, stream, parent);
   else
-    launch_rows_j<MODE, 32>(S, qp, kp, idx_out, idx_in, vp, cmax, csum, cvec, bh, nb, d, m, stream);
+    launch_rows_j<MODE, 32>(S, qp, kp, idx_out, idx_in, vp, cmax, csum, cvec, bh, nb, d, m, stream, parent);
   return hipGetLastError();
 }
 
@@ -427,6 +458,12 @@ hipError_t launch_select(const float* S, int32_t* idx, long long bh, int nb, int
                          hipStream_t stream) {
   return launch_rows<kSelectOnly>(S, nullptr, nullptr, idx, nullptr, nullptr, nullptr, nullptr,
                                   nullptr, bh, nb, 64, m, stream);
+}
+
+hipError_t launch_select_among(const float* S, int32_t* idx, const int32_t* parent_idx, long long bh, int nb, int m,
+                               int nbp, int mp, hipStream_t stream) {
+  return launch_rows<kSelectAmong>(S, nullptr, nullptr, idx, nullptr, nullptr, nullptr, nullptr, nullptr, bh, nb, 64, m,
+                                   stream, Parent{parent_idx, nbp, mp, nb / nbp});
 }
 
 hipError_t launch_coarse_term(const float* S, const int32_t* idx, const float* vp, float* cmax,
