@@ -66,12 +66,13 @@ def tile_floors(w) -> dict:
     resource: matrix cores (the MFMA roofline), the vector ALU (per selected
     tile and lane: 16 exponentials at quarter rate plus, for bfloat16, 16 FMA,
     8 conversions and 8 row-sum dot products at full rate; float32: 16 FMA and
-    16 adds), and the per-CU vector-memory path (the tile's K and V bytes at
-    the measured L2 -> CU ceiling). The measured pass exceeds the largest."""
+    16 adds, the splitting of its operands not counted), and the per-CU vector-memory path (the tile's K and V bytes at
+    the measured L2 -> CU ceiling). The measured pass exceeds the largest.
+    A float32 product is six products of bfloat16 planes."""
     tiles = w.B * w.H * w.nb * w.budget
     e = 2 if w.dtype == "bf16" else 4
-    peak = PEAK_BF16_TFLOPS if w.dtype == "bf16" else PEAK_F32_TFLOPS
-    mfma = tile_flops(w) / (peak * 1e12) * 1e6
+    products = 1 if w.dtype == "bf16" else 6
+    mfma = products * tile_flops(w) / (PEAK_BF16_TFLOPS * 1e12) * 1e6
     valu_cycles = 16 * 16 + 32 * 4                          # per tile, one SIMD (wave64 on 16 lanes)
     valu = tiles * valu_cycles / (CUS * SIMDS_PER_CU * CLOCK_HZ) * 1e6
     vmem = tiles * 2 * 32 * w.d * e / (CUS * L1_BYTES_PER_CLK_CU * CLOCK_HZ) * 1e6
