@@ -1046,7 +1046,7 @@ __global__ __launch_bounds__(WAVES * kWave) void bwd_dq_tr128_kernel(
 template <bool COARSE>
 __global__ __launch_bounds__(kWave) void bwd_dkdv_tr128_kernel(
     const void* __restrict__ kin, const void* __restrict__ vin, const void* __restrict__ qin,
-    const void* __restrict__ gin, const uint32_t* __restrict__ bits, const uint16_t* __restrict__ order,
+    const void* __restrict__ gin, const uint32_t* __restrict__ bits, const uint32_t* __restrict__ order,
     const uint32_t* __restrict__ bias, const float* __restrict__ dkp, const float* __restrict__ dvp,
     void* __restrict__ dk, void* __restrict__ dv, int nb, long long rows, float scale,
     float scale_log2) {
@@ -1066,7 +1066,7 @@ __global__ __launch_bounds__(kWave) void bwd_dkdv_tr128_kernel(
   long long gy = xcd_remap(blockIdx.x, gridDim.x);
   if (gy >= rows) return;
   const long long bh = gy / nb;
-  if (order != nullptr) gy = bh * nb + wave_uniform((int)order[gy]);
+  if (order != nullptr) gy = wave_uniform((int)order[gy]);
   if constexpr (COARSE) {
     prefetch_vec_lds<D>(dkp + gy * D, (lptr_t)addl[0]);
     prefetch_vec_lds<D>(dvp + gy * D, (lptr_t)addl[1]);
@@ -1461,12 +1461,14 @@ __global__ __launch_bounds__(2 * kWave) void bwd_dq_split_kernel(
 template <int D, bool COARSE>
 __global__ __launch_bounds__(2 * kWave) void bwd_dkdv_split_kernel(
     const void* __restrict__ kpl, const void* __restrict__ vpl, const void* __restrict__ qpl,
-    const void* __restrict__ gpl, const uint32_t* __restrict__ bits, const float* __restrict__ ld,
+    const void* __restrict__ gpl, const uint32_t* __restrict__ bits, const uint32_t* __restrict__ order, const float* __restrict__ ld,
     const float* __restrict__ dkp, const float* __restrict__ dvp, float* __restrict__ dk,
     float* __restrict__ dv, int nb, float scale, float scale_log2) {
   __shared__ SplitLds<D, 2, 2> S;
   extern __shared__ uint16_t list_all[];                    // [2][nb]
-  dkdv_split_body<D, COARSE, false>(xcd_remap(blockIdx.x, gridDim.x), S, list_all, ColTerms{}, kpl, vpl, qpl, gpl, bits,
+  long long gy = xcd_remap(blockIdx.x, gridDim.x);
+  if (order != nullptr) gy = wave_uniform((int)order[gy]);
+  dkdv_split_body<D, COARSE, false>(gy, S, list_all, ColTerms{}, kpl, vpl, qpl, gpl, bits,
                                     ld, dkp, dvp, dk, dv, nb, scale, scale_log2);
 }
 
@@ -1489,8 +1491,8 @@ __global__ __launch_bounds__(2 * kWave) void bwd_tiles_split_kernel(
                              scale_log2);
 }
 
-// Column blocks of each head in the order of falling list length (order
-// [bh, nb]): first the lengths, one workgroup per head and 32 columns, a lane per
+// Column blocks in the order of falling list length, within each of the launch's
+// equal ranges of them (order: rows entries): first the lengths, one workgroup per head and 32 columns, a lane per
 // block-row and one ballot per column.
 constexpr int kOrderWaves = 4;
 __global__ __launch_bounds__(kOrderWaves * kWave) void bwd_lengths_kernel(const uint32_t* __restrict__ bits,
@@ -1520,19 +1522,22 @@ __global__ __launch_bounds__(kOrderWaves * kWave) void bwd_lengths_kernel(const 
   }
 }
 
-// then a counting sort, one workgroup per head. Blocks of equal length come in
+// then a counting sort, one workgroup per range. Blocks of equal length come in
 // any order: it decides only where and when a block is worked on.
-__global__ __launch_bounds__(256) void bwd_order_kernel(const uint16_t* __restrict__ len, uint16_t* __restrict__ order,
-                                                        int nb) {
+constexpr int kOrderThreads = 1024;
+constexpr int kXcds = 8;                  // ranges of xcd_remap
+__global__ __launch_bounds__(kOrderThreads) void bwd_order_kernel(const uint16_t* __restrict__ len,
+                                                                  uint32_t* __restrict__ order, int nb, int rows) {
   __shared__ int off[2049];
-  const int tid = threadIdx.x;
-  const long long hb = (long long)blockIdx.x * nb;
-  for (int i = tid; i <= nb; i += 256) off[i] = 0;
+  const int tid = threadIdx.x, parts = gridDim.x, p = blockIdx.x;
+  const int q = rows / parts, r = rows % parts;
+  const int i0 = p * q + (p < r ? p : r), i1 = i0 + q + (p < r);
+  for (int i = tid; i <= nb; i += kOrderThreads) off[i] = 0;
   __syncthreads();
-  for (int i = tid; i < nb; i += 256) atomicAdd(&off[len[hb + i]], 1);
+  for (int i = i0 + tid; i < i1; i += kOrderThreads) atomicAdd(&off[len[i]], 1);
   __syncthreads();
   if (tid < kWave) {                                        // where each length starts, longest first
-    int run = 0;
+    int run = i0;
     for (int l0 = nb; l0 >= 0; l0 -= kWave) {
       const int l = l0 - tid;
       const int mine = l >= 0 ? off[l] : 0;
@@ -1546,7 +1551,20 @@ __global__ __launch_bounds__(256) void bwd_order_kernel(const uint16_t* __restri
     }
   }
   __syncthreads();
-  for (int i = tid; i < nb; i += 256) order[hb + atomicAdd(&off[len[hb + i]], 1)] = (uint16_t)i;
+  for (int i = i0 + tid; i < i1; i += kOrderThreads) order[atomicAdd(&off[len[i]], 1)] = (uint32_t)i;
+}
+
+// Writes the order of the column blocks within each of `parts` equal ranges of
+// them to the grid of W (nothing reads it any more; six bytes per column block,
+// so nb > 1) and returns it.
+static const uint32_t* launch_order(const BwdArgs& A, int parts, hipStream_t stream) {
+  const int nb = A.n / kBlock;
+  const long long rows = A.bh * nb;
+  uint32_t* order = reinterpret_cast<uint32_t*>(A.W);
+  uint16_t* len = reinterpret_cast<uint16_t*>(order + rows);
+  bwd_lengths_kernel<<<(unsigned)(A.bh * ((nb + 31) / 32)), kOrderWaves * kWave, 0, stream>>>(A.bits, len, nb);
+  bwd_order_kernel<<<parts, kOrderThreads, 0, stream>>>(len, order, nb, (int)rows);
+  return order;
 }
 
 // ---------------------------------------------------------------------------
@@ -1612,12 +1630,9 @@ static void launch_tiles_t(const BwdArgs& A, bool own, hipStream_t stream) {
     // 2422 us, the two launches included; 8 heads of 16384: 391 -> 382 us. Below
     // d = 128 nothing is gained (12 heads of 32768 x 64: 717 and 716 us). The grid
     // of W serves as scratch: nothing reads it any more.
-    const uint16_t* order = nullptr;
+    const uint32_t* order = nullptr;
     if ((size_t)4 * A.n * D > kL2PerXcd) {
-      uint16_t *len = reinterpret_cast<uint16_t*>(A.W), *ord = len + rows;
-      bwd_lengths_kernel<<<(unsigned)(A.bh * ((nb + 31) / 32)), kOrderWaves * kWave, 0, stream>>>(A.bits, len, nb);
-      bwd_order_kernel<<<(unsigned)A.bh, 256, 0, stream>>>(len, ord, nb);
-      order = ord;
+      order = launch_order(A, (int)A.bh, stream);
     }
     bwd_dkdv_tr128_kernel<COARSE><<<(unsigned)rows, kWave, nb * sizeof(int32_t), stream>>>(
         A.k, A.v, A.q, A.dout, A.bits, order, A.bias, A.dkp, A.dvp, A.dk, A.dv, nb, rows, scale, scale_log2);
@@ -1625,8 +1640,21 @@ static void launch_tiles_t(const BwdArgs& A, bool own, hipStream_t stream) {
     if (!one_launch) {
       bwd_dq_split_kernel<D, COARSE><<<(unsigned)rows, 2 * kWave, 2 * A.m * sizeof(uint16_t), stream>>>(
           A.q_pl, A.g_pl, A.k_pl, A.v_pl, A.idx, A.ld, A.dqp, static_cast<float*>(A.dq), nb, A.m, scale, scale_log2);
-      bwd_dkdv_split_kernel<D, COARSE><<<(unsigned)rows, 2 * kWave, 2 * nb * sizeof(uint16_t), stream>>>(
-          A.k_pl, A.v_pl, A.q_pl, A.g_pl, A.bits, A.ld, A.dkp, A.dvp, static_cast<float*>(A.dk),
+      // More column blocks than are resident at once (at d = 128 two workgroups
+      // per CU): the order of falling list length over each XCD's range, or the
+      // longest lists, which start at any time, end the pass alone. Training step,
+      // the two launches included: 32 heads x 1504 x 128, budget 8 (lists of up to
+      // 21, three rounds): 337 -> 319 us; 32 x 4096 x 32: 216 -> 207; 12 x 4096 x
+      // 64, budget 16: 278 -> 266; 4 x 16384 x 128, budget 32: 1333 -> 1237. With
+      // all of them resident it only costs its launches (40 x 1024 x 32: 74 -> 79),
+      // and bfloat16 (d <= 64), whose passes wait more on L2, loses by working on
+      // all heads of a range at once: 96 x 4096 x 64: 409 -> 429.
+      auto dkdv = bwd_dkdv_split_kernel<D, COARSE>;
+      const size_t lists = 2 * nb * sizeof(uint16_t);
+      const long long resident = resident_items(dkdv, 2 * kWave, lists, 1);
+      const uint32_t* order = nb > 1 && resident > 0 && rows > resident ? launch_order(A, kXcds, stream) : nullptr;
+      dkdv<<<(unsigned)rows, 2 * kWave, lists, stream>>>(
+          A.k_pl, A.v_pl, A.q_pl, A.g_pl, A.bits, order, A.ld, A.dkp, A.dvp, static_cast<float*>(A.dk),
           static_cast<float*>(A.dv), nb, scale, scale_log2);
     } else {
       const size_t lists = (size_t)2 * (nb > A.m ? nb : A.m) * sizeof(uint16_t);

@@ -349,3 +349,36 @@ def test_backward_in_one_launch(gpu, d, dtype, H, nb):
     _say("one launch", d, dtype, H, nb)
     q, k, v, g = _case(700 + nb + H, 1, H, 32 * nb, d, dtype, m)
     _check(gpu, "mra2", q, k, v, g, m, dtype, heads=[(0, 0), (0, H - 1)])
+
+
+@pytest.mark.parametrize("variant,d,H,nb", [("mra2", 32, 73, 33), ("mra2s", 64, 33, 33), ("mra2", 128, 23, 47),
+                                            ("global", 128, 29, 37), ("mra2", 128, 2, 513)])
+def test_backward_columns_by_list_length(gpu, variant, d, H, nb):
+    """float32 with more column blocks than are resident: they run by falling list
+    length within each eighth of them (totals that eight does not divide, heads
+    across two eighths). Which block runs when changes no sum, so each head's
+    gradients are those of a call with this head alone, whose column blocks run in
+    their own order (another kernel of the same sums: at most float32 roundings of
+    the final scale and add differ, 1e-6 of the largest entry)."""
+    from paper_2207_10284_amd import ops
+    m = 5 * nb if variant == "global" else 5
+    _say("columns by length", variant, d, H, nb)
+    q, k, v, g = (torch.randn(1, H, 32 * nb, d, device="cuda", generator=torch.Generator("cuda").manual_seed(i + nb))
+                  for i in range(4))
+    k[:, :, : 32 * 5] *= 4.0                                # some columns are in most rows' lists, some in none
+
+    out, lse = torch.empty_like(q), torch.empty(1, H, 32 * nb, device="cuda")
+    idx = torch.empty(1, H, nb, nb if variant == "global" else m, dtype=torch.int32, device="cuda")
+    forward = {"mra2": ops.attention_forward, "mra2s": ops.sparse_attention_forward,
+               "global": ops.attention_forward_global}[variant]
+    forward(q, k, v, m, out=out, idx_out=idx, lse_out=lse)
+
+    def grads(*t):
+        return ops.attention_backward(*(x.clone() for x in t), coarse=variant != "mra2s")
+
+    args = (q, k, v, out, g, lse, idx)
+    whole = grads(*args)
+    for h in (0, H // 2, H - 1):
+        alone = grads(*(t[:, h : h + 1] for t in args))
+        for a, b in zip(whole, alone):
+            assert float((a[:, h] - b[:, 0]).abs().max()) <= 1e-6 * float(b.abs().max())
