@@ -1065,8 +1065,8 @@ __global__ __launch_bounds__(kWave) void bwd_dkdv_tr128_kernel(
   const int lane = lane_id();
   long long gy = xcd_remap(blockIdx.x, gridDim.x);
   if (gy >= rows) return;
-  const long long bh = gy / nb;
   if (order != nullptr) gy = wave_uniform((int)order[gy]);
+  const long long bh = gy / nb;
   if constexpr (COARSE) {
     prefetch_vec_lds<D>(dkp + gy * D, (lptr_t)addl[0]);
     prefetch_vec_lds<D>(dvp + gy * D, (lptr_t)addl[1]);
