@@ -177,10 +177,6 @@ struct TileRow {
   // the row); with check == false the caller guarantees it cannot.
   template <class VA>
   __device__ __forceinline__ bool accumulate(const f32x16& s, bool check, VA va) {
-    if (first) {                              // wave-uniform: the row's first tile
-      mrun = tile_ref(s) + kRefMargin;
-      first = false;
-    }
     float t;
     if constexpr (DT == BF16) {
       uint32_t pk[8];
@@ -385,8 +381,11 @@ constexpr int kStreamWaves = 4;
 // exchange per tile: the scores are the sum of the two waves' products.
 //
 // SPLIT > 1: the workgroup's SPLIT waves share one block-row, wave p taking the
-// tiles p, p + SPLIT, ... of its list with a reference of its own; the sums are
-// brought to one reference and added through LDS at the end.
+// tiles p, p + SPLIT, ... of its list; the sums are added through LDS at the end.
+// All of them weigh relative to the reference of the row's first tile, which wave
+// 0 has (and restart together, relative to the max over the whole list), so the
+// weights, bfloat16 ones included, are those that one wave alone would form,
+// whatever SPLIT: a call's sums differ from an unsplit one's in their order only.
 template <int DT, int D, bool COARSE, int WAVES, int HALVES, int SPLIT>
 __global__ __launch_bounds__(WAVES * kWave) void tile_stream_kernel(
     const void* __restrict__ qv, const void* __restrict__ kv, const void* __restrict__ vv,
@@ -414,7 +413,11 @@ __global__ __launch_bounds__(WAVES * kWave) void tile_stream_kernel(
   constexpr bool kTermAhead = COARSE && D2 >= 128;
   __shared__ __attribute__((aligned(16))) float cvl[WAVES][kTermAhead ? add_lds_floats(D) : 1];
   __shared__ __attribute__((aligned(16))) float ex[HALVES == 2 ? 2 : 1][2][HALVES == 2 ? 16 * kWave : 1];
-  __shared__ float ml[SPLIT > 1 ? SPLIT : 1][2][SPLIT > 1 ? kWave : 1];
+  // waves that share a row: their references (first wave 0's; in a restart each
+  // wave's max), their weights' sums and whether some weight grew too large
+  __shared__ float refs[SPLIT > 1 ? SPLIT : 1][SPLIT > 1 ? kWave : 1];
+  __shared__ float sums[SPLIT > 1 ? SPLIT : 1][SPLIT > 1 ? kWave : 1];
+  __shared__ int grown[SPLIT > 1 ? SPLIT : 1];
   extern __shared__ int32_t sidx_all[];
 
   const int w = wave_uniform(threadIdx.x / kWave);
@@ -440,6 +443,7 @@ __global__ __launch_bounds__(WAVES * kWave) void tile_stream_kernel(
   TileRow<DT, D, COARSE, HALVES> row;
   row.init(reinterpret_cast<const elem*>(qv) + hoff, x, scale_log2);
   m = stage_selection(idx + g * m, m, nb, myidx);  // valid entries only, in order
+  const bool tiles = m > 0;                        // of the row; wave 0 has the first
   if constexpr (SPLIT > 1) {
     myidx += part;
     m = (m - part + SPLIT - 1) / SPLIT;
@@ -510,6 +514,19 @@ __global__ __launch_bounds__(WAVES * kWave) void tile_stream_kernel(
     }
     return s;
   };
+  // The reference of the row's first tile (mine: wave 0's); every wave of a shared
+  // row calls it once.
+  auto row_reference = [&](float mine) -> float {
+    if constexpr (SPLIT == 1) {
+      return mine;
+    } else {
+      if (w == 0) refs[0][lane] = mine;
+      asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");
+      float ref;                                     // in one block with its wait, as list_entry
+      asm volatile("ds_read_b32 %0, %1\n\ts_waitcnt lgkmcnt(0)" : "=v"(ref) : "v"(lds_addr(&refs[0][lane])) : "memory");
+      return ref;
+    }
+  };
   // The list holds valid blocks only. The entry after the next is read before
   // the wait for a tile, so the refill is issued as soon as the slot is read.
   auto pass = [&](bool check) -> bool {
@@ -531,15 +548,20 @@ __global__ __launch_bounds__(WAVES * kWave) void tile_stream_kernel(
       lds_done(vf);
       if (more) issue(yn);                           // refill the slot just read
       if (in_step) wait_loads<0>();                  // launched in rounds: see launch_stream_c
-      if (!row.accumulate(whole_scores(kf), check, [&](int c) { return vf[c]; })) {
+      const f32x16 s = whole_scores(kf);
+      if (row.first) {                               // wave-uniform: the first tile of the first pass
+        row.mrun = row_reference(row.tile_ref(s) + kRefMargin);
+        row.first = false;
+      }
+      if (!row.accumulate(s, check, [&](int c) { return vf[c]; })) {
         wait_loads<0>();                             // the slot is idle again
         return false;
       }
     }
     return true;
   };
-  if (!pass(true)) {
-    // some weight grew too large: again, relative to the row's exact max
+  // this wave's largest score, per query
+  auto largest = [&]() -> float {
     float mx = -INFINITY;
     for (int i = 0; i < m; ++i) {
       const int yy = list_entry(myidx + SPLIT * i);
@@ -550,39 +572,53 @@ __global__ __launch_bounds__(WAVES * kWave) void tile_stream_kernel(
       for (int c = 0; c < KC; ++c) kf[c] = krow[c];
       mx = __builtin_elementwise_maximum(mx, row.tile_ref(whole_scores(kf)));
     }
-    row.restart(mx);
-    pass(false);
-  }
-  if constexpr (SPLIT > 1) {
-    // every wave's (reference, sum) and the accumulators of waves 1 .. SPLIT - 1
-    // (a slot holds 32 x d floats)
-    const float l = halves_sum(row.lrun);
-    ml[w][0][lane] = row.mrun;
-    ml[w][1][lane] = l;
-    if (w != 0) {
-      f32x4* to = reinterpret_cast<f32x4*>(slot_all[w]) + lane;
-#pragma unroll
-      for (int t = 0; t < NT; ++t)
-#pragma unroll
-        for (int q = 0; q < 4; ++q)
-          to[(4 * t + q) * kWave] = f32x4{row.o[t][4 * q], row.o[t][4 * q + 1], row.o[t][4 * q + 2], row.o[t][4 * q + 3]};
+    return mx;
+  };
+  // false: some weight grew too large, and the row is computed again relative to
+  // its exact max
+  const bool fits = pass(true);
+  if constexpr (SPLIT == 1) {
+    if (!fits) {
+      row.restart(largest());
+      pass(false);
     }
-    __syncthreads();
+  } else {
+    if (m == 0 && tiles) row_reference(0.0f);        // a wave without a tile meets the others
+    // the sums, and the accumulators of waves 1 .. SPLIT - 1 in their slots (32 x d
+    // floats each), behind a barrier
+    auto share = [&]() {
+      const float l = halves_sum(row.lrun);
+      sums[w][lane] = l;
+      if (w != 0) {
+        f32x4* to = reinterpret_cast<f32x4*>(slot_all[w]) + lane;
+#pragma unroll
+        for (int t = 0; t < NT; ++t)
+#pragma unroll
+          for (int q = 0; q < 4; ++q)
+            to[(4 * t + q) * kWave] = f32x4{row.o[t][4 * q], row.o[t][4 * q + 1], row.o[t][4 * q + 2], row.o[t][4 * q + 3]};
+      }
+      __syncthreads();
+      return l;
+    };
+    if (lane == 0) grown[w] = !fits;
+    float lt = share();
+    int any = 0;
+#pragma unroll
+    for (int p = 0; p < SPLIT; ++p) any |= grown[p];
+    if (wave_uniform(any)) {                         // all waves of the row, or none
+      refs[w][lane] = largest();
+      __syncthreads();
+      float mx = refs[0][lane];
+#pragma unroll
+      for (int p = 1; p < SPLIT; ++p) mx = __builtin_elementwise_maximum(mx, refs[p][lane]);
+      row.restart(mx);
+      pass(false);
+      lt = share();
+    }
     if (w != 0) return;
-    float M = row.mrun;
-#pragma unroll
-    for (int p = 1; p < SPLIT; ++p) M = fmaxf(M, ml[p][0][lane]);
-    auto factor = [&](float ref) { return ref == -INFINITY ? 0.0f : exp2f(ref - M); };   // no tile: no weight
-    const float a0 = factor(row.mrun);
-    float lt = l * a0;
-#pragma unroll
-    for (int t = 0; t < NT; ++t)
-#pragma unroll
-      for (int r = 0; r < 16; ++r) row.o[t][r] *= a0;
 #pragma unroll
     for (int p = 1; p < SPLIT; ++p) {
-      const float a = factor(ml[p][0][lane]);
-      lt = fmaf(ml[p][1][lane], a, lt);
+      lt += sums[p][lane];
       const f32x4* from = reinterpret_cast<const f32x4*>(slot_all[p]) + lane;
 #pragma unroll
       for (int t = 0; t < NT; ++t)
@@ -590,10 +626,9 @@ __global__ __launch_bounds__(WAVES * kWave) void tile_stream_kernel(
         for (int q = 0; q < 4; ++q) {
           const f32x4 v = from[(4 * t + q) * kWave];
 #pragma unroll
-          for (int e = 0; e < 4; ++e) row.o[t][4 * q + e] = fmaf(v[e], a, row.o[t][4 * q + e]);
+          for (int e = 0; e < 4; ++e) row.o[t][4 * q + e] += v[e];
         }
     }
-    row.mrun = M;
     row.lrun = h == 0 ? lt : 0.0f;                   // finish() adds the halves
   }
   if constexpr (kTermAhead) {

@@ -266,8 +266,7 @@ def test_reference_restart(gpu, dtype, d):
     selected block has logits of 120: relative to the first block's max the
     later weights would overflow, so the tile pass computes the row again
     relative to its exact max. The result matches the oracle, is finite, and
-    the forward agrees bitwise with the step-wise calls (for float32 d = 128
-    that compares the packed-operand path with the row-major one)."""
+    the forward agrees bitwise with the step-wise calls."""
     _say("restart", dtype, d)
     n, m = 256, 4
     r = np.random.Generator(np.random.PCG64(4242 + d))
@@ -368,3 +367,70 @@ def test_shared_rows_without_valid_entries(gpu, d):
         E = np.exp(P)
         ref = (E @ vd[cols] + np.exp(0.5) * 16.0) / (E.sum(1, keepdims=True) + np.exp(0.5) * 32.0)
         assert row_rel_err(out[32 * x:32 * x + 32], ref) <= TOL["bf16"], x
+
+
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
+@pytest.mark.parametrize("d", [32, 64, 128])
+def test_shared_rows_weigh_as_one_wave(gpu, dtype, d):
+    """A head of 16 block-rows alone (four waves per row), among 40 (two) and
+    among 65 (one): the weights, rounded to bfloat16 there, are the same, so the
+    row sums differ by the order of their additions only. Each of the two sums
+    of 32 m positive terms is off by at most 32 m u, its logarithm by as much,
+    and the log normaliser is rounded twice more; an output entry is a sum of
+    as many terms, rounded to its type."""
+    _say("shared rows, weights", dtype, d)
+    H, n, m = 65, 512, 7
+    q, k, v = inputs.random_qkv(5200 + d, 1, H, n, d, dtype, scale=1.6)
+    r = np.random.Generator(np.random.PCG64(d))
+    idx = np.sort(np.argsort(r.random((1, H, n // 32, n // 32)), axis=-1)[..., :m], axis=-1).astype(np.int32)
+    args = [dev(q, dtype), dev(k, dtype), dev(v, dtype), torch.from_numpy(idx).cuda()]
+
+    def tiles(heads):
+        lse = torch.empty(1, heads, n, device="cuda")
+        out = gpu.block_sddmm_spmm(*(t[:, :heads].contiguous() for t in args), lse_out=lse)
+        return out.float(), lse
+
+    whole, lse = tiles(H)
+    order = 2 * 32 * m * U
+    ulp = U if dtype == "f32" else 2.0 ** -8
+    for heads in (1, 40):
+        o, l = tiles(heads)
+        far = (l - lse[:, :heads]).abs().max()
+        _say("  heads", heads, "lse", float(far))
+        assert far <= order + 4 * U * lse.abs().max()
+        assert (o - whole[:, :heads]).abs().sub(2 * ulp * whole[:, :heads].abs()).max() <= 2 * order * np.abs(v).max()
+
+
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
+@pytest.mark.parametrize("d", [32, 64, 128])
+@pytest.mark.parametrize("H,m,hot", [(130, 6, 1), (130, 6, 5), (40, 6, 1), (40, 6, 2), (40, 6, 5), (1, 2, 1), (1, 6, 1),
+                                     (1, 6, 4), (1, 6, 5), (1, 3, 2)])
+def test_reference_restart_shared_rows(gpu, dtype, d, H, m, hot):
+    """The restart with one wave per block-row (1040 rows), two (320 rows, or two
+    tiles) and four (8 rows): the tile at place `hot` of each list has logits
+    near 120 above the first one's, so its weights overflow the first tile's
+    reference in whichever wave has it (its first tile or its second), and the
+    whole row, the waves that saw nothing included, is formed again. An error of
+    a logit of magnitude 120 moves a weight by (d + 2) u 120."""
+    _say("restart, shared rows", dtype, d, H, m, hot)
+    n = 256
+    r = np.random.Generator(np.random.PCG64(100 * d + 10 * m + hot))
+    q, k, v = (0.3 * r.standard_normal((1, H, n, d)) for _ in range(3))
+    logit = np.full(n // 32, -2.0)
+    logit[hot + 1] = 120.0
+    q[..., 0] = 16.0
+    k[..., 0] = np.repeat(logit, 32) * math.sqrt(d) / 16.0
+    q, k, v = (inputs.round_to_bf16(a) if dtype == "bf16" else a.astype(np.float32) for a in (q, k, v))
+    idx = np.broadcast_to(np.arange(1, m + 1, dtype=np.int32), (1, H, n // 32, m)).copy()
+    lse = torch.empty(1, H, n, device="cuda")
+    out = gpu.block_sddmm_spmm(dev(q, dtype), dev(k, dtype), dev(v, dtype), torch.from_numpy(idx).cuda(), lse_out=lse)
+    assert torch.isfinite(out.float()).all() and torch.isfinite(lse).all()
+    tol = max(TOL[dtype], 2 * (d + 2) * U * 130)
+    cols = slice(32, 32 * (m + 1))
+    for h in (0, H - 1):
+        qd, kd, vd = (a[0, h].astype(np.float64) for a in (q, k, v))
+        P = qd @ kd[cols].T / math.sqrt(d)
+        L = np.log(np.exp(P - 120).sum(1)) + 120
+        ref = np.exp(P - L[:, None]) @ vd[cols]
+        assert np.abs(host(out)[0, h] - ref).max() <= tol * np.abs(vd[cols]).max()
+        assert np.abs(host(lse)[0, h] - L).max() <= tol
