@@ -288,7 +288,7 @@ def test_backward_long_sequence_full_head(gpu):
 
 
 @pytest.mark.parametrize("n,m", [(8224, 3), (9216, 288)])
-def test_backward_columns_by_list_length(gpu, n, m):
+def test_backward_columns_by_list_length_bf16_d128(gpu, n, m):
     """Heads at bfloat16 d = 128 whose Q and dZ exceed an XCD's L2 (n > 8192)
     take the column blocks by falling list length: every block-row is worked on
     once, whatever the lists (257 blocks with few entries, some columns in no
