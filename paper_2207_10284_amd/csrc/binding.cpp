@@ -14,6 +14,7 @@
 #include <ATen/ops/empty.h>
 #include <ATen/ops/empty_like.h>
 #include <c10/hip/HIPStream.h>
+#include <torch/csrc/Exceptions.h>
 #include <torch/csrc/autograd/custom_function.h>
 #include <torch/csrc/utils/pybind.h>
 
@@ -36,50 +37,51 @@ struct Api {
   decltype(&mra_backward_workspace_bytes) backward_ws;
   decltype(&mra_attention_backward) backward;
   decltype(&mra_attention_backward_pooled) backward_pooled;
-  decltype(&mra_status_str) status_str;
 };
 Api api{};
 
 enum Variant { kMra2 = 0, kSparse = 1, kGlobal = 2 };
 
-// A call that the library refused; ops.py turns it into its MraError.
-struct StatusError : std::runtime_error {
-  StatusError(const char* f, int st)
-      : std::runtime_error(std::string(f) + ": " + api.status_str((mra_status_t)st)), fn(f), status(st) {}
-  const char* fn;
-  int status;
-};
+// ops.py's MraError factory; never destroyed (the interpreter ends first)
+py::object& status_error = *new py::object();
 
+// What fails here is raised as the Python function of ops.py raises it, also from
+// the backward, whose errors reach the caller through the autograd engine: a
+// refusal by the library as MraError, one by the checks as c10's ValueError and
+// TypeError, which torch turns into Python's (as it does its own, an exhausted
+// allocator's, and a saved-tensor hook's exception).
 void ok(const char* fn, mra_status_t st) {
-  if (st != MRA_OK) throw StatusError(fn, (int)st);
-}
-
-void require(bool cond, const char* what) {
-  if (!cond) throw py::value_error(what);
+  if (st == MRA_OK) return;
+  py::gil_scoped_acquire gil;
+  const py::object err = status_error(fn, (int)st);
+  PyErr_SetObject(reinterpret_cast<PyObject*>(Py_TYPE(err.ptr())), err.ptr());
+  python_error e;
+  e.persist();
+  throw e;
 }
 
 mra_dtype_t dtype_code(const at::Tensor& t) {
   if (t.scalar_type() == at::kFloat) return MRA_F32;
   if (t.scalar_type() == at::kBFloat16) return MRA_BF16;
-  throw py::type_error(std::string("unsupported dtype ") + c10::toString(t.scalar_type()) +
-                       "; expected float32 or bfloat16");
+  TORCH_CHECK_TYPE(false, "unsupported dtype ", c10::toString(t.scalar_type()), "; expected float32 or bfloat16");
 }
 
 void check_like(const at::Tensor& t, const at::Tensor& ref) {
-  require(t.is_cuda(), "tensors must be on a ROCm device");
-  require(t.dim() == 4 && t.sizes() == ref.sizes() && t.scalar_type() == ref.scalar_type() && t.device() == ref.device(),
-          "q, k, v must share shape [B, H, n, d], dtype and device");
-  require(t.is_contiguous(), "q, k, v must be contiguous");
+  TORCH_CHECK_VALUE(t.is_cuda(), "tensors must be on a ROCm device");
+  TORCH_CHECK_VALUE(t.dim() == 4 && t.sizes() == ref.sizes() && t.scalar_type() == ref.scalar_type() &&
+                        t.device() == ref.device(),
+                    "q, k, v must share shape [B, H, n, d], dtype and device");
+  TORCH_CHECK_VALUE(t.is_contiguous(), "q, k, v must be contiguous");
 }
 
 void check_f32(const at::Tensor& t, at::IntArrayRef shape, const char* name) {
-  if (t.scalar_type() != at::kFloat || t.sizes() != shape || !t.is_contiguous() || !t.is_cuda())
-    throw py::value_error(std::string(name) + " must be a contiguous float32 device tensor of the call's shape");
+  TORCH_CHECK_VALUE(t.scalar_type() == at::kFloat && t.sizes() == shape && t.is_contiguous() && t.is_cuda(), name,
+                    " must be a contiguous float32 device tensor of the call's shape");
 }
 
 void check_idx(const at::Tensor& t, at::IntArrayRef shape, const at::Device& dev) {
-  if (t.scalar_type() != at::kInt || t.sizes() != shape || !t.is_contiguous() || t.device() != dev)
-    throw py::value_error("idx must be a contiguous int32 tensor of the call's shape");
+  TORCH_CHECK_VALUE(t.scalar_type() == at::kInt && t.sizes() == shape && t.is_contiguous() && t.device() == dev,
+                    "idx must be a contiguous int32 tensor of the call's shape");
 }
 
 void* ptr(const std::optional<at::Tensor>& t) { return t ? t->data_ptr() : nullptr; }
@@ -161,7 +163,7 @@ std::vector<at::Tensor> backward(const at::Tensor& q, const at::Tensor& k, const
   } else {
     for (const at::Tensor& p : pooled) {
       check_f32(p, {s.B, s.H, nb, s.d}, "pooled rows");
-      require(p.device() == q.device(), "pooled rows must be on the inputs' device");
+      TORCH_CHECK_VALUE(p.device() == q.device(), "pooled rows must be on the inputs' device");
     }
     ok("mra_attention_backward_pooled",
        api.backward_pooled(q.data_ptr(), k.data_ptr(), v.data_ptr(), out.data_ptr(), dout.data_ptr(), lp, ip,
@@ -235,26 +237,15 @@ void bind(const py::dict& a) {
   bind_one(a, "mra_backward_workspace_bytes", api.backward_ws);
   bind_one(a, "mra_attention_backward", api.backward);
   bind_one(a, "mra_attention_backward_pooled", api.backward_pooled);
-  bind_one(a, "mra_status_str", api.status_str);
 }
 
 }  // namespace
 
 PYBIND11_MODULE(_binding, m) {
-  // ops.py's MraError factory; never destroyed (the interpreter ends first)
-  static py::object& raise_status = *new py::object();
   m.def("bind", [](const py::dict& addresses, py::object raiser) {
     bind(addresses);
-    raise_status = std::move(raiser);
+    status_error = std::move(raiser);
   });
-  py::register_exception_translator([](std::exception_ptr p) {
-    try {
-      if (p) std::rethrow_exception(p);
-    } catch (const StatusError& e) {
-      py::object err = raise_status(e.fn, e.status);
-      PyErr_SetObject(reinterpret_cast<PyObject*>(Py_TYPE(err.ptr())), err.ptr());
-    }
-  });
-  m.def("forward", &forward, py::call_guard<py::gil_scoped_release>());
-  m.def("mra_attention", &mra_attention, py::call_guard<py::gil_scoped_release>());
+  m.def("forward", torch::wrap_pybind_function_no_gil(forward));
+  m.def("mra_attention", torch::wrap_pybind_function_no_gil(mra_attention));
 }

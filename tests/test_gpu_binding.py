@@ -93,3 +93,44 @@ def test_refusals(gpu):
         torch.func.vmap(lambda a: gpu.mra_attention(a, k, v, 2))(q.expand(2, *q.shape))
     with torch.autograd.forward_ad.dual_level(), pytest.raises(RuntimeError):
         gpu.mra_attention(torch.autograd.forward_ad.make_dual(q, torch.ones_like(q)), k, v, 2)
+
+
+def test_errors_of_the_backward(gpu):
+    """What the backward refuses (here tensors that a saved-tensor hook swapped)
+    is the exception of the Python function: ValueError by the checks, MraError
+    with its status by the library; a hook's own exception and an exhausted
+    allocator come through as they are."""
+    q, k, v, g = _inputs("f32")
+
+    def backward(f, unpack):
+        a = [t.clone().requires_grad_(True) for t in (q, k, v)]
+        with torch.autograd.graph.saved_tensors_hooks(lambda t: t, unpack):
+            z = f(*a, 2, "mra2", False)
+        z.backward(g)
+
+    def boom(t):
+        raise LookupError("unpack")
+
+    def wider(t):                              # a selection of more columns than there are
+        return torch.zeros(2, 3, 5, 6, dtype=torch.int32, device="cuda") if t.dtype == torch.int32 else t
+
+    for f in (gpu.MraAttention.apply, gpu.mra_attention):
+        with pytest.raises(ValueError, match="ROCm device"):
+            backward(f, lambda t: t.cpu())
+        with pytest.raises(LookupError, match="unpack"):
+            backward(f, boom)
+        with pytest.raises(gpu.MraError) as e:
+            backward(f, wider)
+        assert e.value.status == 1
+    with torch.autograd.graph.saved_tensors_hooks(boom, lambda t: t), pytest.raises(LookupError, match="unpack"):
+        gpu.mra_attention(q.clone().requires_grad_(True), k, v, 2)
+    big = [torch.zeros(8, 16, 4096, 64, device="cuda") for _ in range(3)]
+    torch.cuda.empty_cache()
+    total = torch.cuda.get_device_properties(0).total_memory
+    try:
+        torch.cuda.set_per_process_memory_fraction((torch.cuda.memory_reserved() + (8 << 20)) / total)
+        for call in (gpu.attention_forward, gpu.mra_attention):
+            with pytest.raises(torch.OutOfMemoryError):
+                call(*big, 8)
+    finally:
+        torch.cuda.set_per_process_memory_fraction(1.0)
