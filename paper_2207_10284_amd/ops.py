@@ -4,8 +4,8 @@ Argument marshalling only: every function checks tensor placement, dtype and
 shape, allocates outputs with torch (device memory is plumbing here), and
 calls the library on the current torch stream. All arithmetic runs in the HIP
 kernels. The forward calls and ``mra_attention`` do this in native code
-(csrc/binding.cpp). There is no fallback: if the library or the binding is not
-built, ``load`` raises.
+(csrc/binding.cpp, loaded by the first of them). There is no fallback: if the
+library is not built, ``load`` raises, and these calls do if the binding is not.
 
 Shapes: q, k, v are [B, H, n, d] tensors on a ROCm device, float32 or
 bfloat16, contiguous; n is a multiple of 32 and d is 32, 64 or 128.
@@ -55,7 +55,7 @@ SIGNATURES = {
 }
 
 _lib = None
-_native = None          # csrc/binding.cpp, bound to _lib
+_native = None          # csrc/binding.cpp, bound to _lib by the first call that needs it
 
 
 class MraError(RuntimeError):
@@ -78,22 +78,26 @@ def load(path: str = LIB_PATH):
         for name, (res, args) in SIGNATURES.items():
             fn = getattr(lib, name)
             fn.restype, fn.argtypes = res, args
-        bind(lib)
         _lib = lib
     return _lib
 
 
-def bind(lib):
-    """Hand the library's entry points to the native binding."""
+def bind():
+    """The native binding, holding the library's entry points. Raises if it
+    cannot be imported (it is built for one Python and one torch); the other
+    calls need only the library."""
     global _native
-    try:
-        from paper_2207_10284_amd import _binding
-    except ImportError as e:
-        raise RuntimeError(f"the torch binding is not built ({e}); run `python -m paper_2207_10284_amd.build` "
-                           "first") from e
-    _binding.bind({name: ctypes.cast(getattr(lib, name), ctypes.c_void_p).value for name in SIGNATURES},
-                  lambda fn, status: MraError(fn, status, lib))
-    _native = _binding
+    if _native is None:
+        lib = load()
+        try:
+            from paper_2207_10284_amd import _binding
+        except ImportError as e:
+            raise RuntimeError(f"the torch binding is not built ({e}); run `python -m paper_2207_10284_amd.build` "
+                               "first") from e
+        _binding.bind({name: ctypes.cast(getattr(lib, name), ctypes.c_void_p).value for name in SIGNATURES},
+                      lambda fn, status: MraError(fn, status, lib))
+        _native = _binding
+    return _native
 
 
 def _call(name: str, *args):
@@ -233,8 +237,7 @@ def attention_forward(q, k, v, budget: int, out=None, idx_out=None, workspace=No
     """The whole MRA-2 forward pass. Returns the output Z ([B, H, n, d], input
     dtype); the selection is written to ``idx_out`` and each query's log
     normaliser (float32 [B, H, n]) to ``lse_out`` when given."""
-    load()
-    return _native.forward(0, q, k, v, budget, False, out, idx_out, workspace, lse_out)
+    return bind().forward(0, q, k, v, budget, False, out, idx_out, workspace, lse_out)
 
 
 def attention_forward_noalloc(q, k, v, budget: int, out=None, idx_out=None, lse_out=None):
@@ -259,8 +262,7 @@ def sparse_attention_forward(q, k, v, budget: int, out=None, idx_out=None, works
     """The sparse-only variant MRA-2-s (Sec. 5): softmax over the selected
     blocks only, no low-resolution term; budget >= 1. Same arguments and
     result as ``attention_forward``."""
-    load()
-    return _native.forward(1, q, k, v, budget, False, out, idx_out, workspace, lse_out)
+    return bind().forward(1, q, k, v, budget, False, out, idx_out, workspace, lse_out)
 
 
 def forward_global_workspace_bytes(B: int, H: int, n: int, d: int, dtype=torch.bfloat16) -> int:
@@ -274,8 +276,7 @@ def attention_forward_global(q, k, v, budget: int, prior_diagonal: bool = False,
     plus the diagonal with ``prior_diagonal``). Returns Z; the selection
     (int32 [B, H, nb, nb], rows padded with -1) goes to ``idx_out`` and the
     log normalisers to ``lse_out`` when given."""
-    load()
-    return _native.forward(2, q, k, v, budget, bool(prior_diagonal), out, idx_out, workspace, lse_out)
+    return bind().forward(2, q, k, v, budget, bool(prior_diagonal), out, idx_out, workspace, lse_out)
 
 
 def forward_multilevel_workspace_bytes(B: int, H: int, n: int, d: int, coarse_block: int, budget1: int,
@@ -471,8 +472,7 @@ def mra_attention(q, k, v, budget: int, variant: str = "mra2", prior_diagonal: b
     if (type(q) in _PLAIN and type(k) in _PLAIN and type(v) in _PLAIN and variant in _VARIANTS
             and not torch._C._are_functorch_transforms_active() and torch._C._get_tracing_state() is None
             and not torch.compiler.is_compiling()):
-        load()
-        return _native.mra_attention(q, k, v, budget, _VARIANTS[variant], bool(prior_diagonal))
+        return bind().mra_attention(q, k, v, budget, _VARIANTS[variant], bool(prior_diagonal))
     return MraAttention.apply(q, k, v, budget, variant, prior_diagonal)
 
 
