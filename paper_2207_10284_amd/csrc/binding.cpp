@@ -74,14 +74,21 @@ void check_like(const at::Tensor& t, const at::Tensor& ref) {
   TORCH_CHECK_VALUE(t.is_contiguous(), "q, k, v must be contiguous");
 }
 
+// A shape as Python writes it.
+std::string tuple_of(at::IntArrayRef shape) {
+  std::string s = "(";
+  for (size_t i = 0; i < shape.size(); ++i) s += (i ? ", " : "") + std::to_string(shape[i]);
+  return s + (shape.size() == 1 ? ",)" : ")");
+}
+
 void check_f32(const at::Tensor& t, at::IntArrayRef shape, const char* name) {
   TORCH_CHECK_VALUE(t.scalar_type() == at::kFloat && t.sizes() == shape && t.is_contiguous() && t.is_cuda(), name,
-                    " must be a contiguous float32 device tensor of the call's shape");
+                    " must be a contiguous float32 device tensor of shape ", tuple_of(shape));
 }
 
 void check_idx(const at::Tensor& t, at::IntArrayRef shape, const at::Device& dev) {
   TORCH_CHECK_VALUE(t.scalar_type() == at::kInt && t.sizes() == shape && t.is_contiguous() && t.device() == dev,
-                    "idx must be a contiguous int32 tensor of the call's shape");
+                    "idx must be a contiguous int32 tensor of shape ", tuple_of(shape));
 }
 
 void* ptr(const std::optional<at::Tensor>& t) { return t ? t->data_ptr() : nullptr; }
@@ -161,9 +168,10 @@ std::vector<at::Tensor> backward(const at::Tensor& q, const at::Tensor& k, const
                     dk.data_ptr(), dv.data_ptr(), ws.data_ptr(), ws.nbytes(), s.B, s.H, s.n, s.d, kBlock, width, coarse,
                     dt, stream_of(q)));
   } else {
-    for (const at::Tensor& p : pooled) {
-      check_f32(p, {s.B, s.H, nb, s.d}, "pooled rows");
-      TORCH_CHECK_VALUE(p.device() == q.device(), "pooled rows must be on the inputs' device");
+    const char* names[3] = {"qp", "kp", "vp"};
+    for (int i = 0; i < 3; ++i) {
+      check_f32(pooled[i], {s.B, s.H, nb, s.d}, names[i]);
+      TORCH_CHECK_VALUE(pooled[i].device() == q.device(), names[i], " must be on ", q.device());
     }
     ok("mra_attention_backward_pooled",
        api.backward_pooled(q.data_ptr(), k.data_ptr(), v.data_ptr(), out.data_ptr(), dout.data_ptr(), lp, ip,

@@ -134,3 +134,13 @@ def test_errors_of_the_backward(gpu):
                 call(*big, 8)
     finally:
         torch.cuda.set_per_process_memory_fraction(1.0)
+
+
+def test_refusals_name_what_they_expect(gpu):
+    q, k, v, _ = _inputs("f32")
+    short = torch.empty(2, device="cuda")
+    for call, width in ((gpu.attention_forward, 2), (gpu.sparse_attention_forward, 2), (gpu.attention_forward_global, 5)):
+        with pytest.raises(ValueError, match=rf"idx must be .* of shape \(2, 3, 5, {width}\)"):
+            call(q, k, v, 2, idx_out=short.int())
+        with pytest.raises(ValueError, match=r"lse_out must be .* of shape \(2, 3, 160\)"):
+            call(q, k, v, 2, lse_out=short)
