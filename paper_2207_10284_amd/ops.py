@@ -233,11 +233,22 @@ def forward_workspace_bytes(B: int, H: int, n: int, d: int, budget: int, dtype=t
     return int(load().mra_forward_workspace_bytes(B, H, n, d, BLOCK, budget, code))
 
 
+_PLAIN = (torch.Tensor, torch.nn.Parameter)
+
+
+def _result(q, out):
+    """``out``, allocated here for a tensor subclass (its own ``empty_like``
+    decides the result's type), else where it is needed."""
+    if out is None and type(q) not in _PLAIN and isinstance(q, torch.Tensor):
+        return torch.empty_like(q)
+    return out
+
+
 def attention_forward(q, k, v, budget: int, out=None, idx_out=None, workspace=None, lse_out=None):
     """The whole MRA-2 forward pass. Returns the output Z ([B, H, n, d], input
     dtype); the selection is written to ``idx_out`` and each query's log
     normaliser (float32 [B, H, n]) to ``lse_out`` when given."""
-    return bind().forward(0, q, k, v, budget, False, out, idx_out, workspace, lse_out)
+    return bind().forward(0, q, k, v, budget, False, _result(q, out), idx_out, workspace, lse_out)
 
 
 def attention_forward_noalloc(q, k, v, budget: int, out=None, idx_out=None, lse_out=None):
@@ -262,7 +273,7 @@ def sparse_attention_forward(q, k, v, budget: int, out=None, idx_out=None, works
     """The sparse-only variant MRA-2-s (Sec. 5): softmax over the selected
     blocks only, no low-resolution term; budget >= 1. Same arguments and
     result as ``attention_forward``."""
-    return bind().forward(1, q, k, v, budget, False, out, idx_out, workspace, lse_out)
+    return bind().forward(1, q, k, v, budget, False, _result(q, out), idx_out, workspace, lse_out)
 
 
 def forward_global_workspace_bytes(B: int, H: int, n: int, d: int, dtype=torch.bfloat16) -> int:
@@ -276,7 +287,7 @@ def attention_forward_global(q, k, v, budget: int, prior_diagonal: bool = False,
     plus the diagonal with ``prior_diagonal``). Returns Z; the selection
     (int32 [B, H, nb, nb], rows padded with -1) goes to ``idx_out`` and the
     log normalisers to ``lse_out`` when given."""
-    return bind().forward(2, q, k, v, budget, bool(prior_diagonal), out, idx_out, workspace, lse_out)
+    return bind().forward(2, q, k, v, budget, bool(prior_diagonal), _result(q, out), idx_out, workspace, lse_out)
 
 
 def forward_multilevel_workspace_bytes(B: int, H: int, n: int, d: int, coarse_block: int, budget1: int,
@@ -462,7 +473,7 @@ class MraAttention(torch.autograd.Function):
         return dq, dk, dv, None, None, None
 
 
-_VARIANTS = {"mra2": 0, "mra2s": 1, "global": 2}
+_VARIANTS = ("mra2", "mra2s", "global")       # the native variants, in their order
 
 
 def mra_attention(q, k, v, budget: int, variant: str = "mra2", prior_diagonal: bool = False):
@@ -472,8 +483,5 @@ def mra_attention(q, k, v, budget: int, variant: str = "mra2", prior_diagonal: b
     if (type(q) in _PLAIN and type(k) in _PLAIN and type(v) in _PLAIN and variant in _VARIANTS
             and not torch._C._are_functorch_transforms_active() and torch._C._get_tracing_state() is None
             and not torch.compiler.is_compiling()):
-        return bind().mra_attention(q, k, v, budget, _VARIANTS[variant], bool(prior_diagonal))
+        return bind().mra_attention(q, k, v, budget, _VARIANTS.index(variant), bool(prior_diagonal))
     return MraAttention.apply(q, k, v, budget, variant, prior_diagonal)
-
-
-_PLAIN = (torch.Tensor, torch.nn.Parameter)

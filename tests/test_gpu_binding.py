@@ -144,3 +144,21 @@ def test_refusals_name_what_they_expect(gpu):
             call(q, k, v, 2, idx_out=short.int())
         with pytest.raises(ValueError, match=r"lse_out must be .* of shape \(2, 3, 160\)"):
             call(q, k, v, 2, lse_out=short)
+
+
+class _Tagged(torch.Tensor):
+    pass
+
+
+def test_tensor_subclass_gets_its_own_type(gpu):
+    """The result of a call on a tensor subclass is of that type (its empty_like
+    makes it), with the values of the plain call."""
+    q, k, v, g = _inputs("f32")
+    t = [x.as_subclass(_Tagged) for x in (q, k, v)]
+    for call in (gpu.attention_forward, gpu.sparse_attention_forward, gpu.attention_forward_global, gpu.mra_attention):
+        z = call(*t, 2)
+        assert type(z) is _Tagged
+        assert torch.equal(z.as_subclass(torch.Tensor), call(q, k, v, 2))
+    assert type(gpu.attention_forward(*(torch.nn.Parameter(x) for x in (q, k, v)), 2)) is torch.Tensor
+    with pytest.raises(ValueError):
+        gpu.mra_attention(q, k, v, 2, ["mra2"])
