@@ -1526,6 +1526,8 @@ __global__ __launch_bounds__(kOrderWaves * kWave) void bwd_lengths_kernel(const 
 // any order: it decides only where and when a block is worked on.
 constexpr int kOrderThreads = 1024;
 constexpr int kXcds = 8;                  // ranges of xcd_remap
+// bfloat16, d = 128: least tiles per row and rounds of resident column blocks to order them
+constexpr int kOrderTiles = 16, kOrderRounds = 4;
 __global__ __launch_bounds__(kOrderThreads) void bwd_order_kernel(const uint16_t* __restrict__ len,
                                                                   uint32_t* __restrict__ order, int nb, int rows) {
   __shared__ int off[2049];
@@ -1627,14 +1629,22 @@ static void launch_tiles_t(const BwdArgs& A, bool own, hipStream_t stream) {
     // the blocks an XCD works on walk the head at the same pace (the pass is bound
     // by bytes from beyond the L2), and its longest lists do not come last. 16
     // heads of 32768 x 128, budget 32 (lists of 2 to 95): training step 2550 ->
-    // 2422 us, the two launches included; 8 heads of 16384: 391 -> 382 us. Below
-    // d = 128 nothing is gained (12 heads of 32768 x 64: 717 and 716 us). The grid
-    // of W serves as scratch: nothing reads it any more.
+    // 2422 us, the two launches included. It takes several rounds of resident
+    // blocks and lists that are long against the two launches (backward without ->
+    // with, us, budget 16 / 32): 4 x 32768: 374 -> 365 / 526 -> 484, 8 x 16384:
+    // 284 -> 270 / 424 -> 392, 16 x 8224: 295 -> 293 / 440 -> 441; budget 8 loses (4
+    // x 32768: 285 -> 297), and so do three rounds (12 x 8224, budget 16: 215 ->
+    // 231) and fewer: all resident, the launches are all that is added (1 x 8224,
+    // budget 16: 94 -> 102). Below d = 128 nothing is gained (12 heads of 32768 x
+    // 64: 717 and 716 us). The grid of W serves as scratch: nothing reads it any more.
+    auto dkdv = bwd_dkdv_tr128_kernel<COARSE>;
+    const size_t lists = nb * sizeof(int32_t);
     const uint32_t* order = nullptr;
-    if ((size_t)4 * A.n * D > kL2PerXcd) {
-      order = launch_order(A, (int)A.bh, stream);
+    if (A.m >= kOrderTiles && (size_t)4 * A.n * D > kL2PerXcd) {
+      const long long resident = resident_items(dkdv, kWave, lists, 1);
+      if (resident > 0 && rows >= kOrderRounds * resident) order = launch_order(A, (int)A.bh, stream);
     }
-    bwd_dkdv_tr128_kernel<COARSE><<<(unsigned)rows, kWave, nb * sizeof(int32_t), stream>>>(
+    dkdv<<<(unsigned)rows, kWave, lists, stream>>>(
         A.k, A.v, A.q, A.dout, A.bits, order, A.bias, A.dkp, A.dvp, A.dk, A.dv, nb, rows, scale, scale_log2);
   } else {
     if (!one_launch) {

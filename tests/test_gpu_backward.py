@@ -287,27 +287,28 @@ def test_backward_long_sequence_full_head(gpu):
         assert worst[name + "_row"] <= GRAD_ROW_TOL[w.dtype], (name, worst)
 
 
-@pytest.mark.parametrize("n,m", [(8224, 3), (9216, 288)])
-def test_backward_columns_by_list_length_bf16_d128(gpu, n, m):
+@pytest.mark.parametrize("H,n,m", [(2, 8224, 3), (2, 9216, 288), (15, 9216, 288), (16, 8224, 16), (17, 8224, 17)])
+def test_backward_columns_by_list_length_bf16_d128(gpu, H, n, m):
     """Heads at bfloat16 d = 128 whose Q and dZ exceed an XCD's L2 (n > 8192)
-    take the column blocks by falling list length: every block-row is worked on
-    once, whatever the lists (257 blocks with few entries, some columns in no
-    list; 288 blocks all of one length), and the gradients are the bits of the
-    same heads taken one by one in a call of their own."""
-    print("columns by length", n, m, flush=True)
-    q, k, v = inputs.random_qkv(4100 + n, 1, 2, n, 128, "bf16")
+    take the column blocks by falling list length where there are four rounds of
+    them (4096) and 16 tiles a row: every block-row is worked on once, whatever
+    the lists (257 blocks, some columns in no list; 288 blocks all of one length),
+    and the gradients are the bits of the same heads taken one by one in a call of
+    their own, whose column blocks run in their own order (as those of two heads)."""
+    print("columns by length", H, n, m, flush=True)
+    q, k, v = inputs.random_qkv(4100 + n, 1, H, n, 128, "bf16")
     g = inputs.round_to_bf16(np.random.Generator(np.random.PCG64(n)).standard_normal(q.shape))
     tq, tk, tv, tg = (dev(a, "bf16") for a in (q, k, v, g))
     nb = n // 32
-    idx = torch.empty(1, 2, nb, m, dtype=torch.int32, device="cuda")
-    lse = torch.empty(1, 2, n, device="cuda")
+    idx = torch.empty(1, H, nb, m, dtype=torch.int32, device="cuda")
+    lse = torch.empty(1, H, n, device="cuda")
     out = gpu.attention_forward(tq, tk, tv, m, idx_out=idx, lse_out=lse)
     grads = gpu.attention_backward(tq, tk, tv, out, tg, lse, idx)
-    h = 1
-    one = [t[:, h:h + 1].clone() for t in (tq, tk, tv, out, tg, lse, idx)]
-    alone = gpu.attention_backward(*one)
-    for a, b in zip(grads, alone):
-        assert torch.equal(a[:, h:h + 1], b)
+    for h in range(H):
+        one = [t[:, h:h + 1].clone() for t in (tq, tk, tv, out, tg, lse, idx)]
+        alone = gpu.attention_backward(*one)
+        for a, b in zip(grads, alone):
+            assert torch.equal(a[:, h:h + 1], b), h
     # dV against float64 on the head: dV = A^T dZ
     f = lambda t: t[0].double()
     qd, kd, vd, gd = (f(one[i])[0] for i in (0, 1, 2, 4))
