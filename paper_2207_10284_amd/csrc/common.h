@@ -157,17 +157,17 @@ inline long long resident_items(Kernel kernel, int threads, size_t smem, int ite
 
 // Waves that share a block-row (or column block) of up to m tiles in the tile
 // passes, so that few rows still occupy the chip: four up to one row per CU, two
-// up to four rows per CU. Every wave of a row holds its fixed operand and stages
-// its list and the sums are added at the end, so beyond that it costs more than
-// it gives. Measured per call (GPU time, us; 1, 2 and 4 waves per row):
-//   16 rows, float32 d = 64, 4 tiles, forward:      21.5  17.0  16.4
-//   192 rows, bfloat16 d = 64, 8 tiles, training:   48.1  40.0  38.8
-//   256 rows, bfloat16 d = 64, 16 tiles, training:  64.7  48.9  44.5
-//   768 rows, bfloat16 d = 64, 16 tiles, training:  70.9  63.6  69.1
-//   1024 rows, bfloat16 d = 64, 16 tiles, forward:  25.2  23.8  26.6
-//   1536 rows, bfloat16 d = 64, 8 tiles, training:  66.6  70.0  81.2
-inline int row_split(long long rows, int m) {
-  if (m < 2 || rows > 4 * kCus) return 1;
+// up to `per_cu` rows per CU. Every wave of a row holds its fixed operand and
+// stages its list and the sums are added at the end, so beyond that it costs more
+// than it gives. The gradient passes gain up to four rows per CU at any m
+// (backward, GPU time, us; 1, 2 and 4 waves per row):
+//   192 rows, bfloat16 d = 64, 8 tiles:    32.1  20.2  19.7
+//   256 rows, bfloat16 d = 64, 16 tiles:   51.1  32.7  28.9
+//   768 rows, bfloat16 d = 64, 2 tiles:    28.3  22.9  29.6
+//   1024 rows, bfloat16 d = 32, 2 tiles:   24.1  21.7  22.8
+//   1024 rows, bfloat16 d = 64, 16 tiles:  57.4  47.5  54.6
+inline int row_split(long long rows, int m, int per_cu = 4) {
+  if (m < 2 || rows > per_cu * kCus) return 1;
   return rows <= kCus && m >= 3 ? 4 : 2;
 }
 

@@ -657,7 +657,23 @@ __global__ __launch_bounds__(WAVES * kWave) void tile_stream_kernel(
 // and without the wait.
 //
 // Where the block-rows alone leave most of the chip idle, two or four waves
-// share a row (row_split).
+// share a row (row_split). The fewer its tiles, the fewer rows it takes for the
+// sharing to cost more than it gives, at bfloat16, whose tiles are short, and at
+// d = 128, where the shared rows' kernels hold two waves per SIMD, first.
+// Forward, GPU time, us; 1 and 2 waves per row (512 and 1024 rows in heads of
+// 128 blocks, 768 in heads of 16):
+//             512 rows       768 rows                        1024 rows
+//   tiles     2              2          4          8          2          4          8
+//   bf16  32  14.2 14.3      13.4 13.4  14.3 13.9  15.8 14.7  14.4 14.6  15.5 15.3  17.0 16.4
+//   bf16  64  16.4 16.3      15.6 15.8  17.2 17.0  18.3 17.5  17.2 17.8  18.4 18.8  20.7 20.2
+//   bf16 128  22.0 21.5      22.7 23.1  25.1 25.2  28.2 27.0  26.6 27.4  29.9 29.5  31.6 32.2
+//   f32   32  16.0 15.7      15.9 16.0  18.0 17.7  22.1 20.8  16.6 17.0  20.0 20.0  23.6 22.6
+//   f32   64  20.7 20.0      21.7 21.3  26.5 25.0  32.9 31.2  25.3 25.6  29.1 30.3  37.6 36.8
+template <int DT, int D>
+static int shared_rows_per_cu(int m) {
+  if (m >= 8) return D == 128 ? 3 : 4;
+  return DT == F32 || m >= 4 ? 3 : 2;
+}
 template <int DT, int D, bool COARSE, int HALVES, int SPLIT>
 static void launch_stream_s(const void* q, const void* k, const void* v, const int32_t* idx,
                             const float* cmax, const float* csum, const float* cvec, void* out,
@@ -684,7 +700,7 @@ static void launch_stream_c(const void* q, const void* k, const void* v, const i
                             const float* cmax, const float* csum, const float* cvec, void* out,
                             float* lse, long long bh, int n, int m, float scale_log2, hipStream_t stream) {
   if constexpr (HALVES == 1) {
-    const int split = row_split(bh * (n / kBlock), m);
+    const int split = row_split(bh * (n / kBlock), m, shared_rows_per_cu<DT, D>(m));
     if (split == 4)
       return launch_stream_s<DT, D, COARSE, 1, 4>(q, k, v, idx, cmax, csum, cvec, out, lse, bh, n, m, scale_log2, stream);
     if (split == 2)
