@@ -33,7 +33,7 @@ ROOT = os.path.dirname(os.path.abspath(__file__))
 sys.path.insert(0, ROOT)
 
 PEAK_BF16_TFLOPS = 2500.0      # MI355X dense bf16 matrix peak
-PEAK_F32_TFLOPS = 157.3        # MI355X fp32 matrix / vector peak
+PEAK_F32_TFLOPS = PEAK_BF16_TFLOPS / 6   # a float32 tile product is six of bfloat16 planes on the same cores
 PEAK_HBM_GBS = 8000.0          # MI355X HBM3E
 
 

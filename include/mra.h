@@ -40,7 +40,10 @@
  * - Q/K/V/output element type is `dtype` (float32 or bfloat16). Pooled rows,
  *   coarse logits and the coarse term are float32. Fine products accumulate in
  *   float32 (bfloat16 inputs feed bfloat16 matrix-core products; float32
- *   operands enter as sums of three bfloat16 values); coarse logits accumulate in float64 and are rounded once to float32.
+ *   operands enter as sums of three bfloat16 values, exact for magnitudes from
+ *   2^-110 on; of a smaller one, also of a logit's gradient, what is below 2^-126
+ *   may be lost); coarse logits accumulate in float64 and are rounded once to
+ *   float32.
  * - The scale c = 1/sqrt(d) is applied to both the fine and the coarse logits.
  * - Results for non-finite inputs are unspecified.
  *

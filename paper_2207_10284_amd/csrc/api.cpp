@@ -111,7 +111,8 @@ WsLayout ws_layout(long long bh, int nb, int d, int m, mra_dtype_t dtype) {
   L.qp = off; off += pooled;
   L.kp = off; off += pooled;
   L.vp = off; off += pooled;
-  // reserved: part of the size that callers of float32, d = 128 have always given
+  // reserved (float32, d = 128): no kernel uses it, but the size is part of the
+  // interface, and what fits a given buffer or the static scratch stays the same
   if (dtype == MRA_F32 && d == 128) off += align256((size_t)2 * bh * nb * kBlockSize * d * sizeof(float));
   L.idx = off; off += align256((size_t)bh * nb * m * sizeof(int32_t));
   L.cmax = off; off += align256((size_t)bh * nb * sizeof(float));

@@ -20,7 +20,8 @@
 // m_x = min_{i in x} L_i keeps both exponentials at most 1: every L_i is at
 // least each coarse logit S~[x,y] + ln b of its own row.
 //
-// Kernels, in launch order (after the packing pass of pool.hip):
+// Kernels, in launch order (for float32 after split_kernel of pool.hip, which
+// writes the planes):
 //  * bwd_rows_kernel: per block-row (a wave; 16 per workgroup): a 256-byte
 //    record of the 32 log normalisers (log2 units) and the 32 deltas, the
 //    selection as a bitmap; with the coarse
@@ -35,9 +36,13 @@
 //    tiles the row pass also writes, per query, the bfloat16 triples of
 //    -L_i/c and -delta_i, which enter the products as one more contraction
 //    step, so a lane holding 16 queries needs no per-query registers.
+//  * bwd_tiles_*_kernel: both tile passes in one launch where the rows are few,
+//    without the column pass up to 32 blocks per head.
+//  * bwd_lengths_kernel, bwd_order_kernel: before the column pass of many column
+//    blocks, their order by falling list length.
 // Tile operands: for bfloat16 raw 32-row tiles of the inputs (copied into LDS
 // under a swizzle that serves row and transposed reads); for float32 the same
-// tiles of three bfloat16 planes that the packing pass writes.
+// tiles of three bfloat16 planes.
 #include "common.h"
 #include "kernels.h"
 #include "tile_ops.h"
@@ -1143,15 +1148,15 @@ __global__ __launch_bounds__(kWave) void bwd_dkdv_tr128_kernel(
 }
 
 // ---------------------------------------------------------------------------
-// float32 (on the bfloat16 matrix cores, tile_ops.h). The packing pass writes
+// float32 (on the bfloat16 matrix cores, tile_ops.h). split_kernel writes
 // Q, K, V and dZ as planes: per 32-row block the hi, mid and lo tiles one after
 // the other, each a raw bfloat16 tile of the layout above, so a wave reads its
 // operands as planes and splits only the 16 values it computes per tile.
 // The float32 matrix instructions bounded these passes and their operands in
-// registers left one wave per SIMD at d = 128. Measured before -> after, packing
-// included: 32 heads x 4096 x 32, budget 8 (small-4096): dQ 81 -> 47, dK/dV
-// 136 -> 70, packing 29 -> 26 us; 32 heads x 1504 x 128, budget 8: dQ 197 -> 85,
-// dK/dV 473 -> 117, packing 33 -> 37 us.
+// registers left one wave per SIMD at d = 128. Measured before -> after, the
+// copies in operand order and the planes included: 32 heads x 4096 x 32, budget 8 (small-4096): dQ 81 -> 47, dK/dV
+// 136 -> 70, copies / planes 29 -> 26 us; 32 heads x 1504 x 128, budget 8: dQ 197 -> 85,
+// dK/dV 473 -> 117, copies / planes 33 -> 37 us.
 //
 // Both passes give a block-row or column block to a pair of waves that walk
 // its tiles together, each wave holding one fixed operand. The tile's planes

@@ -29,8 +29,8 @@ mra_status_t forward_enqueue(const void* q, const void* k, const void* v, void* 
 // error (mra_last_hip_error) and returns MRA_ERR_HIP.
 mra_status_t hip_error_status(hipError_t e);
 
-// q, k, v, g ([bh, n, d] float32) as three bfloat16 planes each (bwd.hip): per
-// 32-row block the hi, mid and lo tiles (32 x d, row-major) one after the
+// q, k, v, g ([bh, n, d] float32) as three bfloat16 planes each, for the gradient
+// passes: per 32-row block the hi, mid and lo tiles (32 x d, row-major) one after the
 // other, 6 bytes per element.
 hipError_t launch_split(const float* q, const float* k, const float* v, const float* g, void* qpl,
                         void* kpl, void* vpl, void* gpl, long long bh, int n, int d, hipStream_t stream);

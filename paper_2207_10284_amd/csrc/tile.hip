@@ -21,12 +21,11 @@
 //    three bfloat16 planes whose sum they are, and each product is the six
 //    plane products that matter (tile_ops.h). The float32 matrix instructions
 //    (64 cycles for 32x32x2) bounded the tile: 4096 cycles of them at d = 64
-//    against 1730 for the plane products, plus about 2000 of vector work, half
-//    of it the splitting. Measured before -> after: 16 heads x 4096 x 32,
+//    against 1536 for the plane products (48 of 32 cycles), plus about 2000 of
+//    vector work, half of it the splitting. Measured before -> after: 16 heads x 4096 x 32,
 //    budget 8 (small-4096): 47.5 -> 38.9 us; 24 heads x 4096 x 64, budget 16:
 //    127 -> 93.6 us; 32 heads x 1504 x 128, budget 8: 84 (plus 11 for the
-//    copies of K and V in operand order that it needed) -> 66 us. A product's
-//    error against float64 falls from 2.0e-7 to 6.5e-8 (d = 128).
+//    copies of K and V in operand order that it needed) -> 66 us.
 //
 // tile_stream_kernel copies the next selected tile's rows HBM/L2 -> a
 // wave-private LDS slot with direct-to-LDS loads while the current one is

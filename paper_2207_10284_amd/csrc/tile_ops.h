@@ -21,8 +21,11 @@
 // the planes. The six with plane indices p + q <= 2 are formed, the smallest
 // first, and the other three (at most 2^-23 of the product each) dropped. Six
 // 32x32x16 products of 32 cycles do the work of eight 32x32x2 float32 products of
-// 64. Measured against float64 over d = 128: error 6.5e-8 of the result's root
-// mean square, 2.0e-7 for the float32 instruction, whose every step rounds.
+// 64. Relative error of whole calls against float64 (2-norm), with the float32
+// instruction, whose every step rounds, and with the planes: 24 heads x 4096 x 64,
+// four resolutions: 1.9e-6, 0.7e-6; training, 32 heads x 1504 x 128: 2.2e-6, 2.0e-6.
+// The low planes of a value below 2^-110 are no normal bfloat16 numbers: what of
+// it is below 2^-126 may be lost.
 #pragma once
 
 #include "common.h"
