@@ -411,7 +411,7 @@ def test_backward_workspace_bytes(lib):
         want = 7 * al(bh * nb * d * 4) + copies * al(bh * n * d * e) + al(bh * nb * 64 * 4) + bias \
             + al(bh * nb * (nb // 32) * 4) + 2 * al(bh * nb * nb * 4)
         assert f(B, H, n, d, 32, dt) == want
-    # bf16 with d = 128 reads raw tiles too; float32 keeps its rearranged copies
+    # bf16 with d = 128 reads raw tiles too; float32 has its planes there
     want = 7 * al(bh * nb * 128 * 4) + al(bh * nb * 64 * 4) + al(bh * n * 16) \
         + al(bh * nb * (nb // 32) * 4) + 2 * al(bh * nb * nb * 4)
     assert f(B, H, n, 128, 32, 1) == want

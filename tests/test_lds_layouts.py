@@ -10,7 +10,7 @@ transposed layout). This model restates the swizzles of csrc/tile.hip
 the operands of v_mfma_f32_32x32x16_bf16 as the tile pass uses them, and that
 no LDS pass has a bank conflict (64 banks of 4 bytes; 16 lanes per
 ds_read_b128 pass, 32 lanes per ds_read_b64 pass). The GPU parity tests check
-the kernels themselves (the raw path is bit-identical to the packed one).
+the kernels themselves.
 """
 import pytest
 
